@@ -13,6 +13,8 @@
 //                  lines); NVP vectors staged per pass with one frame build per
 //                  site; each thread owns one column and 4 rows and sweeps the
 //                  input rows once (register sliding window);
+//   gather:        tiles of 32 x 8 again, for launches too small to fill the
+//                  chip with strips: the march's sums with one barrier;
 //   march<NVP>:    one workgroup per full-width strip of rows, marching down
 //                  the strip one input row at a time with the accumulators of
 //                  five output rows in registers (each input element is read
@@ -22,6 +24,8 @@
 // with its own L2, and halo rows re-read by the next tile then hit that L2
 // instead of HBM.  The autotuner in the host API times the variants on the
 // caller's shape and keeps the fastest.
+#include <algorithm>
+#include <climits>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -307,6 +311,13 @@ __device__ constexpr int m_shell() {
     return (DX * DX + DX * DY + DY * DY) == 1 ? 0 : (DX * DX + DX * DY + DY * DY) == 3 ? 1 : 2;
 }
 
+// The march and gather kernels write every multiply-add out: where two
+// products are added the compiler may round either one first, and it chose
+// differently from one instantiation to the next.  Spelled out, an output
+// does not depend on the kernel or the vector slot that formed it.
+__device__ __forceinline__ float m_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double m_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // acc (+)= M(dx, dy) u for one stencil offset: exchange of the offset's shell
 // plus, on the first shell, the interfacial DMI term cD [dhat u_z - z (dhat . u)]
 // with dhat = (dx + dy/2, sqrt(3)/2 dy) (lattice coordinates -> Cartesian).
@@ -319,21 +330,41 @@ __device__ __forceinline__ void m_offset(T (&a)[3], const T (&u)[3], const T (&c
         a[1] = cj * u[1];
         a[2] = cj * u[2];
     } else {
-        a[0] += cj * u[0];
-        a[1] += cj * u[1];
-        a[2] += cj * u[2];
+        a[0] = m_fma(cj, u[0], a[0]);
+        a[1] = m_fma(cj, u[1], a[1]);
+        a[2] = m_fma(cj, u[2], a[2]);
     }
     if constexpr (sh == 0) {
         constexpr int px = 2 * DX + DY;  // 2 dhat_x in units of 1/2
         const T dx = px == 2 ? cD : px == -2 ? -cD : px == 1 ? cDh : -cDh;
-        a[0] += dx * u[2];
-        a[2] -= dx * u[0];
+        a[0] = m_fma(dx, u[2], a[0]);
+        a[2] = m_fma(-dx, u[0], a[2]);
         if constexpr (DY != 0) {
             const T dy = DY > 0 ? cDr : -cDr;
-            a[1] += dy * u[2];
-            a[2] -= dy * u[1];
+            a[1] = m_fma(dy, u[2], a[1]);
+            a[2] = m_fma(-dy, u[1], a[2]);
         }
     }
+}
+
+//   ambient vector of frame coordinates (a, b)
+template <class T>
+__device__ __forceinline__ void m_ambient(T a, T b, const T (&e1)[3], const T (&e2)[3], T (&u)[3]) {
+    u[0] = m_fma(a, e1[0], b * e2[0]);
+    u[1] = m_fma(a, e1[1], b * e2[1]);
+    u[2] = m_fma(a, e1[2], b * e2[2]);
+}
+//   centre term: -c u and the anisotropy
+template <class T>
+__device__ __forceinline__ void m_centre(T (&acc)[3], const T (&u)[3], T nc, T cK) {
+    acc[0] = m_fma(nc, u[0], acc[0]);
+    acc[1] = m_fma(nc, u[1], acc[1]);
+    acc[2] += m_fma(cK, u[2], nc * u[2]);
+}
+//   frame coordinate of a
+template <class T>
+__device__ __forceinline__ T m_coord(T f0, T f1, T f2, const T (&a)[3]) {
+    return m_fma(f2, a[2], m_fma(f0, a[0], f1 * a[1]));
 }
 
 // Frame of a unit spin for the march kernel: the Duff et al. basis, with the
@@ -375,6 +406,14 @@ __device__ __forceinline__ T ld_off_nt(const T* __restrict__ base, unsigned byte
 template <class T>
 __device__ __forceinline__ void st_off_nt(T* __restrict__ base, unsigned byte_off, T v) {
     __builtin_nontemporal_store(v, reinterpret_cast<T*>(reinterpret_cast<char*>(base) + byte_off));
+}
+
+// periodic index where one period mostly suffices (the division is left to
+// tiles that overhang a lattice smaller than themselves)
+__device__ __forceinline__ int wrap1(int x, int L) {
+    x += x < 0 ? L : 0;
+    x -= x >= L ? L : 0;
+    return (unsigned)x < (unsigned)L ? x : wrapi(x, L);
 }
 
 // raw buffer stores (stride 0: the range is num_records bytes; a store at
@@ -489,9 +528,7 @@ __global__ __launch_bounds__(XW) void k_hvp_march(Geo g, Coef<T> k, const T* __r
                 a = ract ? a : T(0);
                 bb = ract ? bb : T(0);
             }
-            u[j][0] = a * e1[0] + bb * e2[0];
-            u[j][1] = a * e1[1] + bb * e2[1];
-            u[j][2] = a * e1[2] + bb * e2[2];
+            m_ambient(a, bb, e1, e2, u[j]);
             if (lane) {
                 rb[buf][3 * j + 0][x + 2] = u[j][0];
                 rb[buf][3 * j + 1][x + 2] = u[j][1];
@@ -519,9 +556,7 @@ __global__ __launch_bounds__(XW) void k_hvp_march(Geo g, Coef<T> k, const T* __r
             m_offset<0, -1, false>(acc[SL(1)][j], u[j], cJ, cD, cDh, cDr);
             m_offset<0, 1, false>(acc[SL(-1)][j], u[j], cJ, cD, cDh, cDr);
             m_offset<0, 2, false>(acc[SL(-2)][j], u[j], cJ, cD, cDh, cDr);
-            acc[SL(0)][j][0] += nc * u[j][0];
-            acc[SL(0)][j][1] += nc * u[j][1];
-            acc[SL(0)][j][2] += nc * u[j][2] + cK * u[j][2];
+            m_centre(acc[SL(0)][j], u[j], nc, cK);
         }
         // 2. prefetch row R + 1
         if (it + 1 < nsteps) {
@@ -570,8 +605,8 @@ __global__ __launch_bounds__(XW) void k_hvp_march(Geo g, Coef<T> k, const T* __r
             const unsigned so = row_ok ? (unsigned)(x + g.Lx * yo) * (unsigned)sizeof(T) : BUF_OOB;
 #pragma unroll
             for (int j = 0; j < NVP; ++j) {
-                const T wa = f10 * acc[SL(-2)][j][0] + f11 * acc[SL(-2)][j][1] + f12 * acc[SL(-2)][j][2];
-                const T wb = f20 * acc[SL(-2)][j][0] + f21 * acc[SL(-2)][j][1] + f22 * acc[SL(-2)][j][2];
+                const T wa = m_coord(f10, f11, f12, acc[SL(-2)][j]);
+                const T wb = m_coord(f20, f21, f22, acc[SL(-2)][j]);
                 const unsigned sj = j < nv ? so : BUF_OOB;
                 buf_st_nt<T>(rwb, sj, 2 * j * PB, on ? wa : T(0));
                 buf_st_nt<T>(rwb, sj, (2 * j + 1) * PB, on ? wb : T(0));
@@ -745,9 +780,7 @@ __global__ __launch_bounds__(NT2) void k_hvp_march2(Geo g, Coef<T> k, const T* _
                     a = ract[h] ? a : T(0);
                     bb = ract[h] ? bb : T(0);
                 }
-                u[j][h][0] = a * e1[h][0] + bb * e2[h][0];
-                u[j][h][1] = a * e1[h][1] + bb * e2[h][1];
-                u[j][h][2] = a * e1[h][2] + bb * e2[h][2];
+                m_ambient(a, bb, e1[h], e2[h], u[j][h]);
             }
 #pragma unroll
             for (int cc = 0; cc < 3; ++cc) {
@@ -777,9 +810,7 @@ __global__ __launch_bounds__(NT2) void k_hvp_march2(Geo g, Coef<T> k, const T* _
                 m_offset<0, -1, false>(acc[SL(1)][j][h], u[j][h], cJ, cD, cDh, cDr);
                 m_offset<0, 1, false>(acc[SL(-1)][j][h], u[j][h], cJ, cD, cDh, cDr);
                 m_offset<0, 2, false>(acc[SL(-2)][j][h], u[j][h], cJ, cD, cDh, cDr);
-                acc[SL(0)][j][h][0] += nc * u[j][h][0];
-                acc[SL(0)][j][h][1] += nc * u[j][h][1];
-                acc[SL(0)][j][h][2] += nc * u[j][h][2] + cK * u[j][h][2];
+                m_centre(acc[SL(0)][j][h], u[j][h], nc, cK);
             }
             // column x + 1 is the dx = +1 neighbour of column x, and x the
             // dx = -1 neighbour of x + 1
@@ -845,8 +876,8 @@ __global__ __launch_bounds__(NT2) void k_hvp_march2(Geo g, Coef<T> k, const T* _
                 if constexpr (MASKED) on = cen[cr][MASKED ? 6 : 0][x + h] != T(0);
 #pragma unroll
                 for (int j = 0; j < NVP; ++j) {
-                    const T va = f10 * acc[SL(-2)][j][h][0] + f11 * acc[SL(-2)][j][h][1] + f12 * acc[SL(-2)][j][h][2];
-                    const T vb = f20 * acc[SL(-2)][j][h][0] + f21 * acc[SL(-2)][j][h][1] + f22 * acc[SL(-2)][j][h][2];
+                    const T va = m_coord(f10, f11, f12, acc[SL(-2)][j][h]);
+                    const T vb = m_coord(f20, f21, f22, acc[SL(-2)][j][h]);
                     wa[j][h] = on ? va : T(0);
                     wb[j][h] = on ? vb : T(0);
                 }
@@ -873,12 +904,187 @@ __global__ __launch_bounds__(NT2) void k_hvp_march2(Geo g, Coef<T> k, const T* _
 }
 
 // --------------------------------------------------------------------------
+// gather: one pass over a 32 x 8 tile, one output site per thread
+// --------------------------------------------------------------------------
+// The march walks a strip row by row: at least 12 dependent steps (8 rows and
+// the 4 halo rows), so a launch takes 6 (FP32, one vector a group) to 17 us
+// (four) however little it moves; at one 128x128 state and 12 vectors its 48
+// workgroups took 16.8 us.  Here a workgroup stages its 36 x 12 neighbourhood
+// in one go and gathers (load, convert, one barrier, stencil, store): 4.5 us.
+// A million spins and 4 vectors, wider than the march's rows, take 24.4 us
+// against 34.6 of the 64 x 4 tiles.
+// What it pays is bandwidth and arithmetic: a staged site is read and
+// converted 1.7 times and an output reads 57 LDS values, which costs more
+// than the latency saved once the chip is full (4.2 M site-vectors of FP32:
+// 24.7 us against 23.2 of the march).  `nvg` vectors share one build of the
+// frames; the next vector's coordinates load under the stencil of the
+// current one.  Measured and not kept: two and four output rows per thread
+// (fewer LDS reads, but 142 and 255 VGPRs: 27 and 28 us at 4.2 M).
+//   MORDER: the contributions to an output are added in the march's order
+//   (input rows from above, the same offset order within a row), so both give
+//   the same bits and the choice between them is one of speed alone.
+//   Otherwise the neighbours are summed shell by shell, as the tiled kernels
+//   do: for rows too wide for the march and for the ambient layout, whose
+//   products rounded that way before (a third less error than the march's sum
+//   in FP32, 7e-8 against 1.1e-7).
+//   FRAME: as the march.  Otherwise the ambient layout: u is read as it is
+//   and the output is a - m (m.a) - c u with a = A u.
+template <class T, bool FRAME, bool MORDER, bool MASKED>
+__global__ __launch_bounds__(NT) void k_hvp_gather(Geo g, Coef<T> k, const T* __restrict__ m,
+                                                   const T* __restrict__ c, const uint8_t* __restrict__ mask, int nvec,
+                                                   long long vbs, const T* __restrict__ V, T* __restrict__ W,
+                                                   const int* __restrict__ done, int tiles_x, int tiles_y, int nvg,
+                                                   int ngroups) {
+    if (done != nullptr && *done) return;
+    constexpr int DV = FRAME ? 2 : 3;
+    static_assert(FRAME || !MORDER, "the march has no ambient form");
+    constexpr int SX = TX + 2 * HALO, SS = SX * (TY + 2 * HALO);
+    constexpr int Q = (SS + NT - 1) / NT;  // staged sites per thread
+    __shared__ T su[3][SS];
+    const int lid = xcd_order(true);
+    const int grp = lid % ngroups;
+    const int rest = lid / ngroups;
+    const int tiles = tiles_x * tiles_y;
+    const int b = rest / tiles, t = rest - b * tiles;
+    const int tx0 = (t % tiles_x) * TX, ty0 = (t / tiles_x) * TY;
+    const int j0 = grp * nvg, j1 = min(nvec, j0 + nvg);
+    const size_t N = g.N, off1 = (size_t)b * N;
+    const T* __restrict__ mx = m + 3 * off1;
+    const T* __restrict__ my = mx + N;
+    const T* __restrict__ mz = my + N;
+    const uint8_t* __restrict__ mk = MASKED ? mask + off1 : nullptr;
+    const T* __restrict__ Vj = V + (size_t)b * vbs + (size_t)j0 * DV * N;
+    T* __restrict__ Wj = W + (size_t)b * vbs + (size_t)j0 * DV * N;
+    const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
+    const T cJ[3] = {k.cJ[0], k.cJ[1], k.cJ[2]};
+    const T cD = k.cD, cDh = T(0.5) * k.cD, cDr = T(0.86602540378443864676) * k.cD, cK = k.cK;
+    auto frame = [](T nx, T ny, T nz, T(&e1)[3], T(&e2)[3]) {
+        if constexpr (MORDER)
+            onb_march(nx, ny, nz, e1, e2);
+        else
+            onb(nx, ny, nz, e1, e2);
+    };
+    // staged sites of this thread: index, raw coordinates, frame
+    int ss[Q];
+    bool on[Q];
+    T raw[Q][DV], f1[Q][3], f2[Q][3];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int i = threadIdx.x + q * NT;
+        const int sy = i / SX, sx = i - sy * SX;
+        const int xs = wrap1(tx0 + sx - HALO, g.Lx), ys = wrap1(ty0 + sy - HALO, g.Ly);
+        ss[q] = xs + g.Lx * ys;
+        on[q] = true;
+        if (i < SS) {
+            if constexpr (MASKED) on[q] = mk[ss[q]] != 0;
+#pragma unroll
+            for (int d = 0; d < DV; ++d) raw[q][d] = Vj[d * N + ss[q]];
+            if constexpr (FRAME) frame(mx[ss[q]], my[ss[q]], mz[ss[q]], f1[q], f2[q]);
+        }
+    }
+    // own output: frame (or spin), c, activity
+    const int x = tx0 + lx, y = ty0 + ly;
+    const bool out = x < g.Lx && y < g.Ly;
+    const size_t so = out ? x + (size_t)g.Lx * y : 0;
+    const T oc = c[off1 + so];
+    bool oa = true;
+    if constexpr (MASKED) oa = mk[so] != 0;
+    T o1[3] = {mx[so], my[so], mz[so]}, o2[3];
+    if constexpr (FRAME) frame(mx[so], my[so], mz[so], o1, o2);
+    for (int j = j0; j < j1; ++j) {
+        if (j > j0) __syncthreads();  // the previous vector's reads are done
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int i = threadIdx.x + q * NT;
+            if (i < SS) {
+                if constexpr (FRAME) {
+                    const T a = on[q] ? raw[q][0] : T(0), bb = on[q] ? raw[q][1] : T(0);
+                    T u[3];
+                    m_ambient(a, bb, f1[q], f2[q], u);
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) su[d][i] = u[d];
+                } else {
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) su[d][i] = on[q] ? raw[q][DV == 3 ? d : 0] : T(0);
+                }
+            }
+        }
+        Vj += DV * N;
+        if (j + 1 < j1) {  // the next vector's coordinates load under this one's stencil
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if ((int)threadIdx.x + q * NT < SS)
+#pragma unroll
+                    for (int d = 0; d < DV; ++d) raw[q][d] = Vj[d * N + ss[q]];
+        }
+        __syncthreads();
+        if (out) {
+            T a[3];
+            if constexpr (MORDER) {
+                const int i = ly * SX + lx + 2;  // site of the row above by two, own column
+                auto at = [&](int dx, int dy, T(&u)[3]) {
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) u[d] = su[d][i + (dy + 2) * SX + dx];
+                };
+                T um2[3], um1[3], u0[3], up1[3], up2[3];
+                at(0, -2, u0), at(1, -2, up1), at(2, -2, up2);
+                m_offset<0, -2, true>(a, u0, cJ, cD, cDh, cDr);
+                m_offset<1, -2, false>(a, up1, cJ, cD, cDh, cDr);
+                m_offset<2, -2, false>(a, up2, cJ, cD, cDh, cDr);
+                at(-1, -1, um1), at(0, -1, u0), at(1, -1, up1), at(2, -1, up2);
+                m_offset<0, -1, false>(a, u0, cJ, cD, cDh, cDr);
+                m_offset<1, -1, false>(a, up1, cJ, cD, cDh, cDr);
+                m_offset<2, -1, false>(a, up2, cJ, cD, cDh, cDr);
+                m_offset<-1, -1, false>(a, um1, cJ, cD, cDh, cDr);
+                at(-2, 0, um2), at(-1, 0, um1), at(0, 0, u0), at(1, 0, up1), at(2, 0, up2);
+                m_centre(a, u0, -oc, cK);
+                m_offset<1, 0, false>(a, up1, cJ, cD, cDh, cDr);
+                m_offset<-1, 0, false>(a, um1, cJ, cD, cDh, cDr);
+                m_offset<2, 0, false>(a, up2, cJ, cD, cDh, cDr);
+                m_offset<-2, 0, false>(a, um2, cJ, cD, cDh, cDr);
+                at(-2, 1, um2), at(-1, 1, um1), at(0, 1, u0), at(1, 1, up1);
+                m_offset<0, 1, false>(a, u0, cJ, cD, cDh, cDr);
+                m_offset<1, 1, false>(a, up1, cJ, cD, cDh, cDr);
+                m_offset<-1, 1, false>(a, um1, cJ, cD, cDh, cDr);
+                m_offset<-2, 1, false>(a, um2, cJ, cD, cDh, cDr);
+                at(-2, 2, um2), at(-1, 2, um1), at(0, 2, u0);
+                m_offset<0, 2, false>(a, u0, cJ, cD, cDh, cDr);
+                m_offset<-1, 2, false>(a, um1, cJ, cD, cDh, cDr);
+                m_offset<-2, 2, false>(a, um2, cJ, cD, cDh, cDr);
+                const T wa = m_coord(o1[0], o1[1], o1[2], a);
+                const T wb = m_coord(o2[0], o2[1], o2[2], a);
+                Wj[so] = oa ? wa : T(0);
+                Wj[N + so] = oa ? wb : T(0);
+            } else {
+                const int i = (ly + HALO) * SX + lx + HALO;
+                apply_A_flat<T, SX>(su[0], su[1], su[2], i, k, a);
+                const T u[3] = {su[0][i], su[1][i], su[2][i]};
+                if constexpr (FRAME) {
+                    const T av = o1[0] * u[0] + o1[1] * u[1] + o1[2] * u[2];
+                    const T bv = o2[0] * u[0] + o2[1] * u[1] + o2[2] * u[2];
+                    const T wa = o1[0] * a[0] + o1[1] * a[1] + o1[2] * a[2] - oc * av;
+                    const T wb = o2[0] * a[0] + o2[1] * a[1] + o2[2] * a[2] - oc * bv;
+                    Wj[so] = oa ? wa : T(0);
+                    Wj[N + so] = oa ? wb : T(0);
+                } else {
+                    const T ma = o1[0] * a[0] + o1[1] * a[1] + o1[2] * a[2];
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) Wj[d * N + so] = oa ? a[d] - ma * o1[d] - oc * u[d] : T(0);
+                }
+            }
+        }
+        Wj += DV * N;
+    }
+}
+
+// --------------------------------------------------------------------------
 // variant table
 // --------------------------------------------------------------------------
 static const char* kNames[HVP_NVARIANTS] = {"tiled32x8",          "tiled32x8+xcd",      "tiled64x4+xcd",
                                             "tiled128x2+xcd",     "band128x8/4vec+xcd", "band128x8/2vec+xcd",
                                             "band128x8/1vec+xcd", "march/4vec",         "march/2vec",
-                                            "march/1vec",         "march2/2vec",        "march2/1vec"};
+                                            "march/1vec",         "march2/2vec",        "march2/1vec",
+                                            "gather",             "gather/shell sums"};
 
 const char* hvp_variant_name(int v) { return (v >= 0 && v < HVP_NVARIANTS) ? kNames[v] : "?"; }
 
@@ -895,11 +1101,38 @@ bool hvp_variant_ok(int v, const Geo& g, bool f64) {
     if (v < 0 || v >= HVP_NVARIANTS) return false;
     if (f64 && (v == 4 || v == 7)) return false;
     if (v >= 7 && v <= 9 && !march_fits(g)) return false;
-    if (v >= 10 && !march2_fits(g)) return false;
+    if (v >= 10 && v <= 11 && !march2_fits(g)) return false;
     return true;
 }
 
-int hvp_default_variant(const Geo& g, bool f64) { return march_fits(g) ? (f64 ? 8 : 7) : 2; }
+// The choice without an autotuned or pinned variant: the gather while latency
+// counts and where the march cannot go or idles lanes, then the march.  The
+// line is in site-vectors (batch x sites x vectors), as measured (us: gather /
+// march/2vec / march/4vec):
+//   FP32  0.4 M (24 x 93x61 x 3) 6.5 / 13.4 / 18.4;  1.6 M (24 x 128x128 x 4) 12.5 / 14.1 / 20.6;
+//         3.1 M (512x512 x 12) 19.3 / 24.0 / 24.5;   4.2 M (64 x 128x128 x 4) 24.7 / 23.2 / 24.5;
+//         8.4 M (8 x 512x512 x 4) 43 / 42 / 40;      16.8 M (256 x 128x128 x 4) 117 / 76 / 75
+//   FP64  0.4 M 8.9 / 18.2;  1.1 M (64 x 64x64 x 4) 14.4 / 14.0;  1.6 M 20.0 / 19.8;  4.2 M 44.0 / 42.3;
+//         rows over 256 (512 threads, one workgroup on a compute unit):  3.1 M 32 / 47;  4.2 M 43 / 38
+// The march has one thread per column of 64, 128, 256 or 512; where under
+// four fifths of them hold one the gather stays ahead:
+//   FP32  7.8 M (400 x 70x70 x 4) 52 / 60 / 73;  11.5 M (128 x 150x150 x 4) 60 / 71 / 78;
+//         14.4 M (40 x 300x300 x 4) 98 / 120 / 164
+//   FP64  4.3 M (12 x 300x300 x 4) 47 / 81;  5 M (256 x 70x70 x 4) 64 / 62;  11.5 M 149 / 134
+// Vectors of a march group: as many as divide the vectors at hand (8.4 M
+// site-vectors of one vector a lattice, march/1vec / 2vec / 4vec: 60 / 70 /
+// 113; three vectors, 14.7 M: 68 / 81 / 79; two, 16.8 M: 115 / 79 / 121);
+// four of them only in the largest launches (67 M: 280 / 266).
+static int hvp_default_variant(const Geo& g, bool f64, int batch, int nvec) {
+    const long long sv = (long long)batch * g.N * nvec;
+    const int cols = g.Lx <= 64 ? 64 : g.Lx <= 128 ? 128 : g.Lx <= 256 ? 256 : 512;
+    const bool full = 5 * g.Lx >= 4 * cols;
+    const long long line = full ? (f64 && g.Lx <= 256 ? 3LL << 19 : 1LL << 22) : f64 ? 1LL << 23 : LLONG_MAX;
+    if (!march_fits(g)) return 13;
+    if (sv < line) return 12;
+    if (nvec == 1 || nvec == 3) return 9;
+    return f64 || sv < (1LL << 24) || nvec % 4 == 1 || nvec % 4 == 2 ? 8 : 7;
+}
 
 template <class T, int TXT, int TYT, bool REMAP>
 static void go_tiled(const Geo& g, const CoefD& kd, int batch, const void* m, const void* c, const uint8_t* mask,
@@ -978,6 +1211,28 @@ static void go_march2(const Geo& g, const CoefD& kd, int batch, const void* m, c
         launch(std::integral_constant<int, 256>{});
 }
 
+// vectors per workgroup: one while the tiles alone do not fill the chip, then
+// up to four to share the frames (three vectors of 24 x 93x61 in FP64: 9.7 us
+// one by one, 8.9 together; 12 of one 128x128: 5.3 and 6.4), in even groups
+template <class T, bool FRAME, bool MORDER>
+static void go_gather(const Geo& g, const CoefD& kd, int batch, const void* m, const void* c, const uint8_t* mask,
+                      int nvec, long long vbs, const void* V, void* W, const int* done, hipStream_t st) {
+    const long long tiles = (long long)batch * g.tiles;
+    const int want = (int)std::min(4LL, std::max(1LL, tiles * nvec / (sizeof(T) == 8 ? 512 : 1536)));
+    const int ngroups = (nvec + want - 1) / want;
+    const int nvg = (nvec + ngroups - 1) / ngroups;
+    const dim3 grid((unsigned)(tiles * ngroups));
+    auto launch = [&](auto mc) {
+        hipLaunchKernelGGL((k_hvp_gather<T, FRAME, MORDER, decltype(mc)::value>), grid, dim3(NT), 0, st, g, coef_cast<T>(kd),
+                           (const T*)m, (const T*)c, mask, nvec, vbs, (const T*)V, (T*)W, done, g.tiles_x, g.tiles_y,
+                           nvg, ngroups);
+    };
+    if (mask)
+        launch(std::true_type{});
+    else
+        launch(std::false_type{});
+}
+
 template <class T>
 static void go(int v, const Geo& g, const CoefD& kd, int batch, const void* m, const void* c, const uint8_t* mask,
                int nvec, long long vbs, const void* V, void* W, const int* done, hipStream_t st) {
@@ -997,6 +1252,8 @@ static void go(int v, const Geo& g, const CoefD& kd, int batch, const void* m, c
         case 9: go_march<T, 1>(g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st); break;
         case 10: go_march2<T, 2>(g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st); break;
         case 11: go_march2<T, 1>(g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st); break;
+        case 12: go_gather<T, true, true>(g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st); break;
+        case 13: go_gather<T, true, false>(g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st); break;
         default: go_tiled<T, 64, 4, true>(g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st); break;
     }
 }
@@ -1004,12 +1261,23 @@ static void go(int v, const Geo& g, const CoefD& kd, int batch, const void* m, c
 hipError_t launch_hvp_frame(int variant, const Geo& g, const CoefD& kd, bool f64, int batch, const void* m,
                             const void* c, const uint8_t* mask, int nvec, const void* V, void* W, const int* done,
                             hipStream_t st, long long vbs) {
-    const int v = hvp_variant_ok(variant, g, f64) ? variant : hvp_default_variant(g, f64);
+    const int v = hvp_variant_ok(variant, g, f64) ? variant : hvp_default_variant(g, f64, batch, nvec);
     if (vbs <= 0) vbs = (long long)nvec * 2 * g.N;
     if (f64)
         go<double>(v, g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st);
     else
         go<float>(v, g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st);
+    return hipGetLastError();
+}
+
+hipError_t launch_hvp_ambient(const Geo& g, const CoefD& kd, bool f64, int batch, const void* m, const void* c,
+                              const uint8_t* mask, int nvec, const void* V, void* W, const int* done,
+                              hipStream_t st) {
+    const long long vbs = (long long)nvec * 3 * g.N;
+    if (f64)
+        go_gather<double, false, false>(g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st);
+    else
+        go_gather<float, false, false>(g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st);
     return hipGetLastError();
 }
 

@@ -117,13 +117,16 @@ hipError_t launch_tangent_hvp_gen(const Geo& g, const CoefD& k, bool f64, bool f
                                   const int* done, hipStream_t st);
 
 // ---- hvp.hip: frame-layout tangent HVP variants (tile shapes / staging) ----
-constexpr int HVP_NVARIANTS = 12;
+constexpr int HVP_NVARIANTS = 14;
 bool hvp_variant_ok(int variant, const Geo& g, bool f64);
-int hvp_default_variant(const Geo& g, bool f64);
 const char* hvp_variant_name(int variant);
 hipError_t launch_hvp_frame(int variant, const Geo& g, const CoefD& k, bool f64, int batch, const void* m,
                             const void* c, const uint8_t* mask, int nvec, const void* V, void* W, const int* done,
                             hipStream_t st, long long vbs = 0);
+// ambient layout, vectors back to back
+hipError_t launch_hvp_ambient(const Geo& g, const CoefD& k, bool f64, int batch, const void* m, const void* c,
+                              const uint8_t* mask, int nvec, const void* V, void* W, const int* done,
+                              hipStream_t st);
 hipError_t launch_hessian_apply(const Geo& g, const CoefD& k, bool f64, int batch, int nvec, const void* V,
                                 void* W, hipStream_t st);
 hipError_t launch_topo_charge(const Geo& g, int batch, const double* m, double* part, hipStream_t st);

@@ -175,30 +175,6 @@ __global__ __launch_bounds__(NT) void k_reduce_partials(const double* __restrict
     }
 }
 
-// --------------------------------------------------------------------------
-// Tangent Hessian-vector product  W_j = M H(m) M V_j  (Methods, HVP operator
-// mode): (H v)_i = P_i (A v)_i - c_i v_i.
-//   FRAME: V, W in frame coordinates [nvec][2][N]; the ambient vector of a
-//   staged site is a e1 + b e2, and the output is (e1.(A u) - c a,
-//   e2.(A u) - c b) (P_i drops out against the tangent basis).
-//   AMBIENT: V, W = [nvec][3][N]; output P_i (A u)_i - c_i u_i.
-// An optional device flag `done` turns the launch into a no-op (used by the
-// eigen-solver once converged).
-// --------------------------------------------------------------------------
-template <class T, bool FRAME>
-__global__ __launch_bounds__(NT) void k_tangent_hvp(Geo g, Coef<T> k, const T* __restrict__ m,
-                                                    const T* __restrict__ c, const uint8_t* __restrict__ mask,
-                                                    int nvec, const T* __restrict__ V, T* __restrict__ W,
-                                                    const int* __restrict__ done) {
-    if (done != nullptr && *done) return;
-    constexpr int DV = FRAME ? 2 : 3;
-    __shared__ HvpLDS<T, FRAME> sh;
-    const TileIdx ti = tile_of(g);
-    const size_t vb = (size_t)ti.b * nvec * DV * g.N;
-    tangent_hvp_tile<T, FRAME>(sh, g, k, m + (size_t)ti.b * 3 * g.N, c + (size_t)ti.b * g.N,
-                               mask ? mask + (size_t)ti.b * g.N : nullptr, nvec, V + vb, W + vb, ti.tx0, ti.ty0);
-}
-
 // Euclidean Hessian apply W_j = A V_j (ambient, unmasked).
 template <class T>
 __global__ __launch_bounds__(NT) void k_hessian_apply(Geo g, Coef<T> k, int nvec, const T* __restrict__ V,
@@ -326,14 +302,7 @@ hipError_t launch_tangent_hvp(const Geo& g, const CoefD& kd, bool f64, bool fram
     if (kd.gen) return launch_tangent_hvp_gen(g, kd, f64, frame, batch, m, c, mask, nvec, vbs, V, W, done, st);
     if (frame) return launch_hvp_frame(variant, g, kd, f64, batch, m, c, mask, nvec, V, W, done, st, vbs);
     if (vbs > 0 && vbs != (long long)nvec * 3 * g.N) return hipErrorInvalidValue;
-    dim3 grid(batch * g.tiles);
-    if (f64)
-        hipLaunchKernelGGL((k_tangent_hvp<double, false>), grid, dim3(NT), 0, st, g, coef_cast<double>(kd),
-                           (const double*)m, (const double*)c, mask, nvec, (const double*)V, (double*)W, done);
-    else
-        hipLaunchKernelGGL((k_tangent_hvp<float, false>), grid, dim3(NT), 0, st, g, coef_cast<float>(kd),
-                           (const float*)m, (const float*)c, mask, nvec, (const float*)V, (float*)W, done);
-    return hipGetLastError();
+    return launch_hvp_ambient(g, kd, f64, batch, m, c, mask, nvec, V, W, done, st);
 }
 
 hipError_t launch_hessian_apply(const Geo& g, const CoefD& kd, bool f64, int batch, int nvec, const void* V,
