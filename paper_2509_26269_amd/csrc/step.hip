@@ -8,6 +8,7 @@
 // one fused pass computes the Gram matrix of {S_0.., Y_0.., G} (after the
 // projection transport of the stored pairs), a one-thread kernel runs the
 // recursion on that small matrix, and one pass forms the direction.
+#include "dense_wg.hpp"
 #include "kernels.hpp"
 
 namespace moto {
@@ -281,10 +282,13 @@ __global__ __launch_bounds__(NT) void k_step_gram(StepArgs a, const double* __re
 #pragma unroll
         for (int q = 0; q < EQ; ++q) {
             if ((int)threadIdx.x + q * NT < ne) {
-                double sacc = 0.0;
-                for (int cc = 0; cc < 3; ++cc)
-                    for (int tt = 0; tt < SCH; ++tt) sacc += stage[ei[q]][cc][tt] * stage[ej[q]][cc][tt];
-                acc[q] += sacc;
+                // a chain of dependent adds per component
+                double s3[3] = {0.0, 0.0, 0.0};
+#pragma unroll 4
+                for (int tt = 0; tt < SCH; ++tt)
+#pragma unroll
+                    for (int cc = 0; cc < 3; ++cc) s3[cc] += stage[ei[q]][cc][tt] * stage[ej[q]][cc][tt];
+                acc[q] += (s3[0] + s3[1]) + s3[2];
             }
         }
         __syncthreads();
@@ -301,111 +305,149 @@ __global__ __launch_bounds__(NT) void k_step_gram(StepArgs a, const double* __re
     if (threadIdx.x == 0) pg[SNE] = red[0] + red[1] + red[2] + red[3];
 }
 
-// (3) reduce the Gram (one wavefront per entry, fixed-order sums), then one
-// thread: stop test, two-loop recursion in coefficient space, reset test;
-// writes the direction coefficients.
-__global__ __launch_bounds__(NT) void k_step_ctrl(StepArgs a, StepPtrs P, StepBatch B) {
+// (3) Gram of the step basis summed over the blocks, then on one wavefront:
+// stop test, two-loop recursion in coefficient space, reset test; writes the
+// direction coefficients and the step's outcome.
+//
+// Both halves are latency: one workgroup reads the blocks' partial rows
+// (256 x 154 doubles at 128x128 with 8 pairs) and the recursion is a chain of
+// 2 x 8 dot products of length 17.  A lane takes one entry and walks the rows
+// (coalesced, eight loads in flight, the rows split over the waves that the
+// entries leave free), and lane i of wave 0 holds component i of the
+// recursion's vector, so that a dot product is one cross-lane sum.  The
+// earlier form (a wave per entry, the lanes over the rows; the recursion on
+// one thread) took 45 us a call on average over sixteen steps at 128x128, up
+// to 67 with 8 pairs.
+constexpr int CTN = 1024;  // threads
+__global__ __launch_bounds__(CTN) void k_step_ctrl(StepArgs a, StepPtrs P, double* __restrict__ out, StepBatch B) {
     P = member_ptrs(P, B);
+    out += 2 * blockIdx.y;
     StepHdr* h = P.hdr;
-    if (h->stopped) return;
-    __shared__ double gs[SNE + 1];
+    if (h->stopped) {
+        if (threadIdx.x == 0) {
+            out[0] = h->fnorm;
+            out[1] = 1.0;
+        }
+        return;
+    }
+    __shared__ double ps[CTN];
+    __shared__ double Gm[SNV][SNV];
+    __shared__ double fn2;
     const Ring rg = ring_next(h, a.mem, a.rule);
     const int c = rg.c_new;
     const int nv = 2 * c + 1;
-    const int ne = nv * (nv + 1) / 2;
-    const int lane = threadIdx.x & 63;
-    for (int e = threadIdx.x >> 6; e <= ne; e += NT / 64) {
-        const int ee = e < ne ? e : SNE;  // the last slot is |F_mmf|^2
+    const int ne = nv * (nv + 1) / 2;  // and one more: |F_mmf|^2
+    const int lane = wlane(), wv = threadIdx.x / WL;
+    static_assert((SNE + 1 + WL - 1) / WL <= CTN / WL, "a wave per 64 entries");
+    const int chunks = (ne + 1 + WL - 1) / WL, parts = (CTN / WL) / chunks;
+    const int chunk = wv % chunks, part = wv / chunks;
+    {
+        const int e = chunk * WL + lane, ee = e < ne ? e : SNE;
         double s = 0.0;
-        for (int b = lane; b < P.nblk; b += 64) s += P.pgram[(size_t)b * SPART + ee];
-        s = wave_sum(s);
-        if (lane == 0) gs[ee] = s;
-    }
-    // the serial control below runs on one thread; its arrays live in LDS
-    // (as per-thread arrays indexed at run time they would sit in scratch,
-    // a global-memory round trip per access)
-    __shared__ double Gm[SNV][SNV];
-    __shared__ double coef[SNV], q[SNV], alph[SMEM], rho[SMEM];
-    __shared__ bool valid[SMEM];
-    __syncthreads();
-    // the Gram as a full matrix (every thread decodes its own entries)
-    for (int e = threadIdx.x; e < ne; e += NT) {
-        int p = e, i = 0;
-        while (p >= nv - i) {
-            p -= nv - i;
-            ++i;
+        if (part < parts && e <= ne) {
+            const double* pg = P.pgram + ee;
+#pragma unroll 8
+            for (int b = part; b < P.nblk; b += parts) s += pg[(size_t)b * SPART];
         }
-        Gm[i][i + p] = gs[e];
-        Gm[i + p][i] = gs[e];
+        ps[threadIdx.x] = s;  // wave wv = part * chunks + chunk
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    const double fn = sqrt(gs[SNE]);
-    h->fnorm = fn;
-    h->count = c;
-    h->head = rg.h_new;
-    if (!(fn > a.tau_F)) {  // converged (or NaN): do not move
-        h->stopped = 1;
-        return;
+    if ((int)threadIdx.x <= ne) {
+        const int e = threadIdx.x;
+        double s = 0.0;
+        for (int q = 0; q < parts; ++q) s += ps[q * chunks * WL + e];
+        if (e == ne) {
+            fn2 = s;
+        } else {
+            int p = e, i = 0;
+            while (p >= nv - i) {
+                p -= nv - i;
+                ++i;
+            }
+            Gm[i][i + p] = s;
+            Gm[i + p][i] = s;
+        }
     }
+    __syncthreads();
+    if (threadIdx.x >= WL) return;
+    const double fn = sqrt(fn2);
+    const bool move = fn > a.tau_F;  // else converged (or NaN)
+    if (lane == 0) {
+        h->fnorm = fn;
+        h->count = c;
+        h->head = rg.h_new;
+        out[0] = fn;
+        out[1] = move ? 0.0 : 1.0;
+        if (!move) h->stopped = 1;
+    }
+    if (!move) return;
     const int iG = 2 * c;
-    for (int i = 0; i < nv; ++i) coef[i] = 0.0;
+    const bool in = lane < nv;
+    // lane i: coefficient of vector i
+    double coef = 0.0;
     bool reset = (a.rule == 1);
     if (a.rule == 2) {
         // nonlinear CG (Fletcher-Reeves) on G with one stored pair: S_0 is
         // the transported last step = cg_c x the transported last direction,
         // Y_0 = G - P G_prev, so |P G_prev|^2 = G.G - 2 G.Y_0 + Y_0.Y_0
-        coef[iG] = -a.alpha0;
+        if (lane == iG) coef = -a.alpha0;
         if (c >= 1 && h->iters % CG_RESTART != 0) {
             const double GG = Gm[iG][iG], Gy = Gm[c][iG], yy = Gm[c][c];
             const double gpgp = GG - 2.0 * Gy + yy;
             const double beta = gpgp > 0.0 ? GG / gpgp : 0.0;
             const double bs = beta / h->cg_c;
-            if (-GG + bs * Gm[0][iG] < 0.0) coef[0] = a.alpha0 * bs;
+            if (-GG + bs * Gm[0][iG] < 0.0 && lane == 0) coef = a.alpha0 * bs;
         }
     } else if (a.rule == 0) {
-        for (int i = 0; i < nv; ++i) q[i] = 0.0;
-        q[iG] = 1.0;
-        int newest = -1;
-        for (int j = 0; j < c; ++j) {
-            const double sy = Gm[j][c + j];
-            valid[j] = sy > a.sy_min;
-            rho[j] = valid[j] ? 1.0 / sy : 0.0;
-            if (valid[j]) newest = j;
-        }
+        double q = lane == iG ? 1.0 : 0.0, alph = 0.0;
+        const double sy = lane < c ? Gm[lane][c + lane] : 0.0;  // lane j: pair j
+        const bool valid = lane < c && sy > a.sy_min;
+        const double rho = valid ? 1.0 / sy : 0.0;
+        const unsigned long long vm = __ballot(valid);
         for (int j = c - 1; j >= 0; --j) {
-            if (!valid[j]) continue;
-            double sq = 0.0;
-            for (int i = 0; i < nv; ++i) sq += Gm[j][i] * q[i];
-            alph[j] = rho[j] * sq;
-            q[c + j] -= alph[j];
+            if (!((vm >> j) & 1ull)) continue;
+            const double al = rdlane(rho, j) * wsum_dpp(in ? Gm[j][lane] * q : 0.0);
+            if (lane == j) alph = al;
+            if (lane == c + j) q -= al;
         }
+        const int newest = vm ? 63 - __clzll((long long)vm) : -1;
         const double gamma = newest >= 0 ? Gm[newest][c + newest] / Gm[c + newest][c + newest] : a.alpha0;
-        for (int i = 0; i < nv; ++i) q[i] *= gamma;
+        q *= gamma;
         for (int j = 0; j < c; ++j) {
-            if (!valid[j]) continue;
-            double yr = 0.0;
-            for (int i = 0; i < nv; ++i) yr += Gm[c + j][i] * q[i];
-            const double beta = rho[j] * yr;
-            q[j] += alph[j] - beta;
+            if (!((vm >> j) & 1ull)) continue;
+            const double beta = rdlane(rho, j) * wsum_dpp(in ? Gm[c + j][lane] * q : 0.0);
+            if (lane == j) q += alph - beta;
         }
-        double dG = 0.0;
-        for (int i = 0; i < nv; ++i) {
-            coef[i] = -q[i];
-            dG += coef[i] * Gm[i][iG];
-        }
+        coef = in ? -q : 0.0;
+        const double dG = wsum_dpp(in ? coef * Gm[lane][iG] : 0.0);
         if (!(dG < 0.0)) reset = true;
     }
-    if (reset) {
-        for (int i = 0; i < nv; ++i) coef[i] = 0.0;
-        coef[iG] = -a.alpha0;
-        if (a.rule == 0) h->count = 0;
+    if (reset) coef = lane == iG ? -a.alpha0 : 0.0;
+    if (lane < SNV) h->coef[lane] = coef;
+    if (lane == 0) {
+        if (reset && a.rule == 0) h->count = 0;
+        h->cu = c;
+        h->have_prev = 1;
+        h->iters += 1;
     }
-    for (int i = 0; i < SNV; ++i) h->coef[i] = i < nv ? coef[i] : 0.0;
-    h->cu = c;
 }
 
-// (4) direction d = P(sum coef . vectors) and per-block max |d_i|
+// Threads of the site kernels below: a wave to a workgroup while the blocks
+// then cover the lattice (each of the 256 compute units gets its share of the
+// latency), whole workgroups beyond.
+static int site_threads(int N, int nblk) { return N <= WL * nblk ? WL : NT; }
+
+__device__ __forceinline__ double block_max(double v, double* red /* [NT/64] */) {
+    v = wave_max(v);
+    if (blockDim.x == WL) return v;
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+}
+
+// (4) direction d = P(sum coef . vectors) and per-block max |d_i|.  The pairs
+// are read four at a time, all loads in flight (one pair after another: 5.7
+// us a call at 128x128 with 8 pairs).
 __global__ __launch_bounds__(NT) void k_step_dir(StepArgs a, const double* __restrict__ m, StepPtrs P,
                                                  StepBatch B) {
     P = member_ptrs(P, B);
@@ -413,34 +455,47 @@ __global__ __launch_bounds__(NT) void k_step_dir(StepArgs a, const double* __res
     const StepHdr* h = P.hdr;
     if (h->stopped) return;
     __shared__ double red[NT / 64];
-    const int cu = h->cu;
+    const int cu = h->cu, head = h->head;
+    const size_t N = a.N;
     double mx = 0.0;
-    for (int s = blockIdx.x * NT + threadIdx.x; s < a.N; s += gridDim.x * NT) {
+    for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < a.N; s += gridDim.x * blockDim.x) {
         double d[3] = {0.0, 0.0, 0.0};
-        for (int j = 0; j < cu; ++j) {
-            const int ph = (h->head + j) % a.mem;
-            const double cs = h->coef[j], cy = h->coef[cu + j];
-            if (cs == 0.0 && cy == 0.0) continue;
-            const double* Sj = P.S + ph * P.vstride;
-            const double* Yj = P.Y + ph * P.vstride;
-            for (int cc = 0; cc < 3; ++cc) d[cc] += cs * Sj[cc * a.N + s] + cy * Yj[cc * a.N + s];
+        constexpr int JU = 4;
+        for (int j0 = 0; j0 < cu; j0 += JU) {
+            double sv[JU][3], yv[JU][3];
+#pragma unroll
+            for (int q = 0; q < JU; ++q) {
+                const int j = min(j0 + q, cu - 1);
+                const size_t o = ((head + j) % a.mem) * P.vstride + s;
+#pragma unroll
+                for (int cc = 0; cc < 3; ++cc) {
+                    sv[q][cc] = P.S[o + cc * N];
+                    yv[q][cc] = P.Y[o + cc * N];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < JU; ++q) {
+                if (j0 + q >= cu) break;
+                const double cs = h->coef[j0 + q], cy = h->coef[cu + j0 + q];
+                if (cs == 0.0 && cy == 0.0) continue;
+#pragma unroll
+                for (int cc = 0; cc < 3; ++cc) d[cc] += cs * sv[q][cc] + cy * yv[q][cc];
+            }
         }
         const double cg = h->coef[2 * cu];
-        for (int cc = 0; cc < 3; ++cc) d[cc] += cg * P.G[cc * a.N + s];
-        const double mi[3] = {m[s], m[a.N + s], m[2 * a.N + s]};
+        for (int cc = 0; cc < 3; ++cc) d[cc] += cg * P.G[cc * N + s];
+        const double mi[3] = {m[s], m[N + s], m[2 * N + s]};
         const double md = mi[0] * d[0] + mi[1] * d[1] + mi[2] * d[2];
         double n2 = 0.0;
         for (int cc = 0; cc < 3; ++cc) {
             d[cc] -= md * mi[cc];
-            P.d[cc * a.N + s] = d[cc];
+            P.d[cc * N + s] = d[cc];
             n2 += d[cc] * d[cc];
         }
         mx = fmax(mx, sqrt(n2));
     }
-    mx = wave_max(mx);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
-    __syncthreads();
-    if (threadIdx.x == 0) P.pmax[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    mx = block_max(mx, red);
+    if (threadIdx.x == 0) P.pmax[blockIdx.x] = mx;
 }
 
 // (5) rotation cap and exponential-map rotation of every spin; d -> d_prev,
@@ -461,7 +516,7 @@ __global__ __launch_bounds__(NT) void k_step_rot(StepArgs a, double* __restrict_
     __syncthreads();
     const double sc = scale_s;
     if (a.rule == 2 && blockIdx.x == 0 && threadIdx.x == 0) P.hdr->cg_c = a.alpha0 * sc;
-    for (int s = blockIdx.x * NT + threadIdx.x; s < a.N; s += gridDim.x * NT) {
+    for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < a.N; s += gridDim.x * blockDim.x) {
         double d[3], mi[3];
         double n2 = 0.0;
         for (int cc = 0; cc < 3; ++cc) {
@@ -485,29 +540,16 @@ __global__ __launch_bounds__(NT) void k_step_rot(StepArgs a, double* __restrict_
     }
 }
 
-__global__ void k_step_finish(StepPtrs P, double* __restrict__ out, StepBatch B) {
-    if (threadIdx.x != 0) return;
-    P = member_ptrs(P, B);
-    out += 2 * blockIdx.y;
-    StepHdr* h = P.hdr;
-    out[0] = h->fnorm;
-    out[1] = h->stopped ? 1.0 : 0.0;
-    if (!h->stopped) {
-        h->have_prev = 1;
-        h->iters += 1;
-    }
-}
-
 static hipError_t launch_step_members(const StepArgs& a, double* m, const double* F, const double* V, void* state,
                                       double* out, int members, const StepBatch& B, hipStream_t st) {
     StepPtrs P = step_ptrs(state, a.N, a.mem, nullptr);
     const int nb = P.nblk;
     if (a.k_reflect > 0) hipLaunchKernelGGL(k_step_dots, dim3(nb, members), dim3(NT), 0, st, a, F, V, P, B);
     hipLaunchKernelGGL(k_step_gram, dim3(nb, members), dim3(NT), 0, st, a, m, F, V, P, B);
-    hipLaunchKernelGGL(k_step_ctrl, dim3(1, members), dim3(NT), 0, st, a, P, B);
-    hipLaunchKernelGGL(k_step_dir, dim3(nb, members), dim3(NT), 0, st, a, m, P, B);
-    hipLaunchKernelGGL(k_step_rot, dim3(nb, members), dim3(NT), 0, st, a, m, P, nb, B);
-    hipLaunchKernelGGL(k_step_finish, dim3(1, members), dim3(64), 0, st, P, out, B);
+    hipLaunchKernelGGL(k_step_ctrl, dim3(1, members), dim3(CTN), 0, st, a, P, out, B);
+    const int nt = site_threads(a.N, nb);
+    hipLaunchKernelGGL(k_step_dir, dim3(nb, members), dim3(nt), 0, st, a, m, P, B);
+    hipLaunchKernelGGL(k_step_rot, dim3(nb, members), dim3(nt), 0, st, a, m, P, nb, B);
     return hipGetLastError();
 }
 
