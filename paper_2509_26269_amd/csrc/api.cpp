@@ -270,8 +270,7 @@ namespace {
 // energy_ws(p, batch) bytes), then the fixed-order reduction of E and dE/dtheta
 moto_status energy_grad_into(moto_plan p, moto_dtype dt, int batch, const void* m, const uint8_t* mask, double* E,
                              void* grad, void* c, void* F, double* dE_dtheta, double* part, hipStream_t st) {
-    HIP_TRY(launch_energy_grad(p->g, p->k, dt == MOTO_F64, batch, m, mask, grad, c, F, part, st));
-    if (E || dE_dtheta) HIP_TRY(launch_reduce_partials(part, batch, p->g.tiles, p->ns, E, dE_dtheta, st));
+    HIP_TRY(launch_energy_grad(p->g, p->k, dt == MOTO_F64, batch, m, mask, grad, c, F, part, p->ns, E, dE_dtheta, st));
     return MOTO_OK;
 }
 }  // namespace
@@ -381,8 +380,7 @@ moto_status moto_param_mixed(moto_plan p, moto_dtype dt, int32_t batch, const vo
     if (p->k.gen) return MOTO_EUNSUPPORTED;
     if (!ws || ws_bytes < energy_ws(p, batch)) return MOTO_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    HIP_TRY(launch_param_mixed(p->g, dt == MOTO_F64, batch, m, U, (double*)ws, st));
-    HIP_TRY(launch_reduce_partials((double*)ws, batch, p->g.tiles, p->ns, nullptr, out, st));
+    HIP_TRY(launch_param_mixed(p->g, dt == MOTO_F64, batch, m, U, (double*)ws, p->ns, out, st));
     return MOTO_OK;
 }
 
@@ -399,8 +397,7 @@ moto_status moto_topological_charge(moto_plan p, int32_t batch, const double* m,
     if (!p || !m || !Q || batch < 1) return MOTO_EINVAL;
     if (!ws || ws_bytes < energy_ws(p, batch)) return MOTO_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    HIP_TRY(launch_topo_charge(p->g, batch, m, (double*)ws, st));
-    HIP_TRY(launch_reduce_partials((double*)ws, batch, p->g.tiles, p->ns, Q, nullptr, st));
+    HIP_TRY(launch_topo_charge(p->g, batch, m, (double*)ws, Q, st));
     return MOTO_OK;
 }
 
@@ -484,7 +481,8 @@ static moto_status min_modes_pop_impl(moto_plan p, moto_dtype hvp, int P, const 
     if (c64_in) {
         HIP_TRY(hipMemcpyAsync(c64, c64_in, sizeof(double) * N * (size_t)P, hipMemcpyDeviceToDevice, st));
     } else {
-        HIP_TRY(launch_energy_grad(p->g, p->k, true, P, m, nullptr, nullptr, c64, nullptr, part, st));
+        HIP_TRY(launch_energy_grad(p->g, p->k, true, P, m, nullptr, nullptr, c64, nullptr, part, p->ns, nullptr, nullptr,
+                                   st));
     }
     // the spins are staged in the workspace in the HVP precision (a copy in
     // FP64), so that a captured iteration chunk refers to workspace memory
@@ -752,7 +750,7 @@ moto_status moto_min_modes_lanczos(moto_plan p, moto_dtype hvp, const double* m,
     LzCtrl* ctrl = (LzCtrl*)(ws + L.ctrl);
     void* Q = ws + L.Q;
     const size_t es = f64 ? sizeof(double) : sizeof(float);
-    HIP_TRY(launch_energy_grad(p->g, p->k, true, 1, m, nullptr, nullptr, c64, nullptr, part, st));
+    HIP_TRY(launch_energy_grad(p->g, p->k, true, 1, m, nullptr, nullptr, c64, nullptr, part, p->ns, nullptr, nullptr, st));
     // spins staged in the workspace (see min_modes_pop_impl)
     const void* mT = ws + L.mT;
     const void* cT = c64;
@@ -968,7 +966,8 @@ moto_status moto_descend(moto_plan p, moto_dtype hvp, double* m, const double* v
         // the steps queued past it (all of them with MOTO_ASYNC) change nothing
         const int n = async ? o.max_iter : std::min(every, o.max_iter - it);
         for (int q = 0; q < n; ++q) {
-            HIP_TRY(launch_energy_grad(p->g, p->k, true, 1, m, nullptr, nullptr, nullptr, F, part, st));
+            HIP_TRY(launch_energy_grad(p->g, p->k, true, 1, m, nullptr, nullptr, nullptr, F, part, p->ns, nullptr,
+                                       nullptr, st));
             HIP_TRY(launch_step(a, m, F, nullptr, w + L.state, out, st));
         }
         it += n;
@@ -979,8 +978,7 @@ moto_status moto_descend(moto_plan p, moto_dtype hvp, double* m, const double* v
     }
     // final quantities at the relaxed state
     double* E = (double*)(w + L.ev);
-    HIP_TRY(launch_energy_grad(p->g, p->k, true, 1, m, nullptr, nullptr, nullptr, F, part, st));
-    HIP_TRY(launch_reduce_partials(part, 1, p->g.tiles, p->ns, E, nullptr, st));
+    HIP_TRY(launch_energy_grad(p->g, p->k, true, 1, m, nullptr, nullptr, nullptr, F, part, p->ns, E, nullptr, st));
     // lambda_1 at the relaxed state
     moto_eig_opts eo = o.eig;
     eo.warm = 0;
@@ -990,9 +988,8 @@ moto_status moto_descend(moto_plan p, moto_dtype hvp, double* m, const double* v
     moto_status rs = min_modes_impl(p, hvp, m, nullptr, 1, &eo, E + 1, (double*)(w + L.V), nullptr,
                                     async ? nullptr : &inf, w + L.eig, ws_bytes - L.eig, st, nullptr);
     if (rs != MOTO_OK) return rs;
-    HIP_TRY(launch_topo_charge(p->g, 1, m, part, st));
+    HIP_TRY(launch_topo_charge(p->g, 1, m, part, (double*)(w + L.out) + 2, st));
     double Qd[1];
-    HIP_TRY(launch_reduce_partials(part, 1, p->g.tiles, p->ns, (double*)(w + L.out) + 2, nullptr, st));
     if (async) {
         HIP_TRY(launch_descend_result(w + L.state, N, o.step.mem, out, E, out + 2, (moto_descend_result*)res, st));
         return MOTO_OK;
@@ -1081,7 +1078,7 @@ moto_status moto_saddle_search(moto_plan p, moto_dtype hvp, double* m, const uin
     double ho[2] = {INFINITY, 0.0};
     bool nan = false;
     for (it = 0; it <= o.max_outer; ++it) {
-        HIP_TRY(launch_energy_grad(p->g, p->k, true, 1, m, mask, nullptr, nullptr, F, part, st));
+        HIP_TRY(launch_energy_grad(p->g, p->k, true, 1, m, mask, nullptr, nullptr, F, part, p->ns, nullptr, nullptr, st));
         moto_eig_opts eo = o.eig;
         eo.warm = it == 0 ? 0 : 2;
         eo.flags = 0;  // the driver reads the outcome on the host
@@ -1116,8 +1113,7 @@ moto_status moto_saddle_search(moto_plan p, moto_dtype hvp, double* m, const uin
                                     st, nullptr);
     if (rs != MOTO_OK) return rs;
     n_hvp += inf.n_hvp;
-    HIP_TRY(launch_energy_grad(p->g, p->k, true, 1, m, mask, nullptr, nullptr, F, part, st));
-    HIP_TRY(launch_reduce_partials(part, 1, p->g.tiles, p->ns, out + 2, nullptr, st));
+    HIP_TRY(launch_energy_grad(p->g, p->k, true, 1, m, mask, nullptr, nullptr, F, part, p->ns, out + 2, nullptr, st));
     double hv[3];
     rs = readback(p, out + 2, sizeof(double), hv, st);
     if (rs != MOTO_OK) return rs;
@@ -1247,7 +1243,7 @@ moto_status moto_saddle_search_population(moto_plan p, moto_dtype hvp, int32_t P
     std::vector<long long> n_hvp(P, 0);
     std::vector<moto_info> inf(P);
     for (int it = 0; it <= o.max_outer; ++it) {
-        HIP_TRY(launch_energy_grad(p->g, p->k, true, P, m, mask, nullptr, nullptr, F, part, st));
+        HIP_TRY(launch_energy_grad(p->g, p->k, true, P, m, mask, nullptr, nullptr, F, part, p->ns, nullptr, nullptr, st));
         moto_eig_opts eo = o.eig;
         eo.warm = it == 0 ? 0 : 2;
         eo.flags = 0;  // the driver reads the outcome on the host
@@ -1294,8 +1290,7 @@ moto_status moto_saddle_search_population(moto_plan p, moto_dtype hvp, int32_t P
     moto_status rs = min_modes_pop_impl(p, hvp, P, m, mask, kc, &eo, ev, V, nullptr, inf.data(), eigw, eig_bytes, st,
                                         nullptr);
     if (rs != MOTO_OK) return rs;
-    HIP_TRY(launch_energy_grad(p->g, p->k, true, P, m, mask, nullptr, nullptr, F, part, st));
-    HIP_TRY(launch_reduce_partials(part, P, p->g.tiles, p->ns, E, nullptr, st));
+    HIP_TRY(launch_energy_grad(p->g, p->k, true, P, m, mask, nullptr, nullptr, F, part, p->ns, E, nullptr, st));
     std::vector<double> hE(P), hev((size_t)P * kc);
     rs = readback(p, E, sizeof(double) * (size_t)P, hE.data(), st);
     if (rs != MOTO_OK) return rs;
@@ -1676,13 +1671,10 @@ moto_status moto_explorer_objectives(moto_plan p, moto_dtype hvp, int32_t P, con
     // candidates (and one copy of the mask per candidate for the batched HVP)
     HIP_TRY(launch_candidates(N, P, x0, mask, delta, x_out, mrep, st));
     // energies and c = m . g of every candidate
-    HIP_TRY(launch_energy_grad(p->g, p->k, true, P, x_out, nullptr, nullptr, c, nullptr, part, st));
-    HIP_TRY(launch_reduce_partials(part, P, p->g.tiles, p->ns, E, nullptr, st));
+    HIP_TRY(launch_energy_grad(p->g, p->k, true, P, x_out, nullptr, nullptr, c, nullptr, part, p->ns, E, nullptr, st));
     // topological charges of the candidates, then of x0
-    HIP_TRY(launch_topo_charge(p->g, P, x_out, part, st));
-    HIP_TRY(launch_reduce_partials(part, P, p->g.tiles, p->ns, Qv, nullptr, st));
-    HIP_TRY(launch_topo_charge(p->g, 1, x0, part, st));
-    HIP_TRY(launch_reduce_partials(part, 1, p->g.tiles, p->ns, Qv + P, nullptr, st));
+    HIP_TRY(launch_topo_charge(p->g, P, x_out, part, Qv, st));
+    HIP_TRY(launch_topo_charge(p->g, 1, x0, part, Qv + P, st));
     // l1 distances to S u A
     HIP_TRY(launch_l1(3LL * N, P, n_archive, x_out, archive, (double*)(w + L.l1), Db, st));
     // the k lowest modes of every candidate, in lock step

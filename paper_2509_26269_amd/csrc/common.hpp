@@ -58,6 +58,21 @@ __device__ __forceinline__ int wrapi(int x, int L) {
     return r < 0 ? r + L : r;
 }
 
+// periodic index where one period mostly suffices (the division is left to
+// tiles that overhang a lattice smaller than themselves)
+__device__ __forceinline__ int wrap1(int x, int L) {
+    x += x < 0 ? L : 0;
+    x -= x >= L ? L : 0;
+    return (unsigned)x < (unsigned)L ? x : wrapi(x, L);
+}
+
+// Workgroup order in which consecutive ones run on one XCD (workgroups are
+// dealt round-robin to the eight XCDs).
+__device__ __forceinline__ int xcd_order(bool remap) {
+    const int G = gridDim.x;
+    return (remap && G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
+}
+
 // Orthonormal tangent basis of Duff et al. (JCGT 2017) for a unit vector n.
 template <class T>
 __device__ __forceinline__ void onb(T nx, T ny, T nz, T e1[3], T e2[3]) {

@@ -32,11 +32,6 @@
 
 namespace moto {
 
-__device__ __forceinline__ int xcd_order(bool remap) {
-    const int G = gridDim.x;
-    return (remap && G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
-}
-
 // (A u) at flat LDS index ci of three planes with row stride SX; offsets of
 // the first three shells and the NN interfacial DMI as in apply_A_tile.
 template <class T, int SX>
@@ -406,14 +401,6 @@ __device__ __forceinline__ T ld_off_nt(const T* __restrict__ base, unsigned byte
 template <class T>
 __device__ __forceinline__ void st_off_nt(T* __restrict__ base, unsigned byte_off, T v) {
     __builtin_nontemporal_store(v, reinterpret_cast<T*>(reinterpret_cast<char*>(base) + byte_off));
-}
-
-// periodic index where one period mostly suffices (the division is left to
-// tiles that overhang a lattice smaller than themselves)
-__device__ __forceinline__ int wrap1(int x, int L) {
-    x += x < 0 ? L : 0;
-    x -= x >= L ? L : 0;
-    return (unsigned)x < (unsigned)L ? x : wrapi(x, L);
 }
 
 // raw buffer stores (stride 0: the range is num_records bytes; a store at

@@ -89,15 +89,15 @@ inline Coef<T> coef_cast(const CoefD& d) {
 }
 
 // ---- stencil.hip ----
+// Energy/gradient of a batch; E [batch] and dth [batch][2 ns + 4] or null.
+// part: scratch for the per-tile sums, NPART doubles a tile.
 hipError_t launch_energy_grad(const Geo& g, const CoefD& k, bool f64, int batch, const void* m,
-                              const uint8_t* mask, void* grad, void* c, void* F, double* part,
-                              hipStream_t st);
-hipError_t launch_param_mixed(const Geo& g, bool f64, int batch, const void* m, const void* U, double* part,
-                              hipStream_t st);
+                              const uint8_t* mask, void* grad, void* c, void* F, double* part, int ns, double* E,
+                              double* dth, hipStream_t st);
+hipError_t launch_param_mixed(const Geo& g, bool f64, int batch, const void* m, const void* U, double* part, int ns,
+                              double* out, hipStream_t st);
 hipError_t launch_param_grad_apply(const Geo& g, int ns, bool f64, int batch, const void* m, const double* w,
                                   void* out, hipStream_t st);
-hipError_t launch_reduce_partials(const double* part, int batch, int tiles, int ns, double* E, double* dth,
-                                  hipStream_t st);
 // Device address of this GPU's copy of the energy scratch array (looked up once
 // per device with that device current); ENERGY_SCRATCH_BYTES long.
 constexpr size_t ENERGY_SCRATCH_BYTES = MOTO_NOALLOC_SCRATCH_BYTES;
@@ -110,6 +110,7 @@ hipError_t launch_tangent_hvp(const Geo& g, const CoefD& k, bool f64, bool frame
                               const int* done, hipStream_t st, int variant = -1, long long vbs = 0);
 
 // ---- shells.hip: general-shell lattice kernels (more than three shells) ----
+// part: the energy of each tile
 hipError_t launch_energy_grad_gen(const Geo& g, const CoefD& k, bool f64, int batch, const void* m,
                                   const uint8_t* mask, void* grad, void* c, void* F, double* part, hipStream_t st);
 hipError_t launch_tangent_hvp_gen(const Geo& g, const CoefD& k, bool f64, bool frame, int batch, const void* m,
@@ -129,7 +130,7 @@ hipError_t launch_hvp_ambient(const Geo& g, const CoefD& k, bool f64, int batch,
                               hipStream_t st);
 hipError_t launch_hessian_apply(const Geo& g, const CoefD& k, bool f64, int batch, int nvec, const void* V,
                                 void* W, hipStream_t st);
-hipError_t launch_topo_charge(const Geo& g, int batch, const double* m, double* part, hipStream_t st);
+hipError_t launch_topo_charge(const Geo& g, int batch, const double* m, double* part, double* Q, hipStream_t st);
 
 // ---- lobpcg.hip ----
 // Control block of one eigen-solve, resident in device memory.

@@ -74,15 +74,15 @@ __device__ __forceinline__ void apply_A_gen(const GenLDS<T>& L, const GenShells&
     a[2] += k.cK * L.u[2][cy][cx];
 }
 
-// Energy, gradient, c, F of the general-shell Hamiltonian; partial slot 0 of
-// each tile holds sum_i (1/2 m_i.(A m)_i - B.m_i), the others are zero.
+// Energy, gradient, c, F of the general-shell Hamiltonian; part[tile] =
+// sum_i (1/2 m_i.(A m)_i - B.m_i).
 template <class T>
 __global__ __launch_bounds__(NT) void k_energy_grad_gen(Geo g, GenShells gs, Coef<T> k, const T* __restrict__ m,
                                                         const uint8_t* __restrict__ mask, T* __restrict__ grad,
                                                         T* __restrict__ cout, T* __restrict__ F,
                                                         double* __restrict__ part) {
     __shared__ GenLDS<T> L;
-    __shared__ double red[NPART * (NT / 64)];
+    __shared__ double red[NT / 64];
     const GenTile t = gen_tile(g);
     const int R = gs.R, W = TX + 2 * R, H = TY + 2 * R;
     const size_t N = g.N;
@@ -98,9 +98,7 @@ __global__ __launch_bounds__(NT) void k_energy_grad_gen(Geo g, GenShells gs, Coe
     __syncthreads();
     const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
     const int x = t.tx0 + lx, y = t.ty0 + ly;
-    double v[NPART];
-#pragma unroll
-    for (int q = 0; q < NPART; ++q) v[q] = 0.0;
+    double v[1] = {0.0};
     if (x < g.Lx && y < g.Ly) {
         const int cx = lx + R, cy = ly + R;
         const size_t s = (size_t)t.b * N + x + (size_t)g.Lx * y;
@@ -125,9 +123,8 @@ __global__ __launch_bounds__(NT) void k_energy_grad_gen(Geo g, GenShells gs, Coe
         const double bm = (double)k.B[0] * mi[0] + (double)k.B[1] * mi[1] + (double)k.B[2] * mi[2];
         v[0] = 0.5 * mam - bm;
     }
-    block_sum<NPART>(v, red);
-    if (threadIdx.x == 0)
-        for (int q = 0; q < NPART; ++q) part[(size_t)blockIdx.x * NPART + q] = v[q];
+    block_sum<1>(v, red);
+    if (threadIdx.x == 0) part[blockIdx.x] = v[0];
 }
 
 // Tangent HVP (frame or ambient layout, as the three-shell tile kernel):

@@ -5,6 +5,7 @@
 // wrap at the halo) and evaluates the three-shell stencil of the spin
 // Hamiltonian (Methods, Eq. param-hamiltonian) at one site per thread.
 #include <mutex>
+#include <type_traits>
 
 #include "kernels.hpp"
 #include "tile_ops.hpp"
@@ -13,13 +14,14 @@ namespace moto {
 
 // Map a block to (lattice b, tile origin).
 struct TileIdx {
-    int b, tx0, ty0;
+    int id, b, tx0, ty0;
 };
 
-__device__ __forceinline__ TileIdx tile_of(const Geo& g) {
+__device__ __forceinline__ TileIdx tile_of(const Geo& g, int id) {
     TileIdx r;
-    r.b = blockIdx.x / g.tiles;
-    const int t = blockIdx.x - r.b * g.tiles;
+    r.id = id;
+    r.b = id / g.tiles;
+    const int t = id - r.b * g.tiles;
     r.tx0 = (t % g.tiles_x) * TX;
     r.ty0 = (t / g.tiles_x) * TY;
     return r;
@@ -27,30 +29,168 @@ __device__ __forceinline__ TileIdx tile_of(const Geo& g) {
 
 // --------------------------------------------------------------------------
 // Energy, gradient, c, F and parameter partials.
-// Per-block partial sums (FP64) of
+// Sums (FP64) over the sites of
 //   [e_i, -m.S_0, -m.S_1, -m.S_2, m.Q_0, m.Q_1, m.Q_2, -m_z^2, -m_x, -m_y, -m_z]
 // with e_i = 1/2 m_i.(A m)_i - B.m_i, so that E = sum_i e_i and
 // dE/dJ_s = -sum_i m_i.S_s, dE/dD_s = sum_i m_i.Q_s, dE/dK = -sum m_z^2,
-// dE/dB = -sum m.
+// dE/dB = -sum m.  NP: how many of them the caller asked for (0 none, 1 the
+// energy, NPART all).  The parameter sums cost more than the field itself
+// (the unit-strength shells again and eleven block reductions): on 64 x
+// 128x128 FP64 states with all vector outputs the call took 44 us with them
+// always formed.
 // --------------------------------------------------------------------------
+template <class T, int NP>
+__device__ __forceinline__ void energy_site(const TileLDS<T>& t, int cx, int cy, int s, const Geo& g, const Coef<T>& k,
+                                            const uint8_t* __restrict__ mk, T* __restrict__ gb, T* __restrict__ cb,
+                                            T* __restrict__ fb, double* v) {
+    T a[3];
+    apply_A_tile(t, cx, cy, k, a);
+    const T mi[3] = {t.u[0][cy][cx], t.u[1][cy][cx], t.u[2][cy][cx]};
+    const T gi[3] = {a[0] - k.B[0], a[1] - k.B[1], a[2] - k.B[2]};
+    const T ci = mi[0] * gi[0] + mi[1] * gi[1] + mi[2] * gi[2];
+    const size_t N = g.N;
+    if (gb) {
+        gb[s] = gi[0];
+        gb[N + s] = gi[1];
+        gb[2 * N + s] = gi[2];
+    }
+    if (cb) cb[s] = ci;
+    if (fb) {
+        const bool act = mk == nullptr || mk[s] != 0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) fb[c * N + s] = act ? -(gi[c] - ci * mi[c]) : T(0);
+    }
+    if constexpr (NP > 0) {
+        const double mam = (double)mi[0] * a[0] + (double)mi[1] * a[1] + (double)mi[2] * a[2];
+        const double bm = (double)k.B[0] * mi[0] + (double)k.B[1] * mi[1] + (double)k.B[2] * mi[2];
+        v[0] = 0.5 * mam - bm;
+    }
+    if constexpr (NP == NPART) {
+        T S[3][3], Q[3][3];
+        shell_sums(t, cx, cy, S, Q);
+#pragma unroll
+        for (int sh = 0; sh < 3; ++sh) {
+            v[1 + sh] = -((double)mi[0] * S[sh][0] + (double)mi[1] * S[sh][1] + (double)mi[2] * S[sh][2]);
+            v[4 + sh] = (double)mi[0] * Q[sh][0] + (double)mi[1] * Q[sh][1] + (double)mi[2] * Q[sh][2];
+        }
+        v[7] = -(double)mi[2] * mi[2];
+        v[8] = -(double)mi[0];
+        v[9] = -(double)mi[1];
+        v[10] = -(double)mi[2];
+    }
+}
+
+// spins of one tile and its halo (tid: thread among the tile's NT)
 template <class T>
+__device__ __forceinline__ void stage_spins(TileLDS<T>& t, const Geo& g, const T* __restrict__ mb, int tx0, int ty0,
+                                            int tid) {
+    const size_t N = g.N;
+#pragma unroll
+    for (int q = 0; q < (TILE_SITES + NT - 1) / NT; ++q) {
+        const int i = tid + q * NT;
+        if (i < TILE_SITES) {
+            const int ly = i / LXH, lx = i - ly * LXH;
+            const int s = wrap1(tx0 + lx - HALO, g.Lx) + g.Lx * wrap1(ty0 + ly - HALO, g.Ly);
+            t.u[0][ly][lx] = mb[s];
+            t.u[1][ly][lx] = mb[N + s];
+            t.u[2][ly][lx] = mb[2 * N + s];
+        }
+    }
+}
+
+// the sums of lattice b in their places: E[b] and
+// dtheta[b][.] = (J_0..J_{ns-1}, D_0..D_{ns-1}, K, Bx, By, Bz)
+template <int NP>
+__device__ __forceinline__ void store_sums(const double (&v)[NP], int b, int ns, double* __restrict__ E,
+                                           double* __restrict__ dth) {
+    if (E) E[b] = v[0];
+    if constexpr (NP == NPART) {
+        if (!dth) return;
+        double* o = dth + (size_t)b * (2 * ns + 4);
+        for (int s = 0; s < ns; ++s) {
+            o[s] = v[1 + s];
+            o[ns + s] = v[4 + s];
+        }
+        o[2 * ns] = v[7];
+        o[2 * ns + 1] = v[8];
+        o[2 * ns + 2] = v[9];
+        o[2 * ns + 3] = v[10];
+    }
+}
+
+// One tile per workgroup; the tile's sums go to part[tile][NP].  Consecutive
+// tiles of a lattice run on one XCD, whose L2 then serves the halo rows.
+template <class T, int NP>
 __global__ __launch_bounds__(NT) void k_energy_grad(Geo g, Coef<T> k, const T* __restrict__ m,
                                                     const uint8_t* __restrict__ mask, T* __restrict__ grad,
                                                     T* __restrict__ cout, T* __restrict__ F,
                                                     double* __restrict__ part) {
     __shared__ TileLDS<T> t;
-    __shared__ double red[NPART * (NT / 64)];
-    const TileIdx ti = tile_of(g);
+    __shared__ double red[(NP ? NP : 1) * (NT / 64)];
+    const TileIdx ti = tile_of(g, xcd_order(true));
     const size_t off3 = (size_t)ti.b * 3 * g.N, off1 = (size_t)ti.b * g.N;
-    double v[NPART];
+    stage_spins(t, g, m + off3, ti.tx0, ti.ty0, threadIdx.x);
+    __syncthreads();
+    const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
+    const int x = ti.tx0 + lx, y = ti.ty0 + ly;
+    double v[NP ? NP : 1];
 #pragma unroll
-    for (int q = 0; q < NPART; ++q) v[q] = 0.0;
-    energy_tile(t, g, k, m + off3, mask ? mask + off1 : nullptr, grad ? grad + off3 : nullptr,
-                cout ? cout + off1 : nullptr, F ? F + off3 : nullptr, ti.tx0, ti.ty0, v);
-    block_sum<NPART>(v, red);
-    if (threadIdx.x == 0) {
+    for (int q = 0; q < NP; ++q) v[q] = 0.0;
+    if (x < g.Lx && y < g.Ly)
+        energy_site<T, NP>(t, lx + HALO, ly + HALO, x + g.Lx * y, g, k, mask ? mask + off1 : nullptr,
+                           grad ? grad + off3 : nullptr, cout ? cout + off1 : nullptr, F ? F + off3 : nullptr, v);
+    if constexpr (NP > 0) {
+        block_sum<NP>(v, red);
+        if (threadIdx.x == 0) {
 #pragma unroll
-        for (int q = 0; q < NPART; ++q) part[(size_t)blockIdx.x * NPART + q] = v[q];
+            for (int q = 0; q < NP; ++q) part[(size_t)ti.id * NP + q] = v[q];
+        }
+    }
+}
+
+// One lattice per workgroup, NT threads for each of its (at most four) tiles:
+// the sums stay in the workgroup, so a small lattice is one launch instead of
+// two (the second costs the host and the stream about 2 us each).
+constexpr int ONE_WG_TILES = 4;
+template <class T, int NP>
+__global__ __launch_bounds__(ONE_WG_TILES * NT) void k_energy_grad_wg(Geo g, Coef<T> k, const T* __restrict__ m,
+                                                                      const uint8_t* __restrict__ mask,
+                                                                      T* __restrict__ grad, T* __restrict__ cout,
+                                                                      T* __restrict__ F, int ns,
+                                                                      double* __restrict__ E,
+                                                                      double* __restrict__ dth) {
+    __shared__ TileLDS<T> t[ONE_WG_TILES];
+    constexpr int NV = NP ? NP : 1;
+    __shared__ double red[ONE_WG_TILES * NT / 64][NV];
+    const int b = blockIdx.x, w = threadIdx.x / NT, tid = threadIdx.x % NT;  // tile w of lattice b
+    const int tx0 = (w % g.tiles_x) * TX, ty0 = (w / g.tiles_x) * TY;
+    const size_t off3 = (size_t)b * 3 * g.N, off1 = (size_t)b * g.N;
+    stage_spins(t[w], g, m + off3, tx0, ty0, tid);
+    __syncthreads();
+    const int lx = tid % TX, ly = tid / TX;
+    const int x = tx0 + lx, y = ty0 + ly;
+    double v[NV];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) v[q] = 0.0;
+    if (x < g.Lx && y < g.Ly)
+        energy_site<T, NP>(t[w], lx + HALO, ly + HALO, x + g.Lx * y, g, k, mask ? mask + off1 : nullptr,
+                           grad ? grad + off3 : nullptr, cout ? cout + off1 : nullptr, F ? F + off3 : nullptr, v);
+    if constexpr (NP > 0) {
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const double s = wave_sum(v[q]);
+            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = s;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                double s = 0.0;
+                for (int i = 0; i < (int)blockDim.x / 64; ++i) s += red[i][q];
+                v[q] = s;
+            }
+            store_sums<NV>(v, b, ns, E, dth);
+        }
     }
 }
 
@@ -61,7 +201,7 @@ __global__ __launch_bounds__(NT) void k_param_mixed(Geo g, const T* __restrict__
                                                     double* __restrict__ part) {
     __shared__ TileLDS<T> t;
     __shared__ double red[NPART * (NT / 64)];
-    const TileIdx ti = tile_of(g);
+    const TileIdx ti = tile_of(g, blockIdx.x);
     const size_t off3 = (size_t)ti.b * 3 * g.N;
     const T* mb = m + off3;
     for (int i = threadIdx.x; i < TILE_SITES; i += NT) {
@@ -110,7 +250,7 @@ template <class T>
 __global__ __launch_bounds__(NT) void k_param_grad_apply(Geo g, int ns, const T* __restrict__ m,
                                                          const double* __restrict__ w, T* __restrict__ out) {
     __shared__ TileLDS<T> t;
-    const TileIdx ti = tile_of(g);
+    const TileIdx ti = tile_of(g, blockIdx.x);
     const size_t off3 = (size_t)ti.b * 3 * g.N;
     const T* mb = m + off3;
     for (int i = threadIdx.x; i < TILE_SITES; i += NT) {
@@ -143,36 +283,22 @@ __global__ __launch_bounds__(NT) void k_param_grad_apply(Geo g, int ns, const T*
     ob[2 * g.N + s] = (T)o[2];
 }
 
-// Fixed-order reduction of the per-block partials of each lattice; maps the
-// slots to E[b] and dtheta[b][.] = (J_0..J_{ns-1}, D_0..D_{ns-1}, K, Bx, By, Bz).
+// Fixed-order reduction of the per-tile sums of each lattice.
+template <int NP>
 __global__ __launch_bounds__(NT) void k_reduce_partials(const double* __restrict__ part, int tiles, int ns,
                                                         double* __restrict__ E, double* __restrict__ dth) {
-    __shared__ double red[NPART * (NT / 64)];
+    __shared__ double red[NP * (NT / 64)];
     const int b = blockIdx.x;
-    double v[NPART];
+    double v[NP];
 #pragma unroll
-    for (int q = 0; q < NPART; ++q) v[q] = 0.0;
+    for (int q = 0; q < NP; ++q) v[q] = 0.0;
     for (int i = threadIdx.x; i < tiles; i += NT) {
-        const double* p = part + ((size_t)b * tiles + i) * NPART;
+        const double* p = part + ((size_t)b * tiles + i) * NP;
 #pragma unroll
-        for (int q = 0; q < NPART; ++q) v[q] += p[q];
+        for (int q = 0; q < NP; ++q) v[q] += p[q];
     }
-    block_sum<NPART>(v, red);
-    if (threadIdx.x == 0) {
-        if (E) E[b] = v[0];
-        if (dth) {
-            const int np = 2 * ns + 4;
-            double* o = dth + (size_t)b * np;
-            for (int s = 0; s < ns; ++s) {
-                o[s] = v[1 + s];
-                o[ns + s] = v[4 + s];
-            }
-            o[2 * ns] = v[7];
-            o[2 * ns + 1] = v[8];
-            o[2 * ns + 2] = v[9];
-            o[2 * ns + 3] = v[10];
-        }
-    }
+    block_sum<NP>(v, red);
+    if (threadIdx.x == 0) store_sums<NP>(v, b, ns, E, dth);
 }
 
 // Euclidean Hessian apply W_j = A V_j (ambient, unmasked).
@@ -180,7 +306,7 @@ template <class T>
 __global__ __launch_bounds__(NT) void k_hessian_apply(Geo g, Coef<T> k, int nvec, const T* __restrict__ V,
                                                       T* __restrict__ W) {
     __shared__ TileLDS<T> t;
-    const TileIdx ti = tile_of(g);
+    const TileIdx ti = tile_of(g, blockIdx.x);
     const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
     const int x = ti.tx0 + lx, y = ti.ty0 + ly;
     const int sc = x + g.Lx * y;
@@ -210,16 +336,14 @@ __global__ __launch_bounds__(NT) void k_hessian_apply(Geo g, Coef<T> k, int nvec
 
 // Berg-Luescher charge: per-block partials of -(1/4pi) * sum of the signed
 // solid angles of the two triangles (x,y),(x+1,y),(x,y+1) and
-// (x+1,y),(x+1,y+1),(x,y+1) of every cell (slot 0).
+// (x+1,y),(x+1,y+1),(x,y+1) of every cell.
 __global__ __launch_bounds__(NT) void k_topo_charge(Geo g, const double* __restrict__ m,
                                                     double* __restrict__ part) {
-    __shared__ double red[NPART * (NT / 64)];
-    const TileIdx ti = tile_of(g);
+    __shared__ double red[NT / 64];
+    const TileIdx ti = tile_of(g, blockIdx.x);
     const double* mb = m + (size_t)ti.b * 3 * g.N;
     const int x = ti.tx0 + threadIdx.x % TX, y = ti.ty0 + threadIdx.x / TX;
-    double v[NPART];
-#pragma unroll
-    for (int q = 0; q < NPART; ++q) v[q] = 0.0;
+    double v[1] = {0.0};
     if (x < g.Lx && y < g.Ly) {
         const int x1 = (x + 1) % g.Lx, y1 = (y + 1) % g.Ly;
         const int s00 = x + g.Lx * y, s10 = x1 + g.Lx * y, s01 = x + g.Lx * y1, s11 = x1 + g.Lx * y1;
@@ -241,33 +365,63 @@ __global__ __launch_bounds__(NT) void k_topo_charge(Geo g, const double* __restr
         }
         v[0] = -q / (4.0 * M_PI);
     }
-    block_sum<NPART>(v, red);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int q = 0; q < NPART; ++q) part[(size_t)blockIdx.x * NPART + q] = v[q];
-    }
+    block_sum<1>(v, red);
+    if (threadIdx.x == 0) part[blockIdx.x] = v[0];
 }
 
 // --------------------------------------------------------------------------
 // Launchers
 // --------------------------------------------------------------------------
 
+// sums of every lattice from its per-tile rows of NP
+template <int NP>
+static void reduce_partials(const Geo& g, int batch, const double* part, int ns, double* E, double* dth,
+                            hipStream_t st) {
+    hipLaunchKernelGGL(k_reduce_partials<NP>, dim3(batch), dim3(NT), 0, st, part, g.tiles, ns, E, dth);
+}
+
+template <class T, int NP>
+static void go_energy(const Geo& g, const CoefD& kd, int batch, const void* m, const uint8_t* mask, void* grad,
+                      void* c, void* F, double* part, int ns, double* E, double* dth, hipStream_t st) {
+    const Coef<T> k = coef_cast<T>(kd);
+    if (g.tiles <= ONE_WG_TILES) {
+        hipLaunchKernelGGL((k_energy_grad_wg<T, NP>), dim3(batch), dim3(NT * g.tiles), 0, st, g, k, (const T*)m, mask,
+                           (T*)grad, (T*)c, (T*)F, ns, E, dth);
+        return;
+    }
+    hipLaunchKernelGGL((k_energy_grad<T, NP>), dim3(batch * g.tiles), dim3(NT), 0, st, g, k, (const T*)m, mask,
+                       (T*)grad, (T*)c, (T*)F, part);
+    if constexpr (NP > 0) reduce_partials<NP>(g, batch, part, ns, E, dth, st);
+}
+
 hipError_t launch_energy_grad(const Geo& g, const CoefD& kd, bool f64, int batch, const void* m,
-                              const uint8_t* mask, void* grad, void* c, void* F, double* part,
-                              hipStream_t st) {
-    if (kd.gen) return launch_energy_grad_gen(g, kd, f64, batch, m, mask, grad, c, F, part, st);
-    dim3 grid(batch * g.tiles);
-    if (f64)
-        hipLaunchKernelGGL(k_energy_grad<double>, grid, dim3(NT), 0, st, g, coef_cast<double>(kd),
-                           (const double*)m, mask, (double*)grad, (double*)c, (double*)F, part);
+                              const uint8_t* mask, void* grad, void* c, void* F, double* part, int ns, double* E,
+                              double* dth, hipStream_t st) {
+    if (kd.gen) {
+        if (dth) return hipErrorInvalidValue;
+        const hipError_t e = launch_energy_grad_gen(g, kd, f64, batch, m, mask, grad, c, F, part, st);
+        if (e != hipSuccess) return e;
+        if (E) reduce_partials<1>(g, batch, part, ns, E, nullptr, st);
+        return hipGetLastError();
+    }
+    auto go = [&](auto np) {
+        constexpr int NP = decltype(np)::value;
+        if (f64)
+            go_energy<double, NP>(g, kd, batch, m, mask, grad, c, F, part, ns, E, dth, st);
+        else
+            go_energy<float, NP>(g, kd, batch, m, mask, grad, c, F, part, ns, E, dth, st);
+    };
+    if (dth)
+        go(std::integral_constant<int, NPART>{});
+    else if (E)
+        go(std::integral_constant<int, 1>{});
     else
-        hipLaunchKernelGGL(k_energy_grad<float>, grid, dim3(NT), 0, st, g, coef_cast<float>(kd),
-                           (const float*)m, mask, (float*)grad, (float*)c, (float*)F, part);
+        go(std::integral_constant<int, 0>{});
     return hipGetLastError();
 }
 
-hipError_t launch_param_mixed(const Geo& g, bool f64, int batch, const void* m, const void* U, double* part,
-                              hipStream_t st) {
+hipError_t launch_param_mixed(const Geo& g, bool f64, int batch, const void* m, const void* U, double* part, int ns,
+                              double* out, hipStream_t st) {
     dim3 grid(batch * g.tiles);
     if (f64)
         hipLaunchKernelGGL(k_param_mixed<double>, grid, dim3(NT), 0, st, g, (const double*)m, (const double*)U,
@@ -275,6 +429,7 @@ hipError_t launch_param_mixed(const Geo& g, bool f64, int batch, const void* m, 
     else
         hipLaunchKernelGGL(k_param_mixed<float>, grid, dim3(NT), 0, st, g, (const float*)m, (const float*)U,
                            part);
+    reduce_partials<NPART>(g, batch, part, ns, nullptr, out, st);
     return hipGetLastError();
 }
 
@@ -287,12 +442,6 @@ hipError_t launch_param_grad_apply(const Geo& g, int ns, bool f64, int batch, co
     else
         hipLaunchKernelGGL(k_param_grad_apply<float>, grid, dim3(NT), 0, st, g, ns, (const float*)m, w,
                            (float*)out);
-    return hipGetLastError();
-}
-
-hipError_t launch_reduce_partials(const double* part, int batch, int tiles, int ns, double* E, double* dth,
-                                  hipStream_t st) {
-    hipLaunchKernelGGL(k_reduce_partials, dim3(batch), dim3(NT), 0, st, part, tiles, ns, E, dth);
     return hipGetLastError();
 }
 
@@ -317,8 +466,9 @@ hipError_t launch_hessian_apply(const Geo& g, const CoefD& kd, bool f64, int bat
     return hipGetLastError();
 }
 
-hipError_t launch_topo_charge(const Geo& g, int batch, const double* m, double* part, hipStream_t st) {
+hipError_t launch_topo_charge(const Geo& g, int batch, const double* m, double* part, double* Q, hipStream_t st) {
     hipLaunchKernelGGL(k_topo_charge, dim3(batch * g.tiles), dim3(NT), 0, st, g, m, part);
+    reduce_partials<1>(g, batch, part, 0, Q, nullptr, st);
     return hipGetLastError();
 }
 
