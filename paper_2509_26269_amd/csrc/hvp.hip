@@ -25,7 +25,6 @@
 // instead of HBM.  The autotuner in the host API times the variants on the
 // caller's shape and keeps the fastest.
 #include <algorithm>
-#include <climits>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -1092,33 +1091,53 @@ bool hvp_variant_ok(int v, const Geo& g, bool f64) {
     return true;
 }
 
+// strips per lattice: about `target` workgroups in all (one resident round
+// at the march kernels' occupancy: 1024 of up to 256 threads, 256 of the
+// 512-thread rows), strips of at least 8 rows (the 4 halo rows of a strip
+// are read twice)
+static int march_strips(const Geo& g, int batch, int ngroups, int target) {
+    const long long have = (long long)batch * ngroups;
+    const int want = (int)((target + have - 1) / have);
+    return max(1, min(want, max(1, g.Ly / 8)));
+}
+
 // The choice without an autotuned or pinned variant: the gather while latency
-// counts and where the march cannot go or idles lanes, then the march.  The
-// line is in site-vectors (batch x sites x vectors), as measured (us: gather /
-// march/2vec / march/4vec):
-//   FP32  0.4 M (24 x 93x61 x 3) 6.5 / 13.4 / 18.4;  1.6 M (24 x 128x128 x 4) 12.5 / 14.1 / 20.6;
-//         3.1 M (512x512 x 12) 19.3 / 24.0 / 24.5;   4.2 M (64 x 128x128 x 4) 24.7 / 23.2 / 24.5;
-//         8.4 M (8 x 512x512 x 4) 43 / 42 / 40;      16.8 M (256 x 128x128 x 4) 117 / 76 / 75
-//   FP64  0.4 M 8.9 / 18.2;  1.1 M (64 x 64x64 x 4) 14.4 / 14.0;  1.6 M 20.0 / 19.8;  4.2 M 44.0 / 42.3;
-//         rows over 256 (512 threads, one workgroup on a compute unit):  3.1 M 32 / 47;  4.2 M 43 / 38
-// The march has one thread per column of 64, 128, 256 or 512; where under
-// four fifths of them hold one the gather stays ahead:
-//   FP32  7.8 M (400 x 70x70 x 4) 52 / 60 / 73;  11.5 M (128 x 150x150 x 4) 60 / 71 / 78;
-//         14.4 M (40 x 300x300 x 4) 98 / 120 / 164
-//   FP64  4.3 M (12 x 300x300 x 4) 47 / 81;  5 M (256 x 70x70 x 4) 64 / 62;  11.5 M 149 / 134
-// Vectors of a march group: as many as divide the vectors at hand (8.4 M
-// site-vectors of one vector a lattice, march/1vec / 2vec / 4vec: 60 / 70 /
-// 113; three vectors, 14.7 M: 68 / 81 / 79; two, 16.8 M: 115 / 79 / 121);
-// four of them only in the largest launches (67 M: 280 / 266).
+// counts and where the march cannot go or idles lanes, then the march.
+// The march's group is the one that wastes fewest slots (8.4 M site-vectors of
+// one vector a lattice, FP32, march/1vec / 2vec / 4vec: 60 / 70 / 113 us; three
+// vectors, 14.7 M: 68 / 81 / 79; two, 16.8 M: 115 / 79 / 121; four, 67 M: - /
+// 280 / 266).  Both sides' times are estimated as a start-up plus a rate times
+// the site-vectors that each really works on: whole tiles for the gather,
+// whole rows of threads and the strips' four halo rows for the march.  The
+// rates are fitted to 170 shapes from 12x12 to 1100x1100 (5 - 15 % off for
+// most; the gather must win by a margin), and some of those read (us: gather /
+// march):
+//   FP32  0.4 M site-vectors (24 x 93x61 x 3) 6.5 / 9.5;  1.6 M (24 x 128x128 x 4) 12.5 / 20.6;
+//         4.2 M (64 x 128x128 x 4) 24.7 / 24.5;   16.8 M (256 x 128x128 x 4) 117 / 75;
+//         8.6 M (24 x 300x300 x 4) 47 / 101;      3.5 M (319 x 126x86 x 1) 45 / 28
+//   FP64  0.4 M 8.9 / 18.2;  1.6 M 20.0 / 19.8;  4.2 M 44 / 42;  2.2 M (6 x 300x300 x 4) 26 / 52;
+//         1.4 M (195 x 60x12 x 10) 27 / 20;  6.4 M (404 x 181x88 x 1) 125 / 83
 static int hvp_default_variant(const Geo& g, bool f64, int batch, int nvec) {
-    const long long sv = (long long)batch * g.N * nvec;
-    const int cols = g.Lx <= 64 ? 64 : g.Lx <= 128 ? 128 : g.Lx <= 256 ? 256 : 512;
-    const bool full = 5 * g.Lx >= 4 * cols;
-    const long long line = full ? (f64 && g.Lx <= 256 ? 3LL << 19 : 1LL << 22) : f64 ? 1LL << 23 : LLONG_MAX;
     if (!march_fits(g)) return 13;
-    if (sv < line) return 12;
-    if (nvec == 1 || nvec == 3) return 9;
-    return f64 || sv < (1LL << 24) || nvec % 4 == 1 || nvec % 4 == 2 ? 8 : 7;
+    const int cols = g.Lx <= 64 ? 64 : g.Lx <= 128 ? 128 : g.Lx <= 256 ? 256 : 512;
+    const bool by1 = nvec == 1 || (nvec == 3 && !f64 && cols > 64);
+    const int nvp = by1 ? 1 : f64 || nvec % 4 == 1 || nvec % 4 == 2 ? 2 : 4;
+    const int groups = (nvec + nvp - 1) / nvp;
+    const int strips = march_strips(g, batch, groups, cols > 256 ? 256 : 1024);
+    // millions of site-vectors worked on
+    const double mg = 1e-6 * batch * g.tiles * NT * nvec;
+    const double mm = 1e-6 * batch * cols * (g.Ly + 4.0 * strips) * groups * nvp;
+    const int q = nvec < 4 ? nvec - 1 : 3;
+    static const double gather32[4] = {10.5, 7.6, 6.5, 5.2}, gather64[4] = {17.0, 14.0, 12.5, 11.5};
+    const double tg = 3.0 + (f64 ? gather64[q] : gather32[q]) * mg;
+    double tm;
+    if (f64)
+        tm = nvp == 1 ? 6.0 + 8.0 * mm : 9.0 + 7.0 * mm;
+    else
+        tm = nvp == 1 ? 5.0 + (cols == 64 ? 11.0 : nvec == 1 ? 5.5 : 4.4) * mm : nvp == 2 ? 8.0 + 4.0 * mm
+                                                               : 14.0 + (cols > 256 ? 3.2 : 2.6) * mm;
+    if ((nvp == 4 ? 1.15 : 1.1) * tg < tm) return 12;
+    return nvp == 1 ? 9 : nvp == 2 ? 8 : 7;
 }
 
 template <class T, int TXT, int TYT, bool REMAP>
@@ -1135,16 +1154,6 @@ static void go_band(const Geo& g, const CoefD& kd, int batch, const void* m, con
     const int tx = (g.Lx + BD_TX - 1) / BD_TX, ty = (g.Ly + BD_TY - 1) / BD_TY;
     hipLaunchKernelGGL((k_hvp_band<T, NVP>), dim3(batch * tx * ty), dim3(NT), 0, st, g, coef_cast<T>(kd),
                        (const T*)m, (const T*)c, mask, nvec, vbs, (const T*)V, (T*)W, done, tx, ty);
-}
-
-// strips per lattice: about `target` workgroups in all (one resident round
-// at the march kernels' occupancy: 1024 of up to 256 threads, 256 of the
-// 512-thread rows), strips of at least 8 rows (the 4 halo rows of a strip
-// are read twice)
-static int march_strips(const Geo& g, int batch, int ngroups, int target) {
-    const long long have = (long long)batch * ngroups;
-    const int want = (int)((target + have - 1) / have);
-    return max(1, min(want, max(1, g.Ly / 8)));
 }
 
 template <class T, int NVP, int XW>
