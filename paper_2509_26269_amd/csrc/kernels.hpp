@@ -16,7 +16,7 @@ constexpr int NPART = 11;
 // Shell table of a Hamiltonian with more than three exchange shells: the
 // lattice offsets of every shell (sorted by distance, shell s = offsets
 // [start[s], start[s+1])), the largest |dx|, |dy| (the tile halo) and the
-// stencil coefficients cJ[s] = -2 J_s.  Passed by value as a kernel argument.
+// stencil coefficients cJ[s] = -2 J_s.
 constexpr int GEN_MAX_SHELLS = MOTO_MAX_SHELLS;
 constexpr int GEN_MAX_OFF = 448;
 constexpr int GEN_RMAX = 12;
@@ -110,9 +110,11 @@ hipError_t launch_tangent_hvp(const Geo& g, const CoefD& k, bool f64, bool frame
                               const int* done, hipStream_t st, int variant = -1, long long vbs = 0);
 
 // ---- shells.hip: general-shell lattice kernels (more than three shells) ----
-// part: the energy of each tile
+// part: the energy of each of the *tiles tiles a lattice is cut into (at most
+// the 32 x 8 tiles of the geometry)
 hipError_t launch_energy_grad_gen(const Geo& g, const CoefD& k, bool f64, int batch, const void* m,
-                                  const uint8_t* mask, void* grad, void* c, void* F, double* part, hipStream_t st);
+                                  const uint8_t* mask, void* grad, void* c, void* F, double* part, int* tiles,
+                                  hipStream_t st);
 hipError_t launch_tangent_hvp_gen(const Geo& g, const CoefD& k, bool f64, bool frame, int batch, const void* m,
                                   const void* c, const uint8_t* mask, int nvec, long long vbs, const void* V, void* W,
                                   const int* done, hipStream_t st);

@@ -2,68 +2,227 @@
 // exchange shells (the paper's Pd/Fe/Ir(111) parameter set has 35 shells,
 // 360 bonds per site; Supplementary Note 4, Table S1).
 //
-// With hundreds of offsets per site the stencil is bound by LDS reads and
-// VALU adds, not by HBM: a workgroup stages a TX x TY tile with a halo of R
-// rows and columns (R = the largest |dx|, |dy| of the table, at most 12) in
-// LDS and each thread sums the shells of its site from there, shell by shell
-// (one multiply by cJ[s] per shell).  The spin Hamiltonian is the one of the
+// With hundreds of offsets per site the stencil is bound by multiply-adds, not
+// by HBM: a workgroup stages a tile with the halo of its disc of bonds in LDS
+// and convolves it row by row.  The spin Hamiltonian is the one of the
 // three-shell kernels (Methods, Eq. param-hamiltonian): exchange on every
 // shell, interfacial DMI on the nearest-neighbour shell, uniaxial anisotropy,
 // Zeeman field.
+#include <algorithm>
+#include <type_traits>
 #include <utility>
 
 #include "kernels.hpp"
 
 namespace moto {
 
-constexpr int LXG = TX + 2 * GEN_RMAX;
-constexpr int LYG = TY + 2 * GEN_RMAX;
-
-template <class T>
-struct GenLDS {
-    T u[3][LYG][LXG];
-    uint8_t act[LYG][LXG];
+// Rows of the disc of the first NS shells: shell[dy + GEN_RMAX][dx + GEN_RMAX]
+// (-1 off the disc and at the centre) and the extent lo..hi of each row.
+struct DiscRows {
+    int R;
+    int lo[2 * GEN_RMAX + 1], hi[2 * GEN_RMAX + 1];
+    signed char shell[2 * GEN_RMAX + 1][2 * GEN_RMAX + 1];
 };
 
+constexpr DiscRows make_disc(int ns) {
+    DiscRows t{};
+    for (int y = 0; y <= 2 * GEN_RMAX; ++y) {
+        t.lo[y] = GEN_RMAX + 1;
+        t.hi[y] = -GEN_RMAX - 1;
+        for (int x = 0; x <= 2 * GEN_RMAX; ++x) t.shell[y][x] = -1;
+    }
+    for (int s = 0; s < ns; ++s)
+        for (int o = kShellGeom.start[s]; o < kShellGeom.start[s + 1]; ++o) {
+            const int dx = kShellGeom.dx[o], dy = kShellGeom.dy[o], y = dy + GEN_RMAX;
+            t.shell[y][dx + GEN_RMAX] = (signed char)s;
+            if (dx < t.lo[y]) t.lo[y] = dx;
+            if (dx > t.hi[y]) t.hi[y] = dx;
+            if (dy > t.R) t.R = dy;
+            if (dx > t.R) t.R = dx;
+        }
+    return t;
+}
+template <int NS>
+inline constexpr DiscRows kDisc = make_disc(NS);
+
+// couplings (cJ zero beyond the plan's shells), in scalar registers
+template <class T, int NS>
+struct GenCoef {
+    T cJ[NS];
+    T cD, cK, B[3];
+};
+
+// HX x HY output sites a workgroup, HSP consecutive ones of a row a thread
+template <class T, int NS, int HX_, int HY_, int HSP_>
 struct GenTile {
-    int b, tx0, ty0;
+    static constexpr int HX = HX_, HY = HY_, HSP = HSP_;
+    static constexpr int TPR = HX / HSP, NTH = TPR * HY;
+    static constexpr int V = 16 / sizeof(T);  // values of an aligned 16-byte LDS read
+    static constexpr int RY = kDisc<NS>.R, RX = (RY + V - 1) / V * V;
+    static constexpr int LX = HX + 2 * RX, LY = HY + 2 * RY;
+    // row stride: two rows' reads at 16-byte steps fall on different halves of
+    // the 32 bytes between neighbouring threads
+    static constexpr int LS = LX + V;
+    T u[3][LY][LS];
 };
 
-__device__ __forceinline__ GenTile gen_tile(const Geo& g) {
-    GenTile t;
-    const int bid = blockIdx.x;
-    t.b = bid / g.tiles;
-    const int r = bid - t.b * g.tiles;
-    t.tx0 = (r % g.tiles_x) * TX;
-    t.ty0 = (r / g.tiles_x) * TY;
+// acc[q] += sum over the row's bonds of cJ[shell] u(q + dx)
+template <class T, int NS, class TL, int DY>
+struct DiscRow {
+    static constexpr int LO = kDisc<NS>.lo[DY + GEN_RMAX], HI = kDisc<NS>.hi[DY + GEN_RMAX];
+    // 16-byte aligned window from the first value needed
+    static constexpr int W0 = (TL::RX + LO) / TL::V * TL::V;
+    static constexpr int WN = (TL::RX + HI + TL::HSP - W0 + TL::V - 1) / TL::V * TL::V;
+
+    static __device__ __forceinline__ void load(const T* __restrict__ row, T (&win)[WN]) {
+        typedef T VT __attribute__((ext_vector_type(TL::V)));
+#pragma unroll
+        for (int i = 0; i < WN; i += TL::V) {
+            const VT v = *reinterpret_cast<const VT*>(row + W0 + i);
+#pragma unroll
+            for (int e = 0; e < TL::V; ++e) win[i + e] = v[e];
+        }
+    }
+    template <int I>
+    static __device__ __forceinline__ void term(const T (&win)[WN], const GenCoef<T, NS>& k, T (&acc)[TL::HSP]) {
+        constexpr int S = kDisc<NS>.shell[DY + GEN_RMAX][LO + I + GEN_RMAX];
+        if constexpr (S >= 0) {
+#pragma unroll
+            for (int q = 0; q < TL::HSP; ++q) acc[q] += k.cJ[S] * win[TL::RX + LO + I - W0 + q];
+        }
+    }
+    template <int... I>
+    static __device__ __forceinline__ void terms(std::integer_sequence<int, I...>, const T (&win)[WN],
+                                                 const GenCoef<T, NS>& k, T (&acc)[TL::HSP]) {
+        (term<I>(win, k, acc), ...);
+    }
+    static __device__ __forceinline__ void run(const T* __restrict__ row, const GenCoef<T, NS>& k,
+                                               T (&acc)[TL::HSP]) {
+        T win[WN];
+        load(row, win);
+        terms(std::make_integer_sequence<int, HI - LO + 1>{}, win, k, acc);
+        // one row's window live at a time
+        __builtin_amdgcn_sched_barrier(0);
+    }
+};
+
+template <class T, int NS, class TL, int... Y>
+__device__ __forceinline__ void disc_rows(std::integer_sequence<int, Y...>, const T* __restrict__ base,
+                                          const GenCoef<T, NS>& k, T (&acc)[TL::HSP]) {
+    (DiscRow<T, NS, TL, Y - TL::RY>::run(base + Y * TL::LS, k, acc), ...);
+}
+
+// Field (A u) at the thread's HSP sites (lx0.., ly0), without anisotropy.
+// The disc is unrolled: every bond is one multiply-add with its coupling as a
+// scalar operand and its neighbour in a register, each row's window being read
+// once in 16-byte pieces.  The earlier form convolved the full 25 x 23 square
+// with couplings from LDS (1725 multiply-adds a site-vector instead of 1083,
+// and a quarter as many LDS reads again), a workgroup taking the vectors one
+// after another.  us, before and now, 35 shells: 64 x 128x128 x 4 FP32 471 and
+// 186 (115 for the multiply-adds alone at the vector rate), FP64 1137 and 283;
+// one 128x128 state x 4 FP32 209 and 22; 16x16 x 1 53 and 21.
+template <class T, int NS, class TL>
+__device__ __forceinline__ void disc_field(const TL& L, int lx0, int ly0, const GenCoef<T, NS>& k,
+                                           T (&a)[TL::HSP][3]) {
+#pragma unroll 1
+    for (int cc = 0; cc < 3; ++cc) {
+        T acc[TL::HSP];
+#pragma unroll
+        for (int q = 0; q < TL::HSP; ++q) acc[q] = T(0);
+        disc_rows<T, NS, TL>(std::make_integer_sequence<int, 2 * TL::RY + 1>{}, &L.u[cc][ly0][lx0], k, acc);
+#pragma unroll
+        for (int q = 0; q < TL::HSP; ++q) {
+            a[q][0] = cc == 0 ? acc[q] : a[q][0];
+            a[q][1] = cc == 1 ? acc[q] : a[q][1];
+            a[q][2] = cc == 2 ? acc[q] : a[q][2];
+        }
+    }
+    // nearest-neighbour DMI
+    if (k.cD != T(0)) {
+        constexpr int NDX[6] = {1, 0, -1, -1, 0, 1}, NDY[6] = {0, 1, 1, 0, -1, -1};
+#pragma unroll
+        for (int o = 0; o < 6; ++o) {
+            const T hx = k.cD * (T(NDX[o]) + T(0.5) * T(NDY[o]));
+            const T hy = k.cD * (T(0.86602540378443864676) * T(NDY[o]));
+#pragma unroll
+            for (int q = 0; q < TL::HSP; ++q) {
+                const int y = ly0 + TL::RY + NDY[o], x = lx0 + TL::RX + q + NDX[o];
+                const T u0 = L.u[0][y][x], u1 = L.u[1][y][x], u2 = L.u[2][y][x];
+                a[q][0] += hx * u2;
+                a[q][1] += hy * u2;
+                a[q][2] -= hx * u0 + hy * u1;
+            }
+        }
+    }
+}
+
+struct GenPos {
+    int id, b, tx0, ty0;
+};
+template <class TL>
+__device__ __forceinline__ GenPos gen_pos(const Geo& g, int id) {
+    GenPos t;
+    const int ntx = (g.Lx + TL::HX - 1) / TL::HX, nty = (g.Ly + TL::HY - 1) / TL::HY;
+    t.id = id;
+    t.b = id / (ntx * nty);
+    const int r = id - t.b * ntx * nty;
+    t.tx0 = (r % ntx) * TL::HX;
+    t.ty0 = (r / ntx) * TL::HY;
     return t;
 }
 
-// (A u) at LDS position (cx, cy): sum_s cJ[s] sum_{delta in s} u(. + delta)
-// + cD sum_{delta in NN} [dhat u_z - z (dhat . u)] + cK u_z z.
-template <class T>
-__device__ __forceinline__ void apply_A_gen(const GenLDS<T>& L, const GenShells& gs, const Coef<T>& k, int cx, int cy,
-                                            T (&a)[3]) {
-    a[0] = a[1] = a[2] = T(0);
-    for (int s = 0; s < gs.ns; ++s) {
-        T S0 = T(0), S1 = T(0), S2 = T(0);
-        const int o1 = gs.start[s + 1];
-        for (int o = gs.start[s]; o < o1; ++o) {
-            const int yy = cy + gs.dy[o], xx = cx + gs.dx[o];
-            S0 += L.u[0][yy][xx];
-            S1 += L.u[1][yy][xx];
-            S2 += L.u[2][yy][xx];
-        }
-        const T cj = (T)gs.cJ[s];
-        a[0] += cj * S0;
-        a[1] += cj * S1;
-        a[2] += cj * S2;
+// fill the staged tile: f(site index, u[3])
+template <class TL, class F>
+__device__ __forceinline__ void stage_gen(TL& L, const Geo& g, const GenPos& t, F&& f) {
+    using T = std::remove_reference_t<decltype(L.u[0][0][0])>;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < TL::LX * TL::LY; i += TL::NTH) {
+        const int ly = i / TL::LX, lx = i - ly * TL::LX;
+        T u[3];
+        f(wrap1(t.tx0 + lx - TL::RX, g.Lx) + g.Lx * wrap1(t.ty0 + ly - TL::RY, g.Ly), u);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) L.u[d][ly][lx] = u[d];
     }
+}
+
+// Field (A u) at one site of a staged tile, shell by shell: the members of a
+// shell are added first, then scaled by its coupling.  The FP32 energies keep
+// this order (a third of the rounding error of disc_field's running sum, which
+// shows in an FP64 energy), unrolled so that every neighbour is an LDS read at
+// an immediate offset; shells beyond the plan's are skipped.  64 x 128x128, 35
+// shells: 163 us with the offsets from a table, 86 now.
+template <class T, int NS, class TL, int S, int... I>
+__device__ __forceinline__ void shell_add(std::integer_sequence<int, I...>, const TL& L, int y, int x,
+                                          const GenCoef<T, NS>& k, T (&a)[3]) {
+    T m[3] = {T(0), T(0), T(0)};
+    constexpr int O = kShellGeom.start[S];
+    ((m[0] += L.u[0][y + kShellGeom.dy[O + I]][x + kShellGeom.dx[O + I]],
+      m[1] += L.u[1][y + kShellGeom.dy[O + I]][x + kShellGeom.dx[O + I]],
+      m[2] += L.u[2][y + kShellGeom.dy[O + I]][x + kShellGeom.dx[O + I]]),
+     ...);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) a[d] += k.cJ[S] * m[d];
+    __builtin_amdgcn_sched_barrier(0);  // one shell's neighbours live at a time
+}
+template <class T, int NS, class TL, int... S>
+__device__ __forceinline__ void shells_add(std::integer_sequence<int, S...>, const TL& L, int y, int x, int ns,
+                                           const GenCoef<T, NS>& k, T (&a)[3]) {
+    ((S < ns ? shell_add<T, NS, TL, S>(
+                   std::make_integer_sequence<int, kShellGeom.start[S + 1] - kShellGeom.start[S]>{}, L, y, x, k, a)
+             : void()),
+     ...);
+}
+template <class T, int NS, class TL>
+__device__ __forceinline__ void shell_field(const TL& L, int lx0, int ly0, int ns, const GenCoef<T, NS>& k,
+                                            T (&a)[3]) {
+    const int y = ly0 + TL::RY, x = lx0 + TL::RX;
+    a[0] = a[1] = a[2] = T(0);
+    shells_add<T, NS, TL>(std::make_integer_sequence<int, NS>{}, L, y, x, ns, k, a);
     if (k.cD != T(0)) {
-        for (int o = gs.start[0]; o < gs.start[1]; ++o) {
-            const int ddx = gs.dx[o], ddy = gs.dy[o];
-            const int yy = cy + ddy, xx = cx + ddx;
-            const T u0 = L.u[0][yy][xx], u1 = L.u[1][yy][xx], u2 = L.u[2][yy][xx];
+#pragma unroll
+        for (int o = 0; o < 6; ++o) {
+            const int ddx = kShellGeom.dx[o], ddy = kShellGeom.dy[o];
+            const T u0 = L.u[0][y + ddy][x + ddx], u1 = L.u[1][y + ddy][x + ddx], u2 = L.u[2][y + ddy][x + ddx];
             const T hx = k.cD * (T(ddx) + T(0.5) * T(ddy));
             const T hy = k.cD * (T(0.86602540378443864676) * T(ddy));
             a[0] += hx * u2;
@@ -71,240 +230,216 @@ __device__ __forceinline__ void apply_A_gen(const GenLDS<T>& L, const GenShells&
             a[2] -= hx * u0 + hy * u1;
         }
     }
-    a[2] += k.cK * L.u[2][cy][cx];
 }
 
 // Energy, gradient, c, F of the general-shell Hamiltonian; part[tile] =
 // sum_i (1/2 m_i.(A m)_i - B.m_i).
-template <class T>
-__global__ __launch_bounds__(NT) void k_energy_grad_gen(Geo g, GenShells gs, Coef<T> k, const T* __restrict__ m,
-                                                        const uint8_t* __restrict__ mask, T* __restrict__ grad,
-                                                        T* __restrict__ cout, T* __restrict__ F,
-                                                        double* __restrict__ part) {
-    __shared__ GenLDS<T> L;
-    __shared__ double red[NT / 64];
-    const GenTile t = gen_tile(g);
-    const int R = gs.R, W = TX + 2 * R, H = TY + 2 * R;
+template <class T, int NS, class TL>
+__global__ __launch_bounds__(TL::NTH) void k_energy_grad_gen(Geo g, int ns, GenCoef<T, NS> k, const T* __restrict__ m,
+                                                             const uint8_t* __restrict__ mask, T* __restrict__ grad,
+                                                             T* __restrict__ cout, T* __restrict__ F,
+                                                             double* __restrict__ part) {
+    __shared__ __align__(16) TL L;
+    __shared__ double red[TL::NTH / 64];
+    const GenPos t = gen_pos<TL>(g, blockIdx.x);
     const size_t N = g.N;
     const T* mb = m + (size_t)t.b * 3 * N;
-    for (int i = threadIdx.x; i < W * H; i += NT) {
-        const int lx = i % W, ly = i / W;
-        const int x = wrapi(t.tx0 + lx - R, g.Lx), y = wrapi(t.ty0 + ly - R, g.Ly);
-        const int s = x + g.Lx * y;
-        L.u[0][ly][lx] = mb[s];
-        L.u[1][ly][lx] = mb[N + s];
-        L.u[2][ly][lx] = mb[2 * N + s];
-    }
+    stage_gen(L, g, t, [&](int s, T(&u)[3]) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) u[d] = mb[d * N + s];
+    });
     __syncthreads();
-    const int lx = threadIdx.x % TX, ly = threadIdx.x / TX;
-    const int x = t.tx0 + lx, y = t.ty0 + ly;
-    double v[1] = {0.0};
-    if (x < g.Lx && y < g.Ly) {
-        const int cx = lx + R, cy = ly + R;
-        const size_t s = (size_t)t.b * N + x + (size_t)g.Lx * y;
-        const size_t s3 = (size_t)t.b * 3 * N + x + (size_t)g.Lx * y;
-        T a[3];
-        apply_A_gen(L, gs, k, cx, cy, a);
-        const T mi[3] = {L.u[0][cy][cx], L.u[1][cy][cx], L.u[2][cy][cx]};
-        const T gi[3] = {a[0] - k.B[0], a[1] - k.B[1], a[2] - k.B[2]};
+    const int lx0 = (threadIdx.x % TL::TPR) * TL::HSP, ly0 = threadIdx.x / TL::TPR;
+    const int y = t.ty0 + ly0;
+    T a[TL::HSP][3];
+    if constexpr (TL::HSP == 1)
+        shell_field<T, NS>(L, lx0, ly0, ns, k, a[0]);
+    else
+        disc_field<T, NS>(L, lx0, ly0, k, a);
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < TL::HSP; ++q) {
+        const int x = t.tx0 + lx0 + q;
+        if (x >= g.Lx || y >= g.Ly) continue;
+        const size_t s = x + (size_t)g.Lx * y, s1 = (size_t)t.b * N + s, s3 = (size_t)t.b * 3 * N + s;
+        T mi[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) mi[d] = L.u[d][ly0 + TL::RY][lx0 + TL::RX + q];
+        const T ai[3] = {a[q][0], a[q][1], a[q][2] + k.cK * mi[2]};
+        const T gi[3] = {ai[0] - k.B[0], ai[1] - k.B[1], ai[2] - k.B[2]};
         const T ci = mi[0] * gi[0] + mi[1] * gi[1] + mi[2] * gi[2];
         if (grad) {
-            grad[s3] = gi[0];
-            grad[s3 + N] = gi[1];
-            grad[s3 + 2 * N] = gi[2];
-        }
-        if (cout) cout[s] = ci;
-        if (F) {
-            const bool act = mask == nullptr || mask[s] != 0;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) F[s3 + c * N] = act ? -(gi[c] - ci * mi[c]) : T(0);
+            for (int d = 0; d < 3; ++d) grad[s3 + d * N] = gi[d];
         }
-        const double mam = (double)mi[0] * a[0] + (double)mi[1] * a[1] + (double)mi[2] * a[2];
+        if (cout) cout[s1] = ci;
+        if (F) {
+            const bool act = mask == nullptr || mask[s1] != 0;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) F[s3 + d * N] = act ? -(gi[d] - ci * mi[d]) : T(0);
+        }
+        const double mam = (double)mi[0] * ai[0] + (double)mi[1] * ai[1] + (double)mi[2] * ai[2];
         const double bm = (double)k.B[0] * mi[0] + (double)k.B[1] * mi[1] + (double)k.B[2] * mi[2];
-        v[0] = 0.5 * mam - bm;
+        v += 0.5 * mam - bm;
     }
-    block_sum<1>(v, red);
-    if (threadIdx.x == 0) part[blockIdx.x] = v[0];
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int w = 0; w < TL::NTH / 64; ++w) s += red[w];
+        part[t.id] = s;
+    }
 }
 
-// Tangent HVP (frame or ambient layout, as the three-shell tile kernel):
-// W_j = M H(m) M V_j with (H v)_i = P_i (A v)_i - c_i v_i, one vector at a
-// time through an HX x HY tile staged with the full GEN_RMAX halo.
-//
-// The exchange sum over the disc of bonds is evaluated row by row as a 1-D
-// convolution: a thread owns HSP consecutive sites of one row and, for each
-// row offset dy, reads the HSP + 2 GEN_RMAX values of that input row once
-// (16-byte LDS reads) into registers and applies the row's 2 GEN_RMAX + 1
-// couplings (a per-block LDS table, zero off the disc and beyond the plan's
-// shells) to all HSP sites from there: about 2 LDS values per site, row and
-// component instead of one per bond, at the price of multiply-adds over the
-// full square of offsets (the disc fills 58 % of it).  DMI (nearest
-// neighbours) and anisotropy are added per site afterwards.
-constexpr int HX = 64, HY = 16, HSP = 8, HNT = (HX / HSP) * HY;
-constexpr int HLX = HX + 2 * GEN_RMAX, HLY = HY + 2 * GEN_RMAX;
-constexpr int HW = 2 * GEN_RMAX + 1;   // couplings per row
-constexpr int HWIN = HSP + 2 * GEN_RMAX;  // window values per row
-static_assert(HLX % 4 == 0 && HSP % 4 == 0, "16-byte aligned row windows");
-
-template <class T>
-struct HvpGenLDS {
-    T u[3][HLY][HLX];
-    T wt[HW][HW];  // wt[dy + R][dx + R] = cJ of the shell of (dx, dy)
-};
-
-template <class T, bool FRAME>
-__global__ __launch_bounds__(HNT) void k_tangent_hvp_gen(Geo g, GenShells gs, Coef<T> k, const T* __restrict__ m,
-                                                         const T* __restrict__ c, const uint8_t* __restrict__ mask,
-                                                         int nvec, long long vbs, const T* __restrict__ V,
-                                                         T* __restrict__ W, const int* __restrict__ done) {
+// Tangent HVP (frame or ambient layout, as the three-shell kernels): one tile
+// of one vector a workgroup,
+// W_j = M H(m) M V_j with (H v)_i = P_i (A v)_i - c_i v_i.
+template <class T, bool FRAME, int NS, class TL>
+__global__ __launch_bounds__(TL::NTH) void k_tangent_hvp_gen(Geo g, GenCoef<T, NS> k, const T* __restrict__ m,
+                                                             const T* __restrict__ c,
+                                                             const uint8_t* __restrict__ mask, int nvec,
+                                                             long long vbs, const T* __restrict__ V,
+                                                             T* __restrict__ W, const int* __restrict__ done) {
     if (done != nullptr && *done) return;
     constexpr int DV = FRAME ? 2 : 3;
-    __shared__ __align__(16) HvpGenLDS<T> L;
-    __shared__ uint8_t act[HLY][HLX];
-    const int ntx = (g.Lx + HX - 1) / HX, nty = (g.Ly + HY - 1) / HY;
-    const int bid = blockIdx.x;
-    const int b = bid / (ntx * nty);
-    const int r = bid - b * ntx * nty;
-    const int tx0 = (r % ntx) * HX, ty0 = (r / ntx) * HY;
+    __shared__ __align__(16) TL L;
+    const int j = blockIdx.x % nvec;
+    const GenPos t = gen_pos<TL>(g, blockIdx.x / nvec);
     const size_t N = g.N;
-    const T* mb = m + (size_t)b * 3 * N;
-    const uint8_t* mk = mask ? mask + (size_t)b * N : nullptr;
-    const T* Vb = V + (size_t)b * vbs;
-    T* Wb = W + (size_t)b * vbs;
-    // couplings of the disc, activity of the staged sites
-    for (int i = threadIdx.x; i < HW * HW; i += HNT) (&L.wt[0][0])[i] = T(0);
-    for (int i = threadIdx.x; i < HLX * HLY; i += HNT) {
-        const int lx = i % HLX, ly = i / HLX;
-        const int s = wrapi(tx0 + lx - GEN_RMAX, g.Lx) + g.Lx * wrapi(ty0 + ly - GEN_RMAX, g.Ly);
-        act[ly][lx] = mk ? (mk[s] != 0) : 1;
-    }
+    const T* mb = m + (size_t)t.b * 3 * N;
+    const uint8_t* mk = mask ? mask + (size_t)t.b * N : nullptr;
+    const T* vj = V + (size_t)t.b * vbs + (size_t)j * DV * N;
+    T* wj = W + (size_t)t.b * vbs + (size_t)j * DV * N;
+    stage_gen(L, g, t, [&](int s, T(&u)[3]) {
+        const bool on = mk == nullptr || mk[s] != 0;
+        if constexpr (FRAME) {
+            T f1[3], f2[3];
+            onb(mb[s], mb[N + s], mb[2 * N + s], f1, f2);
+            const T a = on ? vj[s] : T(0);
+            const T bb = on ? vj[N + s] : T(0);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) u[d] = a * f1[d] + bb * f2[d];
+        } else {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) u[d] = on ? vj[d * N + s] : T(0);
+        }
+    });
     __syncthreads();
-    for (int o = threadIdx.x; o < gs.n_off; o += HNT) {
-        int sh = 0;
-        while (o >= gs.start[sh + 1]) ++sh;
-        L.wt[gs.dy[o] + GEN_RMAX][gs.dx[o] + GEN_RMAX] = (T)gs.cJ[sh];
-    }
-    const int lx0 = (threadIdx.x % (HX / HSP)) * HSP, ly0 = threadIdx.x / (HX / HSP);
-    const int y = ty0 + ly0;
-    const int cy = ly0 + GEN_RMAX, cx = lx0 + GEN_RMAX;
-    const int R = gs.R;
-    for (int j = 0; j < nvec; ++j) {
-        const T* vj = Vb + (size_t)j * DV * N;
-        __syncthreads();
-        for (int i = threadIdx.x; i < HLX * HLY; i += HNT) {
-            const int lx = i % HLX, ly = i / HLX;
-            const int s = wrapi(tx0 + lx - GEN_RMAX, g.Lx) + g.Lx * wrapi(ty0 + ly - GEN_RMAX, g.Ly);
-            const bool on = act[ly][lx];
-            if constexpr (FRAME) {
-                T f1[3], f2[3];
-                onb(mb[s], mb[N + s], mb[2 * N + s], f1, f2);
-                const T a = on ? vj[s] : T(0);
-                const T bb = on ? vj[N + s] : T(0);
-                L.u[0][ly][lx] = a * f1[0] + bb * f2[0];
-                L.u[1][ly][lx] = a * f1[1] + bb * f2[1];
-                L.u[2][ly][lx] = a * f1[2] + bb * f2[2];
-            } else {
-                L.u[0][ly][lx] = on ? vj[s] : T(0);
-                L.u[1][ly][lx] = on ? vj[N + s] : T(0);
-                L.u[2][ly][lx] = on ? vj[2 * N + s] : T(0);
-            }
-        }
-        __syncthreads();
-        // exchange: row-by-row convolution of each component
-        T a[HSP][3];
-        for (int cc = 0; cc < 3; ++cc) {
-            T acc[HSP];
+    const int lx0 = (threadIdx.x % TL::TPR) * TL::HSP, ly0 = threadIdx.x / TL::TPR;
+    const int y = t.ty0 + ly0;
+    T a[TL::HSP][3];
+    disc_field<T, NS>(L, lx0, ly0, k, a);
 #pragma unroll
-            for (int q = 0; q < HSP; ++q) acc[q] = T(0);
-            for (int dy = -R; dy <= R; ++dy) {
-                const T* rp = &L.u[cc][cy + dy][lx0];
-                T win[HWIN];
+    for (int q = 0; q < TL::HSP; ++q) {
+        const int x = t.tx0 + lx0 + q;
+        if (x >= g.Lx || y >= g.Ly) continue;
+        const size_t so = x + (size_t)g.Lx * y;
+        const bool on = mk == nullptr || mk[so] != 0;
+        T u[3];
 #pragma unroll
-                for (int i = 0; i < HWIN; ++i) win[i] = rp[i];
-                const T* wr = &L.wt[dy + GEN_RMAX][0];
-#pragma unroll
-                for (int d = 0; d < HW; ++d) {
-                    const T w = wr[d];
-#pragma unroll
-                    for (int q = 0; q < HSP; ++q) acc[q] += w * win[q + d];
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < HSP; ++q) a[q][cc] = acc[q];
-        }
-        // nearest-neighbour DMI and anisotropy, per site
-        if (k.cD != T(0)) {
-#pragma unroll
-            for (int o = 0; o < 6; ++o) {
-                constexpr int NDX[6] = {1, 0, -1, -1, 0, 1}, NDY[6] = {0, 1, 1, 0, -1, -1};
-                const int ddx = NDX[o], ddy = NDY[o];
-                const T hx = k.cD * (T(ddx) + T(0.5) * T(ddy));
-                const T hy = k.cD * (T(0.86602540378443864676) * T(ddy));
-#pragma unroll
-                for (int q = 0; q < HSP; ++q) {
-                    const T u0 = L.u[0][cy + ddy][cx + q + ddx], u1 = L.u[1][cy + ddy][cx + q + ddx],
-                            u2 = L.u[2][cy + ddy][cx + q + ddx];
-                    a[q][0] += hx * u2;
-                    a[q][1] += hy * u2;
-                    a[q][2] -= hx * u0 + hy * u1;
-                }
-            }
-        }
-        T* wj = Wb + (size_t)j * DV * N;
-#pragma unroll
-        for (int q = 0; q < HSP; ++q) {
-            const int x = tx0 + lx0 + q;
-            if (x >= g.Lx || y >= g.Ly) continue;
-            const int so = x + g.Lx * y;
-            const bool on = act[cy][cx + q];
-            const T u0 = L.u[0][cy][cx + q], u1 = L.u[1][cy][cx + q], u2 = L.u[2][cy][cx + q];
-            const T ci = c[(size_t)b * N + so];
-            const T m0 = mb[so], m1 = mb[N + so], m2 = mb[2 * N + so];
-            const T a0 = a[q][0], a1 = a[q][1], a2 = a[q][2] + k.cK * u2;
-            if constexpr (FRAME) {
-                T e1[3], e2[3];
-                onb(m0, m1, m2, e1, e2);
-                const T av = e1[0] * u0 + e1[1] * u1 + e1[2] * u2;
-                const T bv = e2[0] * u0 + e2[1] * u1 + e2[2] * u2;
-                const T wa = e1[0] * a0 + e1[1] * a1 + e1[2] * a2 - ci * av;
-                const T wb = e2[0] * a0 + e2[1] * a1 + e2[2] * a2 - ci * bv;
-                wj[so] = on ? wa : T(0);
-                wj[N + so] = on ? wb : T(0);
-            } else {
-                const T ma = m0 * a0 + m1 * a1 + m2 * a2;
-                wj[so] = on ? a0 - ma * m0 - ci * u0 : T(0);
-                wj[N + so] = on ? a1 - ma * m1 - ci * u1 : T(0);
-                wj[2 * N + so] = on ? a2 - ma * m2 - ci * u2 : T(0);
-            }
+        for (int d = 0; d < 3; ++d) u[d] = L.u[d][ly0 + TL::RY][lx0 + TL::RX + q];
+        const T ci = c[(size_t)t.b * N + so];
+        const T m0 = mb[so], m1 = mb[N + so], m2 = mb[2 * N + so];
+        const T a0 = a[q][0], a1 = a[q][1], a2 = a[q][2] + k.cK * u[2];
+        if constexpr (FRAME) {
+            T e1[3], e2[3];
+            onb(m0, m1, m2, e1, e2);
+            const T av = e1[0] * u[0] + e1[1] * u[1] + e1[2] * u[2];
+            const T bv = e2[0] * u[0] + e2[1] * u[1] + e2[2] * u[2];
+            const T wa = e1[0] * a0 + e1[1] * a1 + e1[2] * a2 - ci * av;
+            const T wb = e2[0] * a0 + e2[1] * a1 + e2[2] * a2 - ci * bv;
+            wj[so] = on ? wa : T(0);
+            wj[N + so] = on ? wb : T(0);
+        } else {
+            const T ma = m0 * a0 + m1 * a1 + m2 * a2;
+            wj[so] = on ? a0 - ma * m0 - ci * u[0] : T(0);
+            wj[N + so] = on ? a1 - ma * m1 - ci * u[1] : T(0);
+            wj[2 * N + so] = on ? a2 - ma * m2 - ci * u[2] : T(0);
         }
     }
 }
 
 // --------------------------------------------------------------------------
-hipError_t launch_energy_grad_gen(const Geo& g, const CoefD& kd, bool f64, int batch, const void* m,
-                                  const uint8_t* mask, void* grad, void* c, void* F, double* part, hipStream_t st) {
-    if (!kd.gen || kd.gen->R > GEN_RMAX) return hipErrorInvalidValue;
-    const dim3 grid(batch * g.tiles);
-    if (f64)
-        hipLaunchKernelGGL(k_energy_grad_gen<double>, grid, dim3(NT), 0, st, g, *kd.gen, coef_cast<double>(kd),
-                           (const double*)m, mask, (double*)grad, (double*)c, (double*)F, part);
+template <class TL>
+static long long gen_tiles(const Geo& g) {
+    return (long long)((g.Lx + TL::HX - 1) / TL::HX) * ((g.Ly + TL::HY - 1) / TL::HY);
+}
+
+// Calls f(couplings, shells) for the precision and the smallest disc of 10, 20
+// or 36 shells (5, 8 and 11 rows of halo) that holds the plan's.
+template <class T, class F>
+static void with_disc(const CoefD& kd, F&& f) {
+    auto go = [&](auto nsc) {
+        constexpr int NS = decltype(nsc)::value;
+        GenCoef<T, NS> k;
+        for (int s = 0; s < NS; ++s) k.cJ[s] = s < kd.gen->ns ? (T)kd.gen->cJ[s] : T(0);
+        k.cD = (T)kd.cD;
+        k.cK = (T)kd.cK;
+        for (int d = 0; d < 3; ++d) k.B[d] = (T)kd.B[d];
+        f(k, nsc);
+    };
+    if (kd.gen->ns <= 10)
+        go(std::integral_constant<int, 10>{});
+    else if (kd.gen->ns <= 20)
+        go(std::integral_constant<int, 20>{});
     else
-        hipLaunchKernelGGL(k_energy_grad_gen<float>, grid, dim3(NT), 0, st, g, *kd.gen, coef_cast<float>(kd),
-                           (const float*)m, mask, (float*)grad, (float*)c, (float*)F, part);
+        go(std::integral_constant<int, GEN_MAX_SHELLS>{});
+}
+
+// Calls f(tile): 64 x 32 sites (2.1 staged sites an output for 36 shells)
+// where `copies` lattices of them fill the chip twice, 32 x 16 (4.2) where
+// they do not.
+template <class T, int NS, class F>
+static void with_tile(const Geo& g, long long copies, F&& f) {
+    using Large = GenTile<T, NS, 64, 32, sizeof(T) == 4 ? 8 : 4>;
+    using Small = GenTile<T, NS, 32, 16, 4>;
+    if (copies * gen_tiles<Large>(g) >= 512)
+        f((Large*)nullptr);
+    else
+        f((Small*)nullptr);
+}
+
+hipError_t launch_energy_grad_gen(const Geo& g, const CoefD& kd, bool f64, int batch, const void* m,
+                                  const uint8_t* mask, void* grad, void* c, void* F, double* part, int* tiles,
+                                  hipStream_t st) {
+    if (!kd.gen || kd.gen->ns > GEN_MAX_SHELLS) return hipErrorInvalidValue;
+    auto launch = [&](auto& k, auto nsc, auto tl) {
+        using TL = std::remove_pointer_t<decltype(tl)>;
+        using T = std::remove_reference_t<decltype(k.cD)>;
+        const long long n = gen_tiles<TL>(g);
+        *tiles = (int)n;
+        hipLaunchKernelGGL((k_energy_grad_gen<T, decltype(nsc)::value, TL>), dim3((unsigned)(batch * n)),
+                           dim3(TL::NTH), 0, st, g, kd.gen->ns, k, (const T*)m, mask, (T*)grad, (T*)c, (T*)F, part);
+    };
+    if (f64)
+        with_disc<double>(kd, [&](auto& k, auto nsc) {
+            with_tile<double, decltype(nsc)::value>(g, batch, [&](auto tl) { launch(k, nsc, tl); });
+        });
+    else
+        with_disc<float>(kd, [&](auto& k, auto nsc) {
+            launch(k, nsc, (GenTile<float, decltype(nsc)::value, 32, 16, 1>*)nullptr);
+        });
     return hipGetLastError();
 }
 
 hipError_t launch_tangent_hvp_gen(const Geo& g, const CoefD& kd, bool f64, bool frame, int batch, const void* m,
                                   const void* c, const uint8_t* mask, int nvec, long long vbs, const void* V, void* W,
                                   const int* done, hipStream_t st) {
-    if (!kd.gen || kd.gen->R > GEN_RMAX) return hipErrorInvalidValue;
+    if (!kd.gen || kd.gen->ns > GEN_MAX_SHELLS) return hipErrorInvalidValue;
     if (vbs <= 0) vbs = (long long)nvec * (frame ? 2 : 3) * g.N;
-    const dim3 grid(batch * ((g.Lx + HX - 1) / HX) * ((g.Ly + HY - 1) / HY));
     auto go = [&](auto tc, auto fc) {
         using T = decltype(tc);
         constexpr bool FR = decltype(fc)::value;
-        hipLaunchKernelGGL((k_tangent_hvp_gen<T, FR>), grid, dim3(HNT), 0, st, g, *kd.gen, coef_cast<T>(kd),
-                           (const T*)m, (const T*)c, mask, nvec, vbs, (const T*)V, (T*)W, done);
+        with_disc<T>(kd, [&](auto& k, auto nsc) {
+            constexpr int NS = decltype(nsc)::value;
+            with_tile<T, NS>(g, (long long)batch * nvec, [&](auto tl) {
+                using TL = std::remove_pointer_t<decltype(tl)>;
+                hipLaunchKernelGGL((k_tangent_hvp_gen<T, FR, NS, TL>),
+                                   dim3((unsigned)(batch * gen_tiles<TL>(g) * nvec)), dim3(TL::NTH), 0, st, g, k,
+                                   (const T*)m, (const T*)c, mask, nvec, vbs, (const T*)V, (T*)W, done);
+            });
+        });
     };
     if (f64) {
         if (frame)

@@ -375,9 +375,9 @@ __global__ __launch_bounds__(NT) void k_topo_charge(Geo g, const double* __restr
 
 // sums of every lattice from its per-tile rows of NP
 template <int NP>
-static void reduce_partials(const Geo& g, int batch, const double* part, int ns, double* E, double* dth,
+static void reduce_partials(int tiles, int batch, const double* part, int ns, double* E, double* dth,
                             hipStream_t st) {
-    hipLaunchKernelGGL(k_reduce_partials<NP>, dim3(batch), dim3(NT), 0, st, part, g.tiles, ns, E, dth);
+    hipLaunchKernelGGL(k_reduce_partials<NP>, dim3(batch), dim3(NT), 0, st, part, tiles, ns, E, dth);
 }
 
 template <class T, int NP>
@@ -391,7 +391,7 @@ static void go_energy(const Geo& g, const CoefD& kd, int batch, const void* m, c
     }
     hipLaunchKernelGGL((k_energy_grad<T, NP>), dim3(batch * g.tiles), dim3(NT), 0, st, g, k, (const T*)m, mask,
                        (T*)grad, (T*)c, (T*)F, part);
-    if constexpr (NP > 0) reduce_partials<NP>(g, batch, part, ns, E, dth, st);
+    if constexpr (NP > 0) reduce_partials<NP>(g.tiles, batch, part, ns, E, dth, st);
 }
 
 hipError_t launch_energy_grad(const Geo& g, const CoefD& kd, bool f64, int batch, const void* m,
@@ -399,9 +399,10 @@ hipError_t launch_energy_grad(const Geo& g, const CoefD& kd, bool f64, int batch
                               double* dth, hipStream_t st) {
     if (kd.gen) {
         if (dth) return hipErrorInvalidValue;
-        const hipError_t e = launch_energy_grad_gen(g, kd, f64, batch, m, mask, grad, c, F, part, st);
+        int tiles = 0;
+        const hipError_t e = launch_energy_grad_gen(g, kd, f64, batch, m, mask, grad, c, F, part, &tiles, st);
         if (e != hipSuccess) return e;
-        if (E) reduce_partials<1>(g, batch, part, ns, E, nullptr, st);
+        if (E) reduce_partials<1>(tiles, batch, part, ns, E, nullptr, st);
         return hipGetLastError();
     }
     auto go = [&](auto np) {
@@ -429,7 +430,7 @@ hipError_t launch_param_mixed(const Geo& g, bool f64, int batch, const void* m, 
     else
         hipLaunchKernelGGL(k_param_mixed<float>, grid, dim3(NT), 0, st, g, (const float*)m, (const float*)U,
                            part);
-    reduce_partials<NPART>(g, batch, part, ns, nullptr, out, st);
+    reduce_partials<NPART>(g.tiles, batch, part, ns, nullptr, out, st);
     return hipGetLastError();
 }
 
@@ -468,7 +469,7 @@ hipError_t launch_hessian_apply(const Geo& g, const CoefD& kd, bool f64, int bat
 
 hipError_t launch_topo_charge(const Geo& g, int batch, const double* m, double* part, double* Q, hipStream_t st) {
     hipLaunchKernelGGL(k_topo_charge, dim3(batch * g.tiles), dim3(NT), 0, st, g, m, part);
-    reduce_partials<1>(g, batch, part, 0, Q, nullptr, st);
+    reduce_partials<1>(g.tiles, batch, part, 0, Q, nullptr, st);
     return hipGetLastError();
 }
 
