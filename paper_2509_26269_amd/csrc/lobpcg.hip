@@ -44,6 +44,12 @@ typedef double mf_d4 __attribute__((ext_vector_type(4)));  // accumulator of a 1
 constexpr int UKS = MAXS / 4;                        // k-steps of 4 basis columns
 constexpr int UPDATE_MFMA_MIN_MB = 5;                // block widths whose FP32 row kernels run on the matrix cores
 
+// staged chunk of one basis column: the row is padded by 16 bytes, so that the
+// lanes of a wave, which read different columns at the same row, fall on
+// different LDS banks
+template <class T>
+constexpr int RCHP = RCH + 16 / (int)sizeof(T);
+
 // FP64 dot product of two staged chunks (RCH rows) with four interleaved
 // partial sums, so the chain of dependent adds is RCH / 4 long; the order is
 // fixed, so the result is reproducible
@@ -198,7 +204,7 @@ __global__ __launch_bounds__(NT) void k_orth_gram(EigArgs a, int target, const T
     ctrl += blockIdx.y;
     if (ctrl->done || (target == 2 && ctrl->orth_skip)) return;
     __shared__ OrthCols oc;
-    __shared__ T ts[MAXS][RCH];
+    __shared__ __align__(16) T ts[MAXS][RCHP<T>];
     if (threadIdx.x == 0) orth_cols(a, target, ctrl, oc);
     __syncthreads();
     const int nrow = oc.nq + a.mb;  // staged columns: Q then Y
@@ -412,22 +418,18 @@ __global__ __launch_bounds__(WL) void k_orth_small(EigArgs a, int target, const 
     if (target == 1 && wlane() == 0) ctrl->orth_skip = settled ? 1 : 0;
 }
 
-// MB: compile-time bound on the block width (mb <= MB), so that the per-row
-// register arrays are sized for the actual block and never spill.
-template <class T, int MB, bool MSK>
-__global__ __launch_bounds__(NT) void k_orth_apply(EigArgs a, int target, T* __restrict__ S,
-                                                   const EigCtrl* __restrict__ ctrl) {
-    S += blockIdx.y * a.s_ms;
-    ctrl += blockIdx.y;
-    if (ctrl->done || (target == 2 && ctrl->orth_skip)) return;
-    __shared__ OrthCols oc;
-    __shared__ double B[2 * MAXB * MAXB];
-    __shared__ double Tw[MAXB * MAXB];
-    if (threadIdx.x == 0) orth_cols(a, target, ctrl, oc);
-    for (int i = threadIdx.x; i < 2 * MAXB * MAXB; i += NT) B[i] = ctrl->Bw[i];
-    for (int i = threadIdx.x; i < MAXB * MAXB; i += NT) Tw[i] = ctrl->Tw[i];
-    __syncthreads();
-    const int mb = a.mb, nq = oc.nq;
+// Row kernels on the vector ALUs (k_orth_apply, k_update).  MB: compile-time
+// bound on the block width (mb <= MB), so that the per-row register arrays are
+// sized for the actual block and never spill.  EX: the block has exactly MB
+// columns and the basis all 3 MB (every iteration but the first), so that no
+// run-time test stands between the LDS reads of the coefficients: with one
+// there, each read waited out its latency (k_update at 64x64, k = 2 FP64: 11
+// us for 32 workgroups of one row a thread).
+template <class T, int MB, bool MSK, bool EX>
+__device__ __forceinline__ void orth_apply_rows(const EigArgs& a, const OrthCols& oc, const double* B,
+                                                const double* Tw, T* __restrict__ S) {
+    const int mb = EX ? MB : a.mb, nq = EX ? 2 * MB : oc.nq;
+    const int t0 = EX ? MB : oc.t0;
     const uint8_t* mk = MSK ? member_mask(a) : nullptr;
     for (int r = blockIdx.x * NT + threadIdx.x; r < a.n2; r += gridDim.x * NT) {
         if constexpr (MSK) {
@@ -437,15 +439,15 @@ __global__ __launch_bounds__(NT) void k_orth_apply(EigArgs a, int target, T* __r
         // coefficients (B: 2 MB x MB, Tw: MB x MB doubles) out of the row
         // loop into registers: that runs at the register limit and spills
         // to scratch; re-reading them from LDS per row does not
-        if constexpr (MB > 8) asm volatile("" ::: "memory");
+        if constexpr (EX || MB > 8) asm volatile("" ::: "memory");
         double q[2 * MB], u[MB];
 #pragma unroll
         for (int i = 0; i < 2 * MB; ++i)
-            if (i < nq) q[i] = (double)S[(size_t)oc.qcol[i] * a.n2 + r];
+            if (i < nq) q[i] = (double)S[(size_t)(EX ? (i < MB ? i : MB + i) : oc.qcol[i]) * a.n2 + r];
 #pragma unroll
         for (int j = 0; j < MB; ++j) {
             if (j < mb) {
-                double v = (double)S[(size_t)(oc.t0 + j) * a.n2 + r];
+                double v = (double)S[(size_t)(t0 + j) * a.n2 + r];
 #pragma unroll
                 for (int i = 0; i < 2 * MB; ++i)
                     if (i < nq) v -= B[i + 2 * MAXB * j] * q[i];
@@ -459,10 +461,32 @@ __global__ __launch_bounds__(NT) void k_orth_apply(EigArgs a, int target, T* __r
 #pragma unroll
                 for (int l = 0; l < MB; ++l)
                     if (l < mb) v += u[l] * Tw[l + mb * j];
-                S[(size_t)(oc.t0 + j) * a.n2 + r] = (T)v;
+                S[(size_t)(t0 + j) * a.n2 + r] = (T)v;
             }
         }
     }
+}
+
+template <class T, int MB, bool MSK>
+__global__ __launch_bounds__(NT) void k_orth_apply(EigArgs a, int target, T* __restrict__ S,
+                                                   const EigCtrl* __restrict__ ctrl) {
+    S += blockIdx.y * a.s_ms;
+    ctrl += blockIdx.y;
+    if (ctrl->done || (target == 2 && ctrl->orth_skip)) return;
+    __shared__ OrthCols oc;
+    __shared__ double B[2 * MAXB * MAXB];
+    __shared__ double Tw[MAXB * MAXB];
+    if (threadIdx.x == 0) orth_cols(a, target, ctrl, oc);
+    for (int i = threadIdx.x; i < 2 * MAXB * a.mb; i += NT) B[i] = ctrl->Bw[i];
+    for (int i = threadIdx.x; i < a.mb * a.mb; i += NT) Tw[i] = ctrl->Tw[i];
+    __syncthreads();
+    if constexpr (MB <= 4) {
+        if (a.mb == MB && oc.nq == 2 * MB) {
+            orth_apply_rows<T, MB, MSK, true>(a, oc, B, Tw, S);
+            return;
+        }
+    }
+    orth_apply_rows<T, MB, MSK, false>(a, oc, B, Tw, S);
 }
 
 // --------------------------------------------------------------------------
@@ -490,8 +514,8 @@ __global__ __launch_bounds__(NT) void k_gram(EigArgs a, int ns_fixed, const T* _
     if (ctrl->done) return;
     const int ns = sol_ns(a, ctrl, ns_fixed);
     const int Eh = ns * (ns + 1) / 2, E = 2 * Eh;
-    __shared__ T ts[MAXS][RCH];
-    __shared__ T th[MAXS][RCH];
+    __shared__ __align__(16) T ts[MAXS][RCHP<T>];
+    __shared__ __align__(16) T th[MAXS][RCHP<T>];
     int ei[GQ], ej[GQ], ew[GQ];
 #pragma unroll
     for (int q = 0; q < GQ; ++q) {
@@ -657,35 +681,20 @@ __global__ __launch_bounds__(RR_WAVES * WL) void k_rr(EigArgs a, int ns_fixed, c
 // and per-block partial sums of |W_j|^2.  At the start (ns == mb) P is left
 // alone.
 // --------------------------------------------------------------------------
-template <class T, int MB, bool MSK>
-__global__ __launch_bounds__(NT) void k_update(EigArgs a, int ns_fixed, T* __restrict__ S, T* __restrict__ HS,
-                                               double* __restrict__ part, const EigCtrl* __restrict__ ctrl) {
-    S += blockIdx.y * a.s_ms;
-    HS += blockIdx.y * a.s_ms;
-    part += blockIdx.y * a.part_ms;
-    ctrl += blockIdx.y;
-    if (ctrl->done) return;
-    const int ns = sol_ns(a, ctrl, ns_fixed);
-    const int mb = a.mb;
-    __shared__ double C[MAXS * MAXB];
-    __shared__ double Cp[MAXS * MAXB];
-    __shared__ double lam[MAXB];
-    __shared__ double red[MAXB * (NT / 64)];
-    for (int i = threadIdx.x; i < ns * mb; i += NT) {
-        C[i] = ctrl->C[i];
-        Cp[i] = ctrl->Cp[i];
-    }
-    for (int i = threadIdx.x; i < mb; i += NT) lam[i] = ctrl->lam[i];
-    __syncthreads();
-    double rs[MB];
-#pragma unroll
-    for (int j = 0; j < MB; ++j) rs[j] = 0.0;
+template <class T, int MB, bool MSK, bool EX>
+__device__ __forceinline__ void update_rows(const EigArgs& a, int ns_, const double* C, const double* Cp,
+                                            const double* lam, T* __restrict__ S, T* __restrict__ HS,
+                                            double (&rs)[MB]) {
+    const int mb = EX ? MB : a.mb, ns = EX ? 3 * MB : ns_;
     const bool has_p = ns > mb;
     const uint8_t* mk = MSK ? member_mask(a) : nullptr;
     for (int r = blockIdx.x * NT + threadIdx.x; r < a.n2; r += gridDim.x * NT) {
         if constexpr (MSK) {
             if (!row_active(mk, a.Nsite, r)) continue;
         }
+        // the coefficients stay in LDS (hoisted out of the row loop they cost
+        // up to 466 registers and all but one wave)
+        if constexpr (EX) asm volatile("" ::: "memory");
         T sv[3 * MB];
 #pragma unroll
         for (int i = 0; i < 3 * MB; ++i)
@@ -729,6 +738,37 @@ __global__ __launch_bounds__(NT) void k_update(EigArgs a, int ns_fixed, T* __res
             }
         }
     }
+}
+
+template <class T, int MB, bool MSK>
+__global__ __launch_bounds__(NT) void k_update(EigArgs a, int ns_fixed, T* __restrict__ S, T* __restrict__ HS,
+                                               double* __restrict__ part, const EigCtrl* __restrict__ ctrl) {
+    S += blockIdx.y * a.s_ms;
+    HS += blockIdx.y * a.s_ms;
+    part += blockIdx.y * a.part_ms;
+    ctrl += blockIdx.y;
+    if (ctrl->done) return;
+    const int ns = sol_ns(a, ctrl, ns_fixed);
+    const int mb = a.mb;
+    __shared__ double C[MAXS * MAXB];
+    __shared__ double Cp[MAXS * MAXB];
+    __shared__ double lam[MAXB];
+    __shared__ double red[MAXB * (NT / 64)];
+    for (int i = threadIdx.x; i < ns * mb; i += NT) {
+        C[i] = ctrl->C[i];
+        Cp[i] = ctrl->Cp[i];
+    }
+    for (int i = threadIdx.x; i < mb; i += NT) lam[i] = ctrl->lam[i];
+    __syncthreads();
+    double rs[MB];
+#pragma unroll
+    for (int j = 0; j < MB; ++j) rs[j] = 0.0;
+    bool exact = false;
+    if constexpr (MB <= 4) {
+        exact = mb == MB && ns == 3 * MB;
+        if (exact) update_rows<T, MB, MSK, true>(a, ns, C, Cp, lam, S, HS, rs);
+    }
+    if (!exact) update_rows<T, MB, MSK, false>(a, ns, C, Cp, lam, S, HS, rs);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
     for (int j = 0; j < MB; ++j) {
@@ -1052,10 +1092,13 @@ int update_blocks(int n2, bool f64, int mb) {
     return nb < 1024 ? nb : 1024;
 }
 
-// dispatch on the block-width bucket (4, 8 or 16 columns)
+// dispatch on the block-width bucket (3, 4, 8 or 16 columns; k = 1 and 2 have
+// 3 and 4)
 template <class F>
 static void go_mb(int mb, F&& f) {
-    if (mb <= 4)
+    if (mb == 3)
+        f(std::integral_constant<int, 3>{});
+    else if (mb <= 4)
         f(std::integral_constant<int, 4>{});
     else if (mb <= 8)
         f(std::integral_constant<int, 8>{});
