@@ -526,29 +526,24 @@ static moto_status min_modes_pop_impl(moto_plan p, moto_dtype hvp, int P, const 
     const size_t es = f64 ? sizeof(double) : sizeof(float);
     void* Wslot = (char*)S + es * (size_t)L.mb * L.n2;
     void* HWslot = (char*)HS + es * (size_t)L.mb * L.n2;
-    // the HVP of the whole population is one batched launch; it stops once
-    // every member is done
-    const int* hv_done = P > 1 ? all_done : &ctrl->done;
+    // the HVP of the whole population is one batched launch, in which the
+    // lattices of members that are done are left out
+    const DoneFlags hv_done(&ctrl->done, (int)(sizeof(EigCtrl) / sizeof(int)));
     const long long vbs = L.s_ms;
     const int warm = o->warm;
     const int hv_var = tuned_variant(p, hvp, P, L.mb);
     double* G = (double*)(ws + L.G);
-    auto control = [&](int first, hipStream_t s) -> hipError_t {
-        hipError_t e = launch_eig_control(a, part, nbu, ctrl, first, s);
-        if (e == hipSuccess && P > 1) e = launch_eig_all_done(a, ctrl, all_done, s);
-        return e;
-    };
     HIP_TRY(launch_eig_init(f64, a, S, m, warm == 1 ? V : nullptr, warm == 1 ? k : 0, ws + L.Xsave, warm == 2,
                             mask, N, o->seed, ctrl, st));
     HIP_TRY(launch_check_finite(m, c64, N, P, ctrl, st));
-    if (P > 1) HIP_TRY(launch_eig_all_done(a, ctrl, all_done, st));
     // start: orthonormal X; HX = H X; Rayleigh-Ritz on span(X); W = HX - X Lam
     for (int pass = 0; pass < 2; ++pass) HIP_TRY(launch_orth(f64, a, 0, S, part, nbg, G, ctrl, st));
     HIP_TRY(launch_tangent_hvp(p->g, p->k, f64, true, P, mT, cT, mask, L.mb, S, HS, hv_done, st, hv_var, vbs));
     HIP_TRY(launch_gram(f64, a, L.mb, S, HS, part, nbg, G, ctrl, st));
     HIP_TRY(launch_rr(a, L.mb, G, ctrl, st));
     HIP_TRY(launch_update(f64, a, L.mb, S, HS, part, nbu, ctrl, st));
-    HIP_TRY(control(1, st));
+    HIP_TRY(launch_eig_control(a, part, nbu, ctrl, 1, st));
+    if (P > 1) HIP_TRY(launch_eig_all_done(a, ctrl, all_done, st));
     const int every = o->check_every > 0 ? o->check_every : 8;
     const int max_chunks = o->max_iter / every + 2;
     auto chunk_launches = [&](hipStream_t s) -> hipError_t {
@@ -562,10 +557,12 @@ static moto_status min_modes_pop_impl(moto_plan p, moto_dtype hvp, int P, const 
             if (e == hipSuccess) e = launch_gram(f64, a, -1, S, HS, part, nbg, G, ctrl, s);
             if (e == hipSuccess) e = launch_rr(a, -1, G, ctrl, s);
             if (e == hipSuccess) e = launch_update(f64, a, -1, S, HS, part, nbu, ctrl, s);
-            if (e == hipSuccess) e = control(0, s);
+            if (e == hipSuccess) e = launch_eig_control(a, part, nbu, ctrl, 0, s);
             if (e != hipSuccess) return e;
         }
-        return hipSuccess;
+        // every kernel looks at its own member's flag; the flag of the whole
+        // population is the host's, between chunks
+        return P > 1 ? launch_eig_all_done(a, ctrl, all_done, s) : hipSuccess;
     };
     // one iteration chunk as a HIP graph, captured once per key on the plan's
     // private stream and replayed on the caller's; any capture failure falls

@@ -64,9 +64,8 @@ template <class T, int TXT, int TYT, bool REMAP>
 __global__ __launch_bounds__(NT) void k_hvp_tiled(Geo g, Coef<T> k, const T* __restrict__ m,
                                                   const T* __restrict__ c, const uint8_t* __restrict__ mask, int nvec, long long vbs,
                                                   const T* __restrict__ V, T* __restrict__ W,
-                                                  const int* __restrict__ done, int tiles_x, int tiles_y) {
+                                                  DoneFlags done, int tiles_x, int tiles_y) {
     static_assert(TXT * TYT == NT, "one site per thread");
-    if (done != nullptr && *done) return;
     constexpr int SX = TXT + 2 * HALO, SY = TYT + 2 * HALO, SS = SX * SY;
     __shared__ T u[3][SS];
     __shared__ T fr[6][SS];
@@ -74,6 +73,7 @@ __global__ __launch_bounds__(NT) void k_hvp_tiled(Geo g, Coef<T> k, const T* __r
     const int bid = xcd_order(REMAP);
     const int tiles = tiles_x * tiles_y;
     const int b = bid / tiles, t = bid - b * tiles;
+    if (done(b)) return;
     const int tx0 = (t % tiles_x) * TXT, ty0 = (t / tiles_x) * TYT;
     const size_t off1 = (size_t)b * g.N;
     const T* mb = m + 3 * off1;
@@ -165,12 +165,12 @@ template <class T, int NVP>
 __global__ __launch_bounds__(NT) void k_hvp_band(Geo g, Coef<T> k, const T* __restrict__ m,
                                                  const T* __restrict__ c, const uint8_t* __restrict__ mask, int nvec, long long vbs,
                                                  const T* __restrict__ V, T* __restrict__ W,
-                                                 const int* __restrict__ done, int tiles_x, int tiles_y) {
-    if (done != nullptr && *done) return;
+                                                 DoneFlags done, int tiles_x, int tiles_y) {
     __shared__ T su[NVP][3][BD_SY][BD_SX];
     const int bid = xcd_order(true);
     const int tiles = tiles_x * tiles_y;
     const int b = bid / tiles;
+    if (done(b)) return;
     const int t = bid - b * tiles;
     const int tx0 = (t % tiles_x) * BD_TX, ty0 = (t / tiles_x) * BD_TY;
     const int txw = min(BD_TX, g.Lx - tx0);
@@ -422,8 +422,7 @@ template <class T, int NVP, int XW, bool MASKED>
 __global__ __launch_bounds__(XW) void k_hvp_march(Geo g, Coef<T> k, const T* __restrict__ m,
                                                   const T* __restrict__ c, const uint8_t* __restrict__ mask, int nvec, long long vbs,
                                                   const T* __restrict__ V, T* __restrict__ W,
-                                                  const int* __restrict__ done, int nstrip, int ngroups) {
-    if (done != nullptr && *done) return;
+                                                  DoneFlags done, int nstrip, int ngroups) {
     constexpr int RS = XW + 4;  // halo 2 | XW columns | halo 2
     __shared__ T rb[2][3 * NVP][RS];
     __shared__ T cen[3][MASKED ? 7 : 6][XW];
@@ -432,6 +431,7 @@ __global__ __launch_bounds__(XW) void k_hvp_march(Geo g, Coef<T> k, const T* __r
     const int rest = lid / ngroups;
     const int strip = rest % nstrip;
     const int b = rest / nstrip;
+    if (done(b)) return;
     const int SH = (g.Ly + nstrip - 1) / nstrip;
     const int y0 = strip * SH;
     const int y1 = min(g.Ly, y0 + SH);
@@ -671,8 +671,7 @@ template <class T, int NVP, int NT2, bool MASKED>
 __global__ __launch_bounds__(NT2) void k_hvp_march2(Geo g, Coef<T> k, const T* __restrict__ m,
                                                    const T* __restrict__ c, const uint8_t* __restrict__ mask,
                                                    int nvec, long long vbs, const T* __restrict__ V, T* __restrict__ W,
-                                                   const int* __restrict__ done, int nstrip, int ngroups) {
-    if (done != nullptr && *done) return;
+                                                   DoneFlags done, int nstrip, int ngroups) {
     constexpr int XW = 2 * NT2;
     constexpr int RS = XW + 4;  // halo 2 | XW columns | halo 2
     __shared__ __align__(16) T rb[2][3 * NVP][RS];
@@ -682,6 +681,7 @@ __global__ __launch_bounds__(NT2) void k_hvp_march2(Geo g, Coef<T> k, const T* _
     const int rest = lid / ngroups;
     const int strip = rest % nstrip;
     const int b = rest / nstrip;
+    if (done(b)) return;
     const int SH = (g.Ly + nstrip - 1) / nstrip;
     const int y0 = strip * SH;
     const int y1 = min(g.Ly, y0 + SH);
@@ -919,9 +919,8 @@ template <class T, bool FRAME, bool MORDER, bool MASKED>
 __global__ __launch_bounds__(NT) void k_hvp_gather(Geo g, Coef<T> k, const T* __restrict__ m,
                                                    const T* __restrict__ c, const uint8_t* __restrict__ mask, int nvec,
                                                    long long vbs, const T* __restrict__ V, T* __restrict__ W,
-                                                   const int* __restrict__ done, int tiles_x, int tiles_y, int nvg,
+                                                   DoneFlags done, int tiles_x, int tiles_y, int nvg,
                                                    int ngroups) {
-    if (done != nullptr && *done) return;
     constexpr int DV = FRAME ? 2 : 3;
     static_assert(FRAME || !MORDER, "the march has no ambient form");
     constexpr int SX = TX + 2 * HALO, SS = SX * (TY + 2 * HALO);
@@ -932,6 +931,7 @@ __global__ __launch_bounds__(NT) void k_hvp_gather(Geo g, Coef<T> k, const T* __
     const int rest = lid / ngroups;
     const int tiles = tiles_x * tiles_y;
     const int b = rest / tiles, t = rest - b * tiles;
+    if (done(b)) return;
     const int tx0 = (t % tiles_x) * TX, ty0 = (t / tiles_x) * TY;
     const int j0 = grp * nvg, j1 = min(nvec, j0 + nvg);
     const size_t N = g.N, off1 = (size_t)b * N;
@@ -1142,7 +1142,7 @@ static int hvp_default_variant(const Geo& g, bool f64, int batch, int nvec) {
 
 template <class T, int TXT, int TYT, bool REMAP>
 static void go_tiled(const Geo& g, const CoefD& kd, int batch, const void* m, const void* c, const uint8_t* mask,
-                     int nvec, long long vbs, const void* V, void* W, const int* done, hipStream_t st) {
+                     int nvec, long long vbs, const void* V, void* W, DoneFlags done, hipStream_t st) {
     const int tx = (g.Lx + TXT - 1) / TXT, ty = (g.Ly + TYT - 1) / TYT;
     hipLaunchKernelGGL((k_hvp_tiled<T, TXT, TYT, REMAP>), dim3(batch * tx * ty), dim3(NT), 0, st, g, coef_cast<T>(kd),
                        (const T*)m, (const T*)c, mask, nvec, vbs, (const T*)V, (T*)W, done, tx, ty);
@@ -1150,7 +1150,7 @@ static void go_tiled(const Geo& g, const CoefD& kd, int batch, const void* m, co
 
 template <class T, int NVP>
 static void go_band(const Geo& g, const CoefD& kd, int batch, const void* m, const void* c, const uint8_t* mask,
-                    int nvec, long long vbs, const void* V, void* W, const int* done, hipStream_t st) {
+                    int nvec, long long vbs, const void* V, void* W, DoneFlags done, hipStream_t st) {
     const int tx = (g.Lx + BD_TX - 1) / BD_TX, ty = (g.Ly + BD_TY - 1) / BD_TY;
     hipLaunchKernelGGL((k_hvp_band<T, NVP>), dim3(batch * tx * ty), dim3(NT), 0, st, g, coef_cast<T>(kd),
                        (const T*)m, (const T*)c, mask, nvec, vbs, (const T*)V, (T*)W, done, tx, ty);
@@ -1158,7 +1158,7 @@ static void go_band(const Geo& g, const CoefD& kd, int batch, const void* m, con
 
 template <class T, int NVP, int XW>
 static void go_march_xw(const Geo& g, const CoefD& kd, int batch, const void* m, const void* c,
-                        const uint8_t* mask, int nvec, long long vbs, const void* V, void* W, const int* done, hipStream_t st) {
+                        const uint8_t* mask, int nvec, long long vbs, const void* V, void* W, DoneFlags done, hipStream_t st) {
     const int ngroups = (nvec + NVP - 1) / NVP;
     const int nstrip = march_strips(g, batch, ngroups, XW > 256 ? 256 : 1024);
     if (mask)
@@ -1173,7 +1173,7 @@ static void go_march_xw(const Geo& g, const CoefD& kd, int batch, const void* m,
 
 template <class T, int NVP>
 static void go_march(const Geo& g, const CoefD& kd, int batch, const void* m, const void* c, const uint8_t* mask,
-                     int nvec, long long vbs, const void* V, void* W, const int* done, hipStream_t st) {
+                     int nvec, long long vbs, const void* V, void* W, DoneFlags done, hipStream_t st) {
     if (g.Lx <= 64)
         go_march_xw<T, NVP, 64>(g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st);
     else if (g.Lx <= 128)
@@ -1186,7 +1186,7 @@ static void go_march(const Geo& g, const CoefD& kd, int batch, const void* m, co
 
 template <class T, int NVP>
 static void go_march2(const Geo& g, const CoefD& kd, int batch, const void* m, const void* c, const uint8_t* mask,
-                      int nvec, long long vbs, const void* V, void* W, const int* done, hipStream_t st) {
+                      int nvec, long long vbs, const void* V, void* W, DoneFlags done, hipStream_t st) {
     const int ngroups = (nvec + NVP - 1) / NVP;
     const int nstrip = march_strips(g, batch, ngroups, g.Lx > 256 ? 256 : 1024);
     const dim3 grid(batch * nstrip * ngroups);
@@ -1212,7 +1212,7 @@ static void go_march2(const Geo& g, const CoefD& kd, int batch, const void* m, c
 // one by one, 8.9 together; 12 of one 128x128: 5.3 and 6.4), in even groups
 template <class T, bool FRAME, bool MORDER>
 static void go_gather(const Geo& g, const CoefD& kd, int batch, const void* m, const void* c, const uint8_t* mask,
-                      int nvec, long long vbs, const void* V, void* W, const int* done, hipStream_t st) {
+                      int nvec, long long vbs, const void* V, void* W, DoneFlags done, hipStream_t st) {
     const long long tiles = (long long)batch * g.tiles;
     const int want = (int)std::min(4LL, std::max(1LL, tiles * nvec / (sizeof(T) == 8 ? 512 : 1536)));
     const int ngroups = (nvec + want - 1) / want;
@@ -1231,7 +1231,7 @@ static void go_gather(const Geo& g, const CoefD& kd, int batch, const void* m, c
 
 template <class T>
 static void go(int v, const Geo& g, const CoefD& kd, int batch, const void* m, const void* c, const uint8_t* mask,
-               int nvec, long long vbs, const void* V, void* W, const int* done, hipStream_t st) {
+               int nvec, long long vbs, const void* V, void* W, DoneFlags done, hipStream_t st) {
     switch (v) {
         case 0: go_tiled<T, 32, 8, false>(g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st); break;
         case 1: go_tiled<T, 32, 8, true>(g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st); break;
@@ -1255,7 +1255,7 @@ static void go(int v, const Geo& g, const CoefD& kd, int batch, const void* m, c
 }
 
 hipError_t launch_hvp_frame(int variant, const Geo& g, const CoefD& kd, bool f64, int batch, const void* m,
-                            const void* c, const uint8_t* mask, int nvec, const void* V, void* W, const int* done,
+                            const void* c, const uint8_t* mask, int nvec, const void* V, void* W, DoneFlags done,
                             hipStream_t st, long long vbs) {
     const int v = hvp_variant_ok(variant, g, f64) ? variant : hvp_default_variant(g, f64, batch, nvec);
     if (vbs <= 0) vbs = (long long)nvec * 2 * g.N;
@@ -1267,7 +1267,7 @@ hipError_t launch_hvp_frame(int variant, const Geo& g, const CoefD& kd, bool f64
 }
 
 hipError_t launch_hvp_ambient(const Geo& g, const CoefD& kd, bool f64, int batch, const void* m, const void* c,
-                              const uint8_t* mask, int nvec, const void* V, void* W, const int* done,
+                              const uint8_t* mask, int nvec, const void* V, void* W, DoneFlags done,
                               hipStream_t st) {
     const long long vbs = (long long)nvec * 3 * g.N;
     if (f64)

@@ -102,12 +102,20 @@ hipError_t launch_param_grad_apply(const Geo& g, int ns, bool f64, int batch, co
 // per device with that device current); ENERGY_SCRATCH_BYTES long.
 constexpr size_t ENERGY_SCRATCH_BYTES = MOTO_NOALLOC_SCRATCH_BYTES;
 hipError_t energy_scratch(double** out);
+// Device flags that turn an HVP into a no-op, one per lattice `stride` ints
+// apart (stride 0: one for all); null: none.
+struct DoneFlags {
+    const int* p = nullptr;
+    int stride = 0;
+    DoneFlags(const int* flag = nullptr, int st = 0) : p(flag), stride(st) {}
+    __device__ __forceinline__ bool operator()(int b) const { return p != nullptr && p[(size_t)b * stride] != 0; }
+};
 // variant: frame-layout kernel variant (-1 = default choice), see hvp.hip;
 // vbs: elements from one lattice's vector block to the next (0 = nvec
 // vectors back to back)
 hipError_t launch_tangent_hvp(const Geo& g, const CoefD& k, bool f64, bool frame, int batch, const void* m,
                               const void* c, const uint8_t* mask, int nvec, const void* V, void* W,
-                              const int* done, hipStream_t st, int variant = -1, long long vbs = 0);
+                              DoneFlags done, hipStream_t st, int variant = -1, long long vbs = 0);
 
 // ---- shells.hip: general-shell lattice kernels (more than three shells) ----
 // part: the energy of each of the *tiles tiles a lattice is cut into (at most
@@ -117,18 +125,18 @@ hipError_t launch_energy_grad_gen(const Geo& g, const CoefD& k, bool f64, int ba
                                   hipStream_t st);
 hipError_t launch_tangent_hvp_gen(const Geo& g, const CoefD& k, bool f64, bool frame, int batch, const void* m,
                                   const void* c, const uint8_t* mask, int nvec, long long vbs, const void* V, void* W,
-                                  const int* done, hipStream_t st);
+                                  DoneFlags done, hipStream_t st);
 
 // ---- hvp.hip: frame-layout tangent HVP variants (tile shapes / staging) ----
 constexpr int HVP_NVARIANTS = 14;
 bool hvp_variant_ok(int variant, const Geo& g, bool f64);
 const char* hvp_variant_name(int variant);
 hipError_t launch_hvp_frame(int variant, const Geo& g, const CoefD& k, bool f64, int batch, const void* m,
-                            const void* c, const uint8_t* mask, int nvec, const void* V, void* W, const int* done,
+                            const void* c, const uint8_t* mask, int nvec, const void* V, void* W, DoneFlags done,
                             hipStream_t st, long long vbs = 0);
 // ambient layout, vectors back to back
 hipError_t launch_hvp_ambient(const Geo& g, const CoefD& k, bool f64, int batch, const void* m, const void* c,
-                              const uint8_t* mask, int nvec, const void* V, void* W, const int* done,
+                              const uint8_t* mask, int nvec, const void* V, void* W, DoneFlags done,
                               hipStream_t st);
 hipError_t launch_hessian_apply(const Geo& g, const CoefD& k, bool f64, int batch, int nvec, const void* V,
                                 void* W, hipStream_t st);

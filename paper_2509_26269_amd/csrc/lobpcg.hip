@@ -39,7 +39,6 @@ constexpr int GQ = (GENT + NT - 1) / NT;             // entries per thread
 constexpr int OENT = MAXS * MAXB;                    // orthonormalisation Gram entries
 constexpr int OQ = (OENT + NT - 1) / NT;
 constexpr int PSTRIDE = GENT;                        // doubles per block partial row
-constexpr int RED_BLOCKS = 64;                       // workgroups of the partial-row reduction
 typedef double mf_d4 __attribute__((ext_vector_type(4)));  // accumulator of a 16x16x4 FP64 product
 constexpr int UKS = MAXS / 4;                        // k-steps of 4 basis columns
 constexpr int UPDATE_MFMA_MIN_MB = 5;                // block widths whose FP32 row kernels run on the matrix cores
@@ -246,6 +245,78 @@ __global__ __launch_bounds__(NT) void k_orth_gram(EigArgs a, int target, const T
     }
 }
 
+// Narrow blocks (3 mb <= SCOL columns: k = 1 and 2 with their default guard).
+// The general kernels size their staging and entry lists for 48 columns and
+// keep a quarter of a compute unit's waves; here a thread owns one entry, and
+// the next chunk's loads are in flight under the dot products of the current
+// one.  Entries, chunk order and dot products are the general kernels', so the
+// sums keep their bits.  24 x 128x128 FP32, k = 2: Gram 25 -> 17.5 us a
+// call, orthonormalisation Gram 13 -> 8.3.
+constexpr int SCOL = 12;
+template <class T>
+struct SmallChunk {
+    static constexpr int Q = SCOL * RCH / NT;  // staged values per thread (of one matrix)
+    static_assert(NT % RCH == 0 && SCOL * RCH % NT == 0, "whole columns per pass");
+    T ts[SCOL][RCHP<T>];
+    // column (and row rr = thread % RCH) of this thread's value q
+    static __device__ __forceinline__ int col(int q) { return (int)threadIdx.x / RCH + q * (NT / RCH); }
+    __device__ __forceinline__ void put(const T (&v)[Q]) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) ts[col(q)][threadIdx.x % RCH] = v[q];
+    }
+};
+
+template <class T, bool MSK>
+__global__ __launch_bounds__(NT) void k_orth_gram_small(EigArgs a, int target, const T* __restrict__ S,
+                                                        double* __restrict__ part,
+                                                        const EigCtrl* __restrict__ ctrl) {
+    S += blockIdx.y * a.s_ms;
+    part += blockIdx.y * a.part_ms;
+    ctrl += blockIdx.y;
+    if (ctrl->done || (target == 2 && ctrl->orth_skip)) return;
+    using SC = SmallChunk<T>;
+    __shared__ __align__(16) SC sc;
+    const int mb = a.mb, n2 = a.n2;
+    const int nq = target >= 1 ? mb + ctrl->np : 0, t0 = target == 0 ? 0 : mb;
+    const int nrow = nq + mb, E = nrow * mb;
+    const uint8_t* mk = MSK ? member_mask(a) : nullptr;
+    const int rr = threadIdx.x % RCH;
+    // physical column of staged column c: X, then P, then the target
+    const T* src[SC::Q];
+    bool use[SC::Q];
+#pragma unroll
+    for (int q = 0; q < SC::Q; ++q) {
+        const int c = SC::col(q);
+        use[q] = c < nrow;
+        src[q] = S + (size_t)(c >= nq ? t0 + (c - nq) : c < mb ? c : mb + c) * n2 + rr;
+    }
+    T v[SC::Q];
+    bool in = false;
+    auto load = [&](int ch) {
+        const int r0 = ch * RCH;
+        in = r0 + rr < n2 && (!MSK || row_active(mk, a.Nsite, r0 + rr));
+#pragma unroll
+        for (int q = 0; q < SC::Q; ++q) v[q] = in && use[q] ? src[q][r0] : T(0);
+    };
+    const int e = threadIdx.x, j = e / nrow, i = e - j * nrow;
+    double acc = 0.0;
+    const int nchunks = (n2 + RCH - 1) / RCH;
+    if ((int)blockIdx.x < nchunks) load(blockIdx.x);
+    for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
+        bool any = true;
+        if constexpr (MSK)
+            any = __syncthreads_or(in) != 0;
+        else
+            __syncthreads();
+        if (any) sc.put(v);
+        if (ch + (int)gridDim.x < nchunks) load(ch + gridDim.x);
+        if (!any) continue;
+        __syncthreads();
+        if (e < E) acc += dot_chunk(sc.ts[i], sc.ts[nq + j]);
+    }
+    if (e < E) part[(size_t)blockIdx.x * PSTRIDE + e] = acc;
+}
+
 // The orthonormalisation Gram and transform on the matrix cores (FP32 blocks,
 // the same lane layout as the Rayleigh-Ritz products below).  Gram: staged
 // columns [Q Y] (nrow = nq + mb, up to three 16-column tiles) against the
@@ -372,12 +443,17 @@ __global__ __launch_bounds__(NT) void k_orth_apply_mfma(EigArgs a, int target, f
     }
 }
 
-// Multi-block fixed-order reduction of per-block partial rows:
+// Fixed-order reduction of per-block partial rows over many workgroups:
 // G[e] = sum_b part[b][e] over the entries in use (kind 0: orthonormalisation
 // Gram of `arg` = target, kind 1: Rayleigh-Ritz Grams of `arg` = ns_fixed).
-// One wavefront per entry: lane l sums blocks l, l + 64, ..., then a fixed
-// butterfly across the lanes.
-__global__ __launch_bounds__(NT) void k_reduce_rows(EigArgs a, const double* __restrict__ part, int nblk, int kind,
+// Slot s of 64 sums blocks s, s + 64, ..., then a fixed butterfly adds the
+// slots.  A wave takes eight neighbouring entries: lane 8 g + e holds slots
+// g, g + 8, ... of entry e, so that the eight lanes of a group read 64
+// consecutive bytes and the butterfly's first three levels stay in the lane
+// (the wave-per-entry form, each lane a line of its own, fetched sixteen
+// times the bytes: 6.3 us a call for 24 members, k = 2, now 4.5).
+constexpr int RED_E = 8;
+__global__ __launch_bounds__(WL) void k_reduce_rows(EigArgs a, const double* __restrict__ part, int nblk, int kind,
                                                     int arg, double* __restrict__ G,
                                                     const EigCtrl* __restrict__ ctrl) {
     part += blockIdx.y * a.part_ms;
@@ -392,15 +468,30 @@ __global__ __launch_bounds__(NT) void k_reduce_rows(EigArgs a, const double* __r
         const int ns = sol_ns(a, ctrl, arg);
         E = ns * (ns + 1);
     }
-    const int lane = threadIdx.x & 63;
-    const int nw = gridDim.x * (NT / 64);
-    for (int e = blockIdx.x * (NT / 64) + (threadIdx.x >> 6); e < E; e += nw) {
-        double s = 0.0;
-#pragma unroll 4  // several loads in flight per lane
-        for (int b = lane; b < nblk; b += 64) s += part[(size_t)b * PSTRIDE + e];
-        s = wave_sum(s);
-        if (lane == 0) G[e] = s;
+    const int e = blockIdx.x * RED_E + threadIdx.x % RED_E, g = threadIdx.x / RED_E;
+    if (blockIdx.x * RED_E >= E) return;
+    const bool on = e < E;
+    const double* p = part + (on ? e : E - 1);
+    constexpr int SL = WL / RED_E;  // slots per lane
+    double s[SL];
+#pragma unroll
+    for (int t = 0; t < SL; ++t) s[t] = 0.0;
+#pragma unroll 2
+    for (int b0 = 0; b0 < nblk; b0 += WL) {
+        double x[SL];  // all in flight: no test stands before a load
+#pragma unroll
+        for (int t = 0; t < SL; ++t) x[t] = p[(size_t)min(b0 + t * SL + g, nblk - 1) * PSTRIDE];
+#pragma unroll
+        for (int t = 0; t < SL; ++t) s[t] += b0 + t * SL + g < nblk ? x[t] : 0.0;
     }
+#pragma unroll
+    for (int o = SL / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int t = 0; t < o; ++t) s[t] += s[t + o];
+    double v = s[0];
+#pragma unroll
+    for (int o = WL / 2; o >= RED_E; o >>= 1) v += __shfl_xor(v, o, WL);
+    if (g == 0 && on) G[e] = v;
 }
 
 __global__ __launch_bounds__(WL) void k_orth_small(EigArgs a, int target, const double* __restrict__ G,
@@ -560,6 +651,62 @@ __global__ __launch_bounds__(NT) void k_gram(EigArgs a, int ns_fixed, const T* _
         const int e = threadIdx.x + q * NT;
         if (e < E) part[(size_t)blockIdx.x * PSTRIDE + e] = acc[q];
     }
+}
+
+template <class T, bool MSK>
+__global__ __launch_bounds__(NT) void k_gram_small(EigArgs a, int ns_fixed, const T* __restrict__ S,
+                                                   const T* __restrict__ HS, double* __restrict__ part,
+                                                   const EigCtrl* __restrict__ ctrl) {
+    S += blockIdx.y * a.s_ms;
+    HS += blockIdx.y * a.s_ms;
+    part += blockIdx.y * a.part_ms;
+    ctrl += blockIdx.y;
+    if (ctrl->done) return;
+    using SC = SmallChunk<T>;
+    __shared__ __align__(16) SC ss, sh;
+    static_assert(SCOL * (SCOL + 1) <= NT, "one entry per thread");
+    const int n2 = a.n2;
+    const int ns = sol_ns(a, ctrl, ns_fixed);
+    const int Eh = ns * (ns + 1) / 2, E = 2 * Eh;
+    const uint8_t* mk = MSK ? member_mask(a) : nullptr;
+    const int rr = threadIdx.x % RCH;
+    T v[SC::Q], w[SC::Q];
+    bool in = false;
+    auto load = [&](int ch) {
+        const int r = ch * RCH + rr;
+        in = r < n2 && (!MSK || row_active(mk, a.Nsite, r));
+#pragma unroll
+        for (int q = 0; q < SC::Q; ++q) {
+            const size_t o = (size_t)SC::col(q) * n2 + r;
+            const bool on = in && SC::col(q) < ns;
+            v[q] = on ? S[o] : T(0);
+            w[q] = on ? HS[o] : T(0);
+        }
+    };
+    const int e = threadIdx.x;
+    int i = 0, j = 0;
+    if (e < E) tri_index(e < Eh ? e : e - Eh, ns, i, j);
+    const T* x = ss.ts[i];
+    const T* y = e < Eh ? sh.ts[j] : ss.ts[j];
+    double acc = 0.0;
+    const int nchunks = (n2 + RCH - 1) / RCH;
+    if ((int)blockIdx.x < nchunks) load(blockIdx.x);
+    for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
+        bool any = true;
+        if constexpr (MSK)
+            any = __syncthreads_or(in) != 0;
+        else
+            __syncthreads();
+        if (any) {
+            ss.put(v);
+            sh.put(w);
+        }
+        if (ch + (int)gridDim.x < nchunks) load(ch + gridDim.x);
+        if (!any) continue;
+        __syncthreads();
+        if (e < E) acc += dot_chunk(x, y);
+    }
+    if (e < E) part[(size_t)blockIdx.x * PSTRIDE + e] = acc;
 }
 
 // The Rayleigh-Ritz Grams on the matrix cores (FP32 blocks): a wave takes
@@ -1150,14 +1297,20 @@ hipError_t launch_orth(bool f64, const EigArgs& a, int target, void* S, double* 
     else
         go_mask(a, [&](auto mk) {
             constexpr bool M = decltype(mk)::value;
-            if (f64)
+            if (3 * a.mb <= SCOL) {
+                if (f64)
+                    hipLaunchKernelGGL((k_orth_gram_small<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, target,
+                                       (const double*)S, part, ctrl);
+                else
+                    hipLaunchKernelGGL((k_orth_gram_small<float, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, target,
+                                       (const float*)S, part, ctrl);
+            } else  // FP32 blocks this wide run on the matrix cores
                 hipLaunchKernelGGL((k_orth_gram<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, target,
                                    (const double*)S, part, ctrl);
-            else
-                hipLaunchKernelGGL((k_orth_gram<float, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, target,
-                                   (const float*)S, part, ctrl);
         });
-    hipLaunchKernelGGL(k_reduce_rows, dim3(RED_BLOCKS, a.P), dim3(NT), 0, st, a, part, nblk, 0, target, G, ctrl);
+    const int E = (target == 0 ? 1 : 3) * a.mb * a.mb;
+    hipLaunchKernelGGL(k_reduce_rows, dim3((E + RED_E - 1) / RED_E, a.P), dim3(WL), 0, st, a, part, nblk, 0, target, G,
+                       ctrl);
     hipLaunchKernelGGL(k_orth_small, dim3(1, a.P), dim3(WL), 0, st, a, target, G, ctrl);
     const int nb = update_blocks(a.n2, f64, a.mb);
     if (mf) {
@@ -1171,7 +1324,7 @@ hipError_t launch_orth(bool f64, const EigArgs& a, int target, void* S, double* 
             if (f64)
                 hipLaunchKernelGGL((k_orth_apply<double, W, M>), dim3(nb, a.P), dim3(NT), 0, st, a, target,
                                    (double*)S, ctrl);
-            else
+            else if constexpr (W < UPDATE_MFMA_MIN_MB)
                 hipLaunchKernelGGL((k_orth_apply<float, W, M>), dim3(nb, a.P), dim3(NT), 0, st, a, target,
                                    (float*)S, ctrl);
         });
@@ -1187,14 +1340,20 @@ hipError_t launch_gram(bool f64, const EigArgs& a, int ns, const void* S, const 
     else
         go_mask(a, [&](auto mk) {
             constexpr bool M = decltype(mk)::value;
-            if (f64)
+            if (3 * a.mb <= SCOL) {
+                if (f64)
+                    hipLaunchKernelGGL((k_gram_small<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns,
+                                       (const double*)S, (const double*)HS, part, ctrl);
+                else
+                    hipLaunchKernelGGL((k_gram_small<float, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns,
+                                       (const float*)S, (const float*)HS, part, ctrl);
+            } else
                 hipLaunchKernelGGL((k_gram<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (const double*)S,
                                    (const double*)HS, part, ctrl);
-            else
-                hipLaunchKernelGGL((k_gram<float, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (const float*)S,
-                                   (const float*)HS, part, ctrl);
         });
-    hipLaunchKernelGGL(k_reduce_rows, dim3(RED_BLOCKS, a.P), dim3(NT), 0, st, a, part, nblk, 1, ns, G, ctrl);
+    const int E = 3 * a.mb * (3 * a.mb + 1);
+    hipLaunchKernelGGL(k_reduce_rows, dim3((E + RED_E - 1) / RED_E, a.P), dim3(WL), 0, st, a, part, nblk, 1, ns, G,
+                       ctrl);
     return hipGetLastError();
 }
 
@@ -1216,7 +1375,7 @@ hipError_t launch_update(bool f64, const EigArgs& a, int ns, void* S, void* HS, 
             if (f64)
                 hipLaunchKernelGGL((k_update<double, W, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (double*)S,
                                    (double*)HS, part, ctrl);
-            else
+            else if constexpr (W < UPDATE_MFMA_MIN_MB)
                 hipLaunchKernelGGL((k_update<float, W, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (float*)S,
                                    (float*)HS, part, ctrl);
         });

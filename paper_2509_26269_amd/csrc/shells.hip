@@ -300,12 +300,12 @@ __global__ __launch_bounds__(TL::NTH) void k_tangent_hvp_gen(Geo g, GenCoef<T, N
                                                              const T* __restrict__ c,
                                                              const uint8_t* __restrict__ mask, int nvec,
                                                              long long vbs, const T* __restrict__ V,
-                                                             T* __restrict__ W, const int* __restrict__ done) {
-    if (done != nullptr && *done) return;
+                                                             T* __restrict__ W, DoneFlags done) {
     constexpr int DV = FRAME ? 2 : 3;
     __shared__ __align__(16) TL L;
     const int j = blockIdx.x % nvec;
     const GenPos t = gen_pos<TL>(g, blockIdx.x / nvec);
+    if (done(t.b)) return;
     const size_t N = g.N;
     const T* mb = m + (size_t)t.b * 3 * N;
     const uint8_t* mk = mask ? mask + (size_t)t.b * N : nullptr;
@@ -425,7 +425,7 @@ hipError_t launch_energy_grad_gen(const Geo& g, const CoefD& kd, bool f64, int b
 
 hipError_t launch_tangent_hvp_gen(const Geo& g, const CoefD& kd, bool f64, bool frame, int batch, const void* m,
                                   const void* c, const uint8_t* mask, int nvec, long long vbs, const void* V, void* W,
-                                  const int* done, hipStream_t st) {
+                                  DoneFlags done, hipStream_t st) {
     if (!kd.gen || kd.gen->ns > GEN_MAX_SHELLS) return hipErrorInvalidValue;
     if (vbs <= 0) vbs = (long long)nvec * (frame ? 2 : 3) * g.N;
     auto go = [&](auto tc, auto fc) {

@@ -448,7 +448,7 @@ hipError_t launch_param_grad_apply(const Geo& g, int ns, bool f64, int batch, co
 
 hipError_t launch_tangent_hvp(const Geo& g, const CoefD& kd, bool f64, bool frame, int batch, const void* m,
                               const void* c, const uint8_t* mask, int nvec, const void* V, void* W,
-                              const int* done, hipStream_t st, int variant, long long vbs) {
+                              DoneFlags done, hipStream_t st, int variant, long long vbs) {
     if (kd.gen) return launch_tangent_hvp_gen(g, kd, f64, frame, batch, m, c, mask, nvec, vbs, V, W, done, st);
     if (frame) return launch_hvp_frame(variant, g, kd, f64, batch, m, c, mask, nvec, V, W, done, st, vbs);
     if (vbs > 0 && vbs != (long long)nvec * 3 * g.N) return hipErrorInvalidValue;
