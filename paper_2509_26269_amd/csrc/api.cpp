@@ -539,8 +539,8 @@ static moto_status min_modes_pop_impl(moto_plan p, moto_dtype hvp, int P, const 
     // start: orthonormal X; HX = H X; Rayleigh-Ritz on span(X); W = HX - X Lam
     for (int pass = 0; pass < 2; ++pass) HIP_TRY(launch_orth(f64, a, 0, S, part, nbg, G, ctrl, st));
     HIP_TRY(launch_tangent_hvp(p->g, p->k, f64, true, P, mT, cT, mask, L.mb, S, HS, hv_done, st, hv_var, vbs));
-    HIP_TRY(launch_gram(f64, a, L.mb, S, HS, part, nbg, G, ctrl, st));
-    HIP_TRY(launch_rr(a, L.mb, G, ctrl, st));
+    HIP_TRY(launch_gram(f64, a, L.mb, S, HS, part, nbg, ctrl, st));
+    HIP_TRY(launch_rr(a, L.mb, part, nbg, G, ctrl, st));
     HIP_TRY(launch_update(f64, a, L.mb, S, HS, part, nbu, ctrl, st));
     HIP_TRY(launch_eig_control(a, part, nbu, ctrl, 1, st));
     if (P > 1) HIP_TRY(launch_eig_all_done(a, ctrl, all_done, st));
@@ -554,8 +554,8 @@ static moto_status min_modes_pop_impl(moto_plan p, moto_dtype hvp, int P, const 
             }
             hipError_t e = launch_tangent_hvp(p->g, p->k, f64, true, P, mT, cT, mask, L.mb, Wslot, HWslot, hv_done,
                                               s, hv_var, vbs);
-            if (e == hipSuccess) e = launch_gram(f64, a, -1, S, HS, part, nbg, G, ctrl, s);
-            if (e == hipSuccess) e = launch_rr(a, -1, G, ctrl, s);
+            if (e == hipSuccess) e = launch_gram(f64, a, -1, S, HS, part, nbg, ctrl, s);
+            if (e == hipSuccess) e = launch_rr(a, -1, part, nbg, G, ctrl, s);
             if (e == hipSuccess) e = launch_update(f64, a, -1, S, HS, part, nbu, ctrl, s);
             if (e == hipSuccess) e = launch_eig_control(a, part, nbu, ctrl, 0, s);
             if (e != hipSuccess) return e;

@@ -266,43 +266,60 @@ __device__ __forceinline__ double wmax_dpp(double v) {
 // 1, p_0, ..., p_(n-1) with p_i = (dh_i - x) p_(i-1) - e2s_i p_(i-2)
 // (e2s_i: squared off-diagonal between i - 1 and i, e2s_0 = 0); an exact zero
 // takes the sign opposite to its predecessor (a tiny negative pivot).  The
-// coefficients come from LDS sixteen at a time.  Entries n .. NM-1 are
+// coefficients come from LDS, four rows at a time.  Entries n .. NM-1 are
 // padding (dh = 4, e2s = 0: p_i = (4 - x) p_(i-1) keeps the sign for
-// |x| <= 1), so the steps of a chunk need no per-step test of i < n.
-template <int NM>
-__device__ __forceinline__ int sturm_below(const double* dh, const double* e2s, int n, double x) {
+// |x| <= 1), so the steps of a group need no per-step test of i < n.
+//
+// A step costs its instructions (one wave on the SIMD): the recurrence, the
+// sign change from the sign bits, and the smallest |p| so far.  Only when that
+// is zero, which exact arithmetic on structured matrices can make it, are the
+// counts taken again with the zero's sign fixed step by step (SLOW).  Powers
+// of two keep |p| in range: a step shrinks it by 2^-56 at most (x and dh on a
+// grid of that size) and grows it by 3.  A round of 16 rows took 1260 cycles
+// with zero test, comparisons and range test in the steps, 12 of them 6.3 us
+// of a Rayleigh-Ritz step.
+template <int NM, bool SLOW>
+__device__ __forceinline__ int sturm_count(const double* dh, const double* e2s, int n, double x, double& least) {
     double pp = 0.0, p = 1.0;
     int cnt = 0;
 #pragma unroll
-    for (int c0 = 0; c0 < NM; c0 += 16) {
+    for (int c0 = 0; c0 < NM; c0 += 4) {
         if (c0 < n) {
             // the first 32 coefficients may stay in registers across calls;
-            // later chunks are reloaded (bounds the register footprint)
-            if (c0 >= 32) asm volatile("" ::: "memory");
-            constexpr int QN = 16;
-            double dc[QN], ec[QN];
+            // later ones are reloaded (bounds the register footprint)
+            if (c0 >= 32 && c0 % 16 == 0) asm volatile("" ::: "memory");
+            double dc[4], ec[4];
 #pragma unroll
-            for (int q = 0; q < QN; ++q) {
-                dc[q] = c0 + q < NM ? dh[c0 + q] : 4.0;
-                ec[q] = c0 + q < NM ? e2s[c0 + q] : 0.0;
+            for (int q = 0; q < 4; ++q) {
+                dc[q] = dh[c0 + q];
+                ec[q] = e2s[c0 + q];
             }
 #pragma unroll
-            for (int q = 0; q < QN; ++q) {
-                if (c0 + q < NM) {
-                    double pn = fma(dc[q] - x, p, -(ec[q] * pp));
+            for (int q = 0; q < 4; ++q) {
+                double pn = fma(dc[q] - x, p, -(ec[q] * pp));
+                if constexpr (SLOW)
                     pn = pn == 0.0 ? -p * 0x1p-52 : pn;
-                    cnt += (pn < 0.0) != (p < 0.0);
-                    pp = p;
-                    p = pn;
-                    if ((q & 3) == 3) {
-                        const double f = fmax(fabs(p), fabs(pp)) < 0x1p-600 ? 0x1p600 : 1.0;
-                        p *= f;
-                        pp *= f;
-                    }
-                }
+                else
+                    least = fmin(least, fabs(pn));
+                cnt += (unsigned)(__double2hiint(pn) ^ __double2hiint(p)) >> 31;
+                pp = p;
+                p = pn;
+            }
+            if (c0 % 8 == 4 && c0 + 4 < NM) {
+                const double f = fmax(fabs(p), fabs(pp)) < 0x1p-400 ? 0x1p400 : 1.0;
+                p *= f;
+                pp *= f;
             }
         }
     }
+    return cnt;
+}
+template <int NM>
+__device__ __forceinline__ int sturm_below(const double* dh, const double* e2s, int n, double x) {
+    static_assert(NM % 4 == 0, "groups of four rows");
+    double least = 1.0;
+    int cnt = sturm_count<NM, false>(dh, e2s, n, x, least);
+    if (__any(least == 0.0)) cnt = sturm_count<NM, true>(dh, e2s, n, x, least);
     return cnt;
 }
 

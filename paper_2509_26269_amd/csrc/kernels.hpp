@@ -243,10 +243,12 @@ hipError_t launch_eig_init(bool f64, const EigArgs& a, void* S, const double* m,
 // first was well conditioned), in place.
 hipError_t launch_orth(bool f64, const EigArgs& a, int target, void* S, double* part, int nblk, double* G,
                        EigCtrl* ctrl, hipStream_t st);
+// Per-block rows of the Grams S^T HS and S^T S; launch_rr sums them (in G).
 hipError_t launch_gram(bool f64, const EigArgs& a, int ns, const void* S, const void* HS, double* part, int nblk,
-                       double* G, const EigCtrl* ctrl, hipStream_t st);
+                       const EigCtrl* ctrl, hipStream_t st);
 int gram_blocks(int n2);
-hipError_t launch_rr(const EigArgs& a, int ns, const double* G, EigCtrl* ctrl, hipStream_t st);
+hipError_t launch_rr(const EigArgs& a, int ns, const double* part, int nblk, double* G, EigCtrl* ctrl,
+                     hipStream_t st);
 hipError_t launch_update(bool f64, const EigArgs& a, int ns, void* S, void* HS, double* part, int nblk,
                          EigCtrl* ctrl, hipStream_t st);
 int update_blocks(int n2, bool f64, int mb);  // row-update workgroups (same rule as the launchers)

@@ -41,6 +41,9 @@ constexpr int OQ = (OENT + NT - 1) / NT;
 constexpr int PSTRIDE = GENT;                        // doubles per block partial row
 typedef double mf_d4 __attribute__((ext_vector_type(4)));  // accumulator of a 16x16x4 FP64 product
 constexpr int UKS = MAXS / 4;                        // k-steps of 4 basis columns
+constexpr int SCOL = 12;                               // narrow: 3 mb <= SCOL (k = 1, 2 with their default guard)
+constexpr int SORTH = SCOL * (SCOL / 3);               // their orthonormalisation and
+constexpr int SGRAM = SCOL * (SCOL + 1);               // Rayleigh-Ritz Gram entries
 constexpr int UPDATE_MFMA_MIN_MB = 5;                // block widths whose FP32 row kernels run on the matrix cores
 
 // staged chunk of one basis column: the row is padded by 16 bytes, so that the
@@ -252,7 +255,6 @@ __global__ __launch_bounds__(NT) void k_orth_gram(EigArgs a, int target, const T
 // one.  Entries, chunk order and dot products are the general kernels', so the
 // sums keep their bits.  24 x 128x128 FP32, k = 2: Gram 25 -> 17.5 us a
 // call, orthonormalisation Gram 13 -> 8.3.
-constexpr int SCOL = 12;
 template <class T>
 struct SmallChunk {
     static constexpr int Q = SCOL * RCH / NT;  // staged values per thread (of one matrix)
@@ -453,25 +455,8 @@ __global__ __launch_bounds__(NT) void k_orth_apply_mfma(EigArgs a, int target, f
 // (the wave-per-entry form, each lane a line of its own, fetched sixteen
 // times the bytes: 6.3 us a call for 24 members, k = 2, now 4.5).
 constexpr int RED_E = 8;
-__global__ __launch_bounds__(WL) void k_reduce_rows(EigArgs a, const double* __restrict__ part, int nblk, int kind,
-                                                    int arg, double* __restrict__ G,
-                                                    const EigCtrl* __restrict__ ctrl) {
-    part += blockIdx.y * a.part_ms;
-    G += blockIdx.y * a.g_ms;
-    ctrl += blockIdx.y;
-    if (ctrl->done || (kind == 0 && arg == 2 && ctrl->orth_skip)) return;
-    int E;
-    if (kind == 0) {
-        const int nq = arg >= 1 ? a.mb + ctrl->np : 0;
-        E = (nq + a.mb) * a.mb;
-    } else {
-        const int ns = sol_ns(a, ctrl, arg);
-        E = ns * (ns + 1);
-    }
-    const int e = blockIdx.x * RED_E + threadIdx.x % RED_E, g = threadIdx.x / RED_E;
-    if (blockIdx.x * RED_E >= E) return;
-    const bool on = e < E;
-    const double* p = part + (on ? e : E - 1);
+__device__ __forceinline__ double reduce_entry(const double* __restrict__ part, int nblk, int e, int g) {
+    const double* p = part + e;
     constexpr int SL = WL / RED_E;  // slots per lane
     double s[SL];
 #pragma unroll
@@ -491,7 +476,53 @@ __global__ __launch_bounds__(WL) void k_reduce_rows(EigArgs a, const double* __r
     double v = s[0];
 #pragma unroll
     for (int o = WL / 2; o >= RED_E; o >>= 1) v += __shfl_xor(v, o, WL);
-    if (g == 0 && on) G[e] = v;
+    return v;
+}
+
+__device__ __forceinline__ int orth_nq(const EigArgs& a, int target, const EigCtrl* ctrl) {
+    return target >= 1 ? a.mb + ctrl->np : 0;
+}
+
+__global__ __launch_bounds__(WL) void k_reduce_rows(EigArgs a, const double* __restrict__ part, int nblk, int kind,
+                                                    int arg, double* __restrict__ G,
+                                                    const EigCtrl* __restrict__ ctrl) {
+    part += blockIdx.y * a.part_ms;
+    G += blockIdx.y * a.g_ms;
+    ctrl += blockIdx.y;
+    if (ctrl->done || (kind == 0 && arg == 2 && ctrl->orth_skip)) return;
+    int E;
+    if (kind == 0) {
+        E = (orth_nq(a, arg, ctrl) + a.mb) * a.mb;
+    } else {
+        const int ns = sol_ns(a, ctrl, arg);
+        E = ns * (ns + 1);
+    }
+    if ((int)blockIdx.x * RED_E >= E) return;
+    const int e = blockIdx.x * RED_E + threadIdx.x % RED_E, g = threadIdx.x / RED_E;
+    const double v = reduce_entry(part, nblk, min(e, E - 1), g);
+    if (g == 0 && e < E) G[e] = v;
+}
+
+// The same by the waves of one workgroup, into LDS (narrow blocks: their few
+// entries are read faster by the workgroup that uses them than by a launch of
+// their own; ends with a barrier).
+__device__ __forceinline__ void reduce_rows_wg(const double* __restrict__ part, int nblk, int E, double* Gl) {
+    const int ln = threadIdx.x % WL, g = ln / RED_E;
+    for (int e0 = (int)threadIdx.x / WL * RED_E; e0 < E; e0 += (int)blockDim.x / WL * RED_E) {
+        const int e = e0 + ln % RED_E;
+        const double v = reduce_entry(part, nblk, min(e, E - 1), g);
+        if (g == 0 && e < E) Gl[e] = v;
+    }
+    __syncthreads();
+}
+
+// after a first pass that kept every column, lost at most half of each
+// column's norm to the projection and met an inverse Cholesky factor with
+// pivots above 0.1, the block is orthonormal and orthogonal to [X P] to a
+// few FP32 roundings, which the Rayleigh-Ritz step's near-identity series
+// absorbs: the second pass is not needed
+__device__ __forceinline__ void orth_settle(int target, bool settled, EigCtrl* ctrl) {
+    if (target == 1 && wlane() == 0) ctrl->orth_skip = settled ? 1 : 0;
 }
 
 __global__ __launch_bounds__(WL) void k_orth_small(EigArgs a, int target, const double* __restrict__ G,
@@ -499,14 +530,25 @@ __global__ __launch_bounds__(WL) void k_orth_small(EigArgs a, int target, const 
     G += blockIdx.y * a.g_ms;
     ctrl += blockIdx.y;
     if (ctrl->done || (target == 2 && ctrl->orth_skip)) return;
-    const int nq = target >= 1 ? a.mb + ctrl->np : 0;
-    const bool settled = orth_small_body<MAXS + 1>(a.mb, nq, a.drop, G, ctrl->Bw, ctrl->Tw);
-    // after a first pass that kept every column, lost at most half of each
-    // column's norm to the projection and met an inverse Cholesky factor with
-    // pivots above 0.1, the block is orthonormal and orthogonal to [X P] to a
-    // few FP32 roundings, which the Rayleigh-Ritz step's near-identity series
-    // absorbs: the second pass is not needed
-    if (target == 1 && wlane() == 0) ctrl->orth_skip = settled ? 1 : 0;
+    orth_settle(target,
+                orth_small_body<MAXS + 1>(a.mb, orth_nq(a, target, ctrl), a.drop, G, ctrl->Bw, ctrl->Tw), ctrl);
+}
+
+// Narrow blocks: the reduction and the small step in one launch, the matrices
+// sized for their basis (the reduction's 3.3 us and a launch gap saved twice
+// an iteration, of 78 us at 64x64, k = 2 FP64).
+constexpr int SORTH_WAVES = (SORTH + RED_E - 1) / RED_E;
+__global__ __launch_bounds__(SORTH_WAVES * WL) void k_orth_small_narrow(EigArgs a, int target,
+                                                                        const double* __restrict__ part, int nblk,
+                                                                        EigCtrl* __restrict__ ctrl) {
+    part += blockIdx.y * a.part_ms;
+    ctrl += blockIdx.y;
+    if (ctrl->done || (target == 2 && ctrl->orth_skip)) return;
+    __shared__ double Gl[SORTH];
+    const int nq = orth_nq(a, target, ctrl);
+    reduce_rows_wg(part, nblk, (nq + a.mb) * a.mb, Gl);
+    if (threadIdx.x >= WL) return;
+    orth_settle(target, orth_small_body<SCOL + 1>(a.mb, nq, a.drop, Gl, ctrl->Bw, ctrl->Tw), ctrl);
 }
 
 // Row kernels on the vector ALUs (k_orth_apply, k_update).  MB: compile-time
@@ -820,6 +862,18 @@ __global__ __launch_bounds__(RR_WAVES * WL) void k_rr(EigArgs a, int ns_fixed, c
     ctrl += blockIdx.y;
     if (ctrl->done) return;
     rr_body<MAXS + 1, RR_WAVES>(a.mb, sol_ns(a, ctrl, ns_fixed), a.drop, Gtri, ctrl);
+}
+
+// Narrow blocks: the reduction of the Grams and the step in one launch.
+__global__ __launch_bounds__(RR_WAVES * WL) void k_rr_narrow(EigArgs a, int ns_fixed, const double* __restrict__ part,
+                                                             int nblk, EigCtrl* __restrict__ ctrl) {
+    part += blockIdx.y * a.part_ms;
+    ctrl += blockIdx.y;
+    if (ctrl->done) return;
+    __shared__ double Gl[SGRAM];
+    const int ns = sol_ns(a, ctrl, ns_fixed);
+    reduce_rows_wg(part, nblk, ns * (ns + 1), Gl);
+    rr_body<SCOL + 1, RR_WAVES>(a.mb, ns, a.drop, Gl, ctrl);
 }
 
 // --------------------------------------------------------------------------
@@ -1288,6 +1342,8 @@ static void go_mask(const EigArgs& a, F&& f) {
         f(std::false_type{});
 }
 
+static bool narrow(const EigArgs& a) { return 3 * a.mb <= SCOL; }
+
 hipError_t launch_orth(bool f64, const EigArgs& a, int target, void* S, double* part, int nblk, double* G,
                        EigCtrl* ctrl, hipStream_t st) {
     const bool mf = rows_on_matrix_cores(f64, a.mb);
@@ -1297,7 +1353,7 @@ hipError_t launch_orth(bool f64, const EigArgs& a, int target, void* S, double* 
     else
         go_mask(a, [&](auto mk) {
             constexpr bool M = decltype(mk)::value;
-            if (3 * a.mb <= SCOL) {
+            if (narrow(a)) {
                 if (f64)
                     hipLaunchKernelGGL((k_orth_gram_small<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, target,
                                        (const double*)S, part, ctrl);
@@ -1308,10 +1364,15 @@ hipError_t launch_orth(bool f64, const EigArgs& a, int target, void* S, double* 
                 hipLaunchKernelGGL((k_orth_gram<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, target,
                                    (const double*)S, part, ctrl);
         });
-    const int E = (target == 0 ? 1 : 3) * a.mb * a.mb;
-    hipLaunchKernelGGL(k_reduce_rows, dim3((E + RED_E - 1) / RED_E, a.P), dim3(WL), 0, st, a, part, nblk, 0, target, G,
-                       ctrl);
-    hipLaunchKernelGGL(k_orth_small, dim3(1, a.P), dim3(WL), 0, st, a, target, G, ctrl);
+    if (narrow(a)) {
+        hipLaunchKernelGGL(k_orth_small_narrow, dim3(1, a.P), dim3(SORTH_WAVES * WL), 0, st, a, target, part, nblk,
+                           ctrl);
+    } else {
+        const int E = (target == 0 ? 1 : 3) * a.mb * a.mb;
+        hipLaunchKernelGGL(k_reduce_rows, dim3((E + RED_E - 1) / RED_E, a.P), dim3(WL), 0, st, a, part, nblk, 0,
+                           target, G, ctrl);
+        hipLaunchKernelGGL(k_orth_small, dim3(1, a.P), dim3(WL), 0, st, a, target, G, ctrl);
+    }
     const int nb = update_blocks(a.n2, f64, a.mb);
     if (mf) {
         hipLaunchKernelGGL(k_orth_apply_mfma, dim3(nb, a.P), dim3(NT), 0, st, a, target, (float*)S, ctrl);
@@ -1333,14 +1394,14 @@ hipError_t launch_orth(bool f64, const EigArgs& a, int target, void* S, double* 
 }
 
 hipError_t launch_gram(bool f64, const EigArgs& a, int ns, const void* S, const void* HS, double* part, int nblk,
-                       double* G, const EigCtrl* ctrl, hipStream_t st) {
+                       const EigCtrl* ctrl, hipStream_t st) {
     if (rows_on_matrix_cores(f64, a.mb))
         hipLaunchKernelGGL(k_gram_mfma, dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (const float*)S, (const float*)HS,
                            part, ctrl);
     else
         go_mask(a, [&](auto mk) {
             constexpr bool M = decltype(mk)::value;
-            if (3 * a.mb <= SCOL) {
+            if (narrow(a)) {
                 if (f64)
                     hipLaunchKernelGGL((k_gram_small<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns,
                                        (const double*)S, (const double*)HS, part, ctrl);
@@ -1351,14 +1412,19 @@ hipError_t launch_gram(bool f64, const EigArgs& a, int ns, const void* S, const 
                 hipLaunchKernelGGL((k_gram<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (const double*)S,
                                    (const double*)HS, part, ctrl);
         });
-    const int E = 3 * a.mb * (3 * a.mb + 1);
-    hipLaunchKernelGGL(k_reduce_rows, dim3((E + RED_E - 1) / RED_E, a.P), dim3(WL), 0, st, a, part, nblk, 1, ns, G,
-                       ctrl);
     return hipGetLastError();
 }
 
-hipError_t launch_rr(const EigArgs& a, int ns, const double* G, EigCtrl* ctrl, hipStream_t st) {
-    hipLaunchKernelGGL(k_rr, dim3(1, a.P), dim3(RR_WAVES * WL), 0, st, a, ns, G, ctrl);
+hipError_t launch_rr(const EigArgs& a, int ns, const double* part, int nblk, double* G, EigCtrl* ctrl,
+                     hipStream_t st) {
+    if (narrow(a)) {
+        hipLaunchKernelGGL(k_rr_narrow, dim3(1, a.P), dim3(RR_WAVES * WL), 0, st, a, ns, part, nblk, ctrl);
+    } else {
+        const int E = 3 * a.mb * (3 * a.mb + 1);
+        hipLaunchKernelGGL(k_reduce_rows, dim3((E + RED_E - 1) / RED_E, a.P), dim3(WL), 0, st, a, part, nblk, 1, ns,
+                           G, ctrl);
+        hipLaunchKernelGGL(k_rr, dim3(1, a.P), dim3(RR_WAVES * WL), 0, st, a, ns, G, ctrl);
+    }
     return hipGetLastError();
 }
 
