@@ -537,27 +537,32 @@ static moto_status min_modes_pop_impl(moto_plan p, moto_dtype hvp, int P, const 
                             mask, N, o->seed, ctrl, st));
     HIP_TRY(launch_check_finite(m, c64, N, P, ctrl, st));
     // start: orthonormal X; HX = H X; Rayleigh-Ritz on span(X); W = HX - X Lam
-    for (int pass = 0; pass < 2; ++pass) HIP_TRY(launch_orth(f64, a, 0, S, part, nbg, G, ctrl, st));
+    for (int pass = 0; pass < 2; ++pass) HIP_TRY(launch_orth(f64, a, 0, S, part, nbg, G, ctrl, false, st));
     HIP_TRY(launch_tangent_hvp(p->g, p->k, f64, true, P, mT, cT, mask, L.mb, S, HS, hv_done, st, hv_var, vbs));
     HIP_TRY(launch_gram(f64, a, L.mb, S, HS, part, nbg, ctrl, st));
     HIP_TRY(launch_rr(a, L.mb, part, nbg, G, ctrl, st));
-    HIP_TRY(launch_update(f64, a, L.mb, S, HS, part, nbu, ctrl, st));
-    HIP_TRY(launch_eig_control(a, part, nbu, ctrl, 1, st));
+    HIP_TRY(launch_update(f64, a, L.mb, S, HS, part, nbg, nbu, ctrl, st));
+    HIP_TRY(launch_eig_control(a, part, nbg, nbu, ctrl, 1, st));
     if (P > 1) HIP_TRY(launch_eig_all_done(a, ctrl, all_done, st));
     const int every = o->check_every > 0 ? o->check_every : 8;
     const int max_chunks = o->max_iter / every + 2;
     auto chunk_launches = [&](hipStream_t s) -> hipError_t {
+        // narrow blocks take an iteration's convergence control with the next
+        // one's first small step; the last of a chunk is on its own, for the
+        // host to read
+        bool pending = false;
         for (int it = 0; it < every; ++it) {
             for (int pass = 0; pass < 2; ++pass) {
-                hipError_t e = launch_orth(f64, a, 1 + pass, S, part, nbg, G, ctrl, s);
+                hipError_t e = launch_orth(f64, a, 1 + pass, S, part, nbg, G, ctrl, pending && pass == 0, s);
                 if (e != hipSuccess) return e;
             }
+            pending = eig_control_folds(a) && it + 1 < every;
             hipError_t e = launch_tangent_hvp(p->g, p->k, f64, true, P, mT, cT, mask, L.mb, Wslot, HWslot, hv_done,
                                               s, hv_var, vbs);
             if (e == hipSuccess) e = launch_gram(f64, a, -1, S, HS, part, nbg, ctrl, s);
             if (e == hipSuccess) e = launch_rr(a, -1, part, nbg, G, ctrl, s);
-            if (e == hipSuccess) e = launch_update(f64, a, -1, S, HS, part, nbu, ctrl, s);
-            if (e == hipSuccess) e = launch_eig_control(a, part, nbu, ctrl, 0, s);
+            if (e == hipSuccess) e = launch_update(f64, a, -1, S, HS, part, nbg, nbu, ctrl, s);
+            if (e == hipSuccess && !pending) e = launch_eig_control(a, part, nbg, nbu, ctrl, 0, s);
             if (e != hipSuccess) return e;
         }
         // every kernel looks at its own member's flag; the flag of the whole

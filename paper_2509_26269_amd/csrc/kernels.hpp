@@ -240,20 +240,25 @@ hipError_t launch_eig_init(bool f64, const EigArgs& a, void* S, const double* m,
                            EigCtrl* ctrl, hipStream_t st);
 // Orthonormalise the X block (target 0, start) or the W block against [X P]
 // and itself (target 1: first pass, target 2: second pass, a no-op when the
-// first was well conditioned), in place.
+// first was well conditioned), in place.  pending (target 1, only where
+// eig_control_folds): takes the convergence control of the update before too.
+// For those blocks launch_update leaves the Gram of target 1 in part, which
+// nothing else may use in between.
+bool eig_control_folds(const EigArgs& a);  // narrow blocks
 hipError_t launch_orth(bool f64, const EigArgs& a, int target, void* S, double* part, int nblk, double* G,
-                       EigCtrl* ctrl, hipStream_t st);
+                       EigCtrl* ctrl, bool pending, hipStream_t st);
 // Per-block rows of the Grams S^T HS and S^T S; launch_rr sums them (in G).
 hipError_t launch_gram(bool f64, const EigArgs& a, int ns, const void* S, const void* HS, double* part, int nblk,
                        const EigCtrl* ctrl, hipStream_t st);
 int gram_blocks(int n2);
 hipError_t launch_rr(const EigArgs& a, int ns, const double* part, int nblk, double* G, EigCtrl* ctrl,
                      hipStream_t st);
-hipError_t launch_update(bool f64, const EigArgs& a, int ns, void* S, void* HS, double* part, int nblk,
+// nbg, nbu: workgroups of the Gram and of the row-update kernels
+hipError_t launch_update(bool f64, const EigArgs& a, int ns, void* S, void* HS, double* part, int nbg, int nbu,
                          EigCtrl* ctrl, hipStream_t st);
 int update_blocks(int n2, bool f64, int mb);  // row-update workgroups (same rule as the launchers)
 bool rows_on_matrix_cores(bool f64, int mb);  // FP32 block widths from 5
-hipError_t launch_eig_control(const EigArgs& a, const double* part, int nblk, EigCtrl* ctrl, int first,
+hipError_t launch_eig_control(const EigArgs& a, const double* part, int nbg, int nbu, EigCtrl* ctrl, int first,
                               hipStream_t st);
 hipError_t launch_eig_gather_info(int P, const EigCtrl* ctrl, moto_info* out, hipStream_t st);
 // all_done = 1 once every member's control block says done (P > 1 only).

@@ -68,6 +68,18 @@ __device__ __forceinline__ double dot_chunk(const T* __restrict__ x, const T* __
     return (s0 + s1) + (s2 + s3);
 }
 
+// the same by a quad of lanes, lane q of four taking partial sum q: the bits
+// of dot_chunk (on every lane of the quad) from a chain a quarter as long
+template <class T>
+__device__ __forceinline__ double dot_quad(const T* __restrict__ x, const T* __restrict__ y, int q) {
+    double s = 0.0;
+#pragma unroll
+    for (int rr = 0; rr < RCH; rr += 4) s += (double)x[rr + q] * (double)y[rr + q];
+    s += dpp_f64<0xB1>(s);
+    s += dpp_f64<0x4E>(s);
+    return s;
+}
+
 __device__ __forceinline__ int sol_ns(const EigArgs& a, const EigCtrl* ctrl, int ns_fixed) {
     return ns_fixed >= 0 ? ns_fixed : 2 * a.mb + ctrl->np;
 }
@@ -250,11 +262,11 @@ __global__ __launch_bounds__(NT) void k_orth_gram(EigArgs a, int target, const T
 
 // Narrow blocks (3 mb <= SCOL columns: k = 1 and 2 with their default guard).
 // The general kernels size their staging and entry lists for 48 columns and
-// keep a quarter of a compute unit's waves; here a thread owns one entry, and
-// the next chunk's loads are in flight under the dot products of the current
-// one.  Entries, chunk order and dot products are the general kernels', so the
-// sums keep their bits.  24 x 128x128 FP32, k = 2: Gram 25 -> 17.5 us a
-// call, orthonormalisation Gram 13 -> 8.3.
+// keep a quarter of a compute unit's waves; here a thread (or a quad) owns one
+// entry, and the next chunk's loads are in flight under the dot products of the
+// current one.  Entries, chunk order and dot products are the general kernels',
+// so the sums keep their bits.  Gram, 24 x 128x128 FP32, k = 2: 25 -> 17.5 us
+// a call.
 template <class T>
 struct SmallChunk {
     static constexpr int Q = SCOL * RCH / NT;  // staged values per thread (of one matrix)
@@ -268,55 +280,58 @@ struct SmallChunk {
     }
 };
 
+// Staged columns of an orthonormalisation: [Q Y] as c < nq: X, then P, else
+// the target block at column t0.
+__device__ __forceinline__ int orth_col(int c, int nq, int mb, int t0) {
+    return c >= nq ? t0 + (c - nq) : c < mb ? c : mb + c;
+}
+
+// Entry e = j nrow + i of the Gram of the staged columns [Q Y] against Y, a
+// quad of lanes to an entry (SORTH entries at most).
+static_assert(SCOL / 3 < UPDATE_MFMA_MIN_MB, "narrow blocks run on the vector units");
+static_assert(4 * SORTH <= NT, "a quad per entry");
+struct OrthEntry {
+    int e, q, i, y;
+    bool on;
+    __device__ __forceinline__ OrthEntry(int nq, int mb) {
+        const int nrow = nq + mb;
+        e = (int)threadIdx.x >> 2;
+        q = (int)threadIdx.x & 3;
+        on = e < nrow * mb;
+        const int j = on ? e / nrow : 0;
+        i = on ? e - j * nrow : 0;
+        y = nq + j;
+    }
+};
+
+// the start block's Gram (nothing to project out; the passes over W form
+// theirs in k_update_gram and k_orth_apply_gram)
 template <class T, bool MSK>
-__global__ __launch_bounds__(NT) void k_orth_gram_small(EigArgs a, int target, const T* __restrict__ S,
+__global__ __launch_bounds__(NT) void k_orth_gram_start(EigArgs a, const T* __restrict__ S,
                                                         double* __restrict__ part,
                                                         const EigCtrl* __restrict__ ctrl) {
     S += blockIdx.y * a.s_ms;
     part += blockIdx.y * a.part_ms;
     ctrl += blockIdx.y;
-    if (ctrl->done || (target == 2 && ctrl->orth_skip)) return;
+    if (ctrl->done) return;
     using SC = SmallChunk<T>;
     __shared__ __align__(16) SC sc;
     const int mb = a.mb, n2 = a.n2;
-    const int nq = target >= 1 ? mb + ctrl->np : 0, t0 = target == 0 ? 0 : mb;
-    const int nrow = nq + mb, E = nrow * mb;
     const uint8_t* mk = MSK ? member_mask(a) : nullptr;
-    const int rr = threadIdx.x % RCH;
-    // physical column of staged column c: X, then P, then the target
-    const T* src[SC::Q];
-    bool use[SC::Q];
-#pragma unroll
-    for (int q = 0; q < SC::Q; ++q) {
-        const int c = SC::col(q);
-        use[q] = c < nrow;
-        src[q] = S + (size_t)(c >= nq ? t0 + (c - nq) : c < mb ? c : mb + c) * n2 + rr;
-    }
-    T v[SC::Q];
-    bool in = false;
-    auto load = [&](int ch) {
-        const int r0 = ch * RCH;
-        in = r0 + rr < n2 && (!MSK || row_active(mk, a.Nsite, r0 + rr));
-#pragma unroll
-        for (int q = 0; q < SC::Q; ++q) v[q] = in && use[q] ? src[q][r0] : T(0);
-    };
-    const int e = threadIdx.x, j = e / nrow, i = e - j * nrow;
+    const int rr = threadIdx.x % RCH, c = threadIdx.x / RCH;
+    static_assert(NT / RCH >= SCOL / 3, "a wave per column");
+    const OrthEntry oe(0, mb);
     double acc = 0.0;
     const int nchunks = (n2 + RCH - 1) / RCH;
-    if ((int)blockIdx.x < nchunks) load(blockIdx.x);
     for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
-        bool any = true;
-        if constexpr (MSK)
-            any = __syncthreads_or(in) != 0;
-        else
-            __syncthreads();
-        if (any) sc.put(v);
-        if (ch + (int)gridDim.x < nchunks) load(ch + gridDim.x);
-        if (!any) continue;
+        const int r = ch * RCH + rr;
+        const bool in = r < n2 && (!MSK || row_active(mk, a.Nsite, r));
         __syncthreads();
-        if (e < E) acc += dot_chunk(sc.ts[i], sc.ts[nq + j]);
+        sc.ts[c][rr] = in && c < mb ? S[(size_t)c * n2 + r] : T(0);
+        __syncthreads();
+        if (oe.on) acc += dot_quad(sc.ts[oe.i], sc.ts[oe.y], oe.q);
     }
-    if (e < E) part[(size_t)blockIdx.x * PSTRIDE + e] = acc;
+    if (oe.on && oe.q == 0) part[(size_t)blockIdx.x * PSTRIDE + oe.e] = acc;
 }
 
 // The orthonormalisation Gram and transform on the matrix cores (FP32 blocks,
@@ -534,24 +549,62 @@ __global__ __launch_bounds__(WL) void k_orth_small(EigArgs a, int target, const 
                 orth_small_body<MAXS + 1>(a.mb, orth_nq(a, target, ctrl), a.drop, G, ctrl->Bw, ctrl->Tw), ctrl);
 }
 
+// Convergence control by one wavefront (the residual norms' squares at rsq, in
+// LDS): checks NaN, rank, convergence and the cap; true when the solve ends.
+__device__ __forceinline__ bool control_wave(const EigArgs& a, const double* rsq, bool first, EigCtrl* ctrl) {
+    const int j = wlane();
+    bool bad = false, open = false;
+    if (j < a.mb) {
+        const double rj = sqrt(rsq[j]);
+        ctrl->resid[j] = rj;
+        bad = !isfinite(rj) || !isfinite(ctrl->lam[j]);
+        open = j < a.k && !(rj <= a.tol_abs);
+    }
+    const int iters = ctrl->iters + (first ? 0 : 1);
+    int status = -1;
+    if (__any(bad))
+        status = MOTO_NAN;
+    else if (ctrl->rank < a.k)
+        status = MOTO_BREAKDOWN;
+    else if (!__any(open))
+        status = MOTO_CONVERGED;
+    else if (iters >= a.max_iter)
+        status = MOTO_NOT_CONVERGED;
+    if (j == 0) {
+        ctrl->n_hvp += a.mb;
+        ctrl->iters = iters;
+        if (!first) ctrl->np = a.mb;
+        if (status >= 0) {
+            ctrl->status = status;
+            ctrl->done = 1;
+        }
+    }
+    return status >= 0;
+}
+
 // Narrow blocks: the reduction and the small step in one launch, the matrices
 // sized for their basis (the reduction's 3.3 us and a launch gap saved twice
-// an iteration, of 78 us at 64x64, k = 2 FP64).
-constexpr int SORTH_WAVES = (SORTH + RED_E - 1) / RED_E;
-__global__ __launch_bounds__(SORTH_WAVES * WL) void k_orth_small_narrow(EigArgs a, int target,
+// an iteration, of 78 us at 64x64, k = 2 FP64).  pending: the convergence
+// control of the iteration before is taken here as well (4.4 us in a launch of
+// its own, 0.7 here); its residual partials follow the Gram entries in the
+// blocks' rows.
+constexpr int SORTH_WAVES = (SORTH + SCOL / 3 + RED_E - 1) / RED_E;
+__global__ __launch_bounds__(SORTH_WAVES * WL) void k_orth_small_narrow(EigArgs a, int target, int pending,
                                                                         const double* __restrict__ part, int nblk,
                                                                         EigCtrl* __restrict__ ctrl) {
     part += blockIdx.y * a.part_ms;
     ctrl += blockIdx.y;
     if (ctrl->done || (target == 2 && ctrl->orth_skip)) return;
-    __shared__ double Gl[SORTH];
-    const int nq = orth_nq(a, target, ctrl);
-    reduce_rows_wg(part, nblk, (nq + a.mb) * a.mb, Gl);
+    __shared__ double Gl[SORTH + SCOL / 3];
+    const int nq = pending ? 2 * a.mb : orth_nq(a, target, ctrl);
+    const int E = (nq + a.mb) * a.mb;
+    reduce_rows_wg(part, nblk, pending ? E + a.mb : E, Gl);
     if (threadIdx.x >= WL) return;
+    if (pending && control_wave(a, Gl + E, false, ctrl)) return;
     orth_settle(target, orth_small_body<SCOL + 1>(a.mb, nq, a.drop, Gl, ctrl->Bw, ctrl->Tw), ctrl);
 }
 
-// Row kernels on the vector ALUs (k_orth_apply, k_update).  MB: compile-time
+// Row transform on the vector ALUs.  MB: compile-time
 // bound on the block width (mb <= MB), so that the per-row register arrays are
 // sized for the actual block and never spill.  EX: the block has exactly MB
 // columns and the basis all 3 MB (every iteration but the first), so that no
@@ -620,6 +673,90 @@ __global__ __launch_bounds__(NT) void k_orth_apply(EigArgs a, int target, T* __r
         }
     }
     orth_apply_rows<T, MB, MSK, false>(a, oc, B, Tw, S);
+}
+
+// Narrow blocks, first pass over W: the transform and the second pass's Gram
+// of its result in one launch, on the chunks of the Gram (the rows are read
+// once, and the Gram's chunks are the ones that k_orth_gram takes, so the sums
+// keep their bits).  Wave l projects column l, wave j forms column j of the
+// product with Tw.  At 64x64, k = 2 FP64, both kernels are launch latency: 4.2
+// and 4.3 us apart, 4.6 together; 24 x 128x128, k = 2 FP32: 7.4 and 8.2, 10.2.
+template <class T, bool MSK>
+__global__ __launch_bounds__(NT) void k_orth_apply_gram(EigArgs a, T* __restrict__ S, double* __restrict__ part,
+                                                        const EigCtrl* __restrict__ ctrl) {
+    S += blockIdx.y * a.s_ms;
+    part += blockIdx.y * a.part_ms;
+    ctrl += blockIdx.y;
+    if (ctrl->done) return;
+    using SC = SmallChunk<T>;
+    constexpr int MB = SCOL / 3;
+    static_assert(RCH == WL && NT / WL == MB, "a wave per column, a row per lane");
+    __shared__ __align__(16) SC sc;
+    __shared__ double su[MB][RCH];
+    const int mb = a.mb, n2 = a.n2, nq = mb + ctrl->np;
+    const bool gram = !ctrl->orth_skip;
+    const uint8_t* mk = MSK ? member_mask(a) : nullptr;
+    const int rr = threadIdx.x % RCH;
+    const int j = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WL);
+    double B[2 * MB], Tw[MB];  // of this wave's column, zero beyond the block
+#pragma unroll
+    for (int i = 0; i < 2 * MB; ++i) B[i] = j < mb && i < nq ? ctrl->Bw[i + 2 * MAXB * j] : 0.0;
+#pragma unroll
+    for (int l = 0; l < MB; ++l) Tw[l] = j < mb && l < mb ? ctrl->Tw[l + mb * j] : 0.0;
+    const T* src[SC::Q];
+    bool use[SC::Q];
+#pragma unroll
+    for (int q = 0; q < SC::Q; ++q) {
+        const int c = SC::col(q);
+        use[q] = c < nq + mb;
+        src[q] = S + (size_t)orth_col(c, nq, mb, mb) * n2 + rr;
+    }
+    T v[SC::Q];
+    bool in = false;
+    auto load = [&](int ch) {
+        const int r0 = ch * RCH;
+        in = r0 + rr < n2 && (!MSK || row_active(mk, a.Nsite, r0 + rr));
+#pragma unroll
+        for (int q = 0; q < SC::Q; ++q) v[q] = in && use[q] ? src[q][r0] : T(0);
+    };
+    const OrthEntry oe(nq, mb);
+    double acc = 0.0;
+    const int nchunks = (n2 + RCH - 1) / RCH;
+    if ((int)blockIdx.x < nchunks) load(blockIdx.x);
+    for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
+        bool any = true;
+        if constexpr (MSK)
+            any = __syncthreads_or(in) != 0;
+        else
+            __syncthreads();
+        if (any) sc.put(v);
+        const bool mine = in && j < mb;
+        if (ch + (int)gridDim.x < nchunks) load(ch + gridDim.x);
+        if (!any) continue;
+        __syncthreads();
+        {
+            double q[2 * MB], u = (double)sc.ts[nq + (j < mb ? j : 0)][rr];
+#pragma unroll
+            for (int i = 0; i < 2 * MB; ++i) q[i] = (double)sc.ts[i][rr];
+            // a column beyond the projection set has the coefficient zero
+#pragma unroll
+            for (int i = 0; i < 2 * MB; ++i) u -= B[i] * q[i];
+            su[j][rr] = u;
+        }
+        __syncthreads();
+        if (j < mb) {
+            double w = 0.0;
+#pragma unroll
+            for (int l = 0; l < MB; ++l) w += su[l][rr] * Tw[l];
+            const T wt = (T)w;
+            if (mine) S[(size_t)(mb + j) * n2 + ch * RCH + rr] = wt;
+            sc.ts[nq + j][rr] = wt;
+        }
+        if (!gram) continue;
+        __syncthreads();
+        if (oe.on) acc += dot_quad(sc.ts[oe.i], sc.ts[oe.y], oe.q);
+    }
+    if (gram && oe.on && oe.q == 0) part[(size_t)blockIdx.x * PSTRIDE + oe.e] = acc;
 }
 
 // --------------------------------------------------------------------------
@@ -882,68 +1019,12 @@ __global__ __launch_bounds__(RR_WAVES * WL) void k_rr_narrow(EigArgs a, int ns_f
 // and per-block partial sums of |W_j|^2.  At the start (ns == mb) P is left
 // alone.
 // --------------------------------------------------------------------------
-template <class T, int MB, bool MSK, bool EX>
-__device__ __forceinline__ void update_rows(const EigArgs& a, int ns_, const double* C, const double* Cp,
-                                            const double* lam, T* __restrict__ S, T* __restrict__ HS,
-                                            double (&rs)[MB]) {
-    const int mb = EX ? MB : a.mb, ns = EX ? 3 * MB : ns_;
-    const bool has_p = ns > mb;
-    const uint8_t* mk = MSK ? member_mask(a) : nullptr;
-    for (int r = blockIdx.x * NT + threadIdx.x; r < a.n2; r += gridDim.x * NT) {
-        if constexpr (MSK) {
-            if (!row_active(mk, a.Nsite, r)) continue;
-        }
-        // the coefficients stay in LDS (hoisted out of the row loop they cost
-        // up to 466 registers and all but one wave)
-        if constexpr (EX) asm volatile("" ::: "memory");
-        T sv[3 * MB];
-#pragma unroll
-        for (int i = 0; i < 3 * MB; ++i)
-            if (i < ns) sv[i] = S[(size_t)i * a.n2 + r];
-        double xn[MB];
-#pragma unroll
-        for (int j = 0; j < MB; ++j) {
-            if (j < mb) {
-                double x = 0.0, p = 0.0;
-#pragma unroll
-                for (int i = 0; i < 3 * MB; ++i) {
-                    if (i < ns) {
-                        x += C[i + ns * j] * (double)sv[i];
-                        p += Cp[i + ns * j] * (double)sv[i];
-                    }
-                }
-                xn[j] = x;
-                S[(size_t)j * a.n2 + r] = (T)x;
-                if (has_p) S[(size_t)(2 * mb + j) * a.n2 + r] = (T)p;
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 3 * MB; ++i)
-            if (i < ns) sv[i] = HS[(size_t)i * a.n2 + r];
-#pragma unroll
-        for (int j = 0; j < MB; ++j) {
-            if (j < mb) {
-                double hx = 0.0, hp = 0.0;
-#pragma unroll
-                for (int i = 0; i < 3 * MB; ++i) {
-                    if (i < ns) {
-                        hx += C[i + ns * j] * (double)sv[i];
-                        hp += Cp[i + ns * j] * (double)sv[i];
-                    }
-                }
-                HS[(size_t)j * a.n2 + r] = (T)hx;
-                if (has_p) HS[(size_t)(2 * mb + j) * a.n2 + r] = (T)hp;
-                const T w = (T)(hx - lam[j] * xn[j]);
-                S[(size_t)(mb + j) * a.n2 + r] = w;
-                rs[j] += (double)w * (double)w;
-            }
-        }
-    }
-}
-
-template <class T, int MB, bool MSK>
-__global__ __launch_bounds__(NT) void k_update(EigArgs a, int ns_fixed, T* __restrict__ S, T* __restrict__ HS,
-                                               double* __restrict__ part, const EigCtrl* __restrict__ ctrl) {
+// Vector form of the FP64 blocks of 5 and more columns (narrower ones:
+// k_update_gram; FP32 ones: k_update_mfma).
+template <int MB, bool MSK>
+__global__ __launch_bounds__(NT) void k_update(EigArgs a, int ns_fixed, double* __restrict__ S,
+                                               double* __restrict__ HS, double* __restrict__ part,
+                                               const EigCtrl* __restrict__ ctrl) {
     S += blockIdx.y * a.s_ms;
     HS += blockIdx.y * a.s_ms;
     part += blockIdx.y * a.part_ms;
@@ -964,12 +1045,55 @@ __global__ __launch_bounds__(NT) void k_update(EigArgs a, int ns_fixed, T* __res
     double rs[MB];
 #pragma unroll
     for (int j = 0; j < MB; ++j) rs[j] = 0.0;
-    bool exact = false;
-    if constexpr (MB <= 4) {
-        exact = mb == MB && ns == 3 * MB;
-        if (exact) update_rows<T, MB, MSK, true>(a, ns, C, Cp, lam, S, HS, rs);
+    const bool has_p = ns > mb;
+    const uint8_t* mk = MSK ? member_mask(a) : nullptr;
+    for (int r = blockIdx.x * NT + threadIdx.x; r < a.n2; r += gridDim.x * NT) {
+        if constexpr (MSK) {
+            if (!row_active(mk, a.Nsite, r)) continue;
+        }
+        double sv[3 * MB];
+#pragma unroll
+        for (int i = 0; i < 3 * MB; ++i)
+            if (i < ns) sv[i] = S[(size_t)i * a.n2 + r];
+        double xn[MB];
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            if (j < mb) {
+                double x = 0.0, p = 0.0;
+#pragma unroll
+                for (int i = 0; i < 3 * MB; ++i) {
+                    if (i < ns) {
+                        x += C[i + ns * j] * sv[i];
+                        p += Cp[i + ns * j] * sv[i];
+                    }
+                }
+                xn[j] = x;
+                S[(size_t)j * a.n2 + r] = x;
+                if (has_p) S[(size_t)(2 * mb + j) * a.n2 + r] = p;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 3 * MB; ++i)
+            if (i < ns) sv[i] = HS[(size_t)i * a.n2 + r];
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            if (j < mb) {
+                double hx = 0.0, hp = 0.0;
+#pragma unroll
+                for (int i = 0; i < 3 * MB; ++i) {
+                    if (i < ns) {
+                        hx += C[i + ns * j] * sv[i];
+                        hp += Cp[i + ns * j] * sv[i];
+                    }
+                }
+                HS[(size_t)j * a.n2 + r] = hx;
+                if (has_p) HS[(size_t)(2 * mb + j) * a.n2 + r] = hp;
+                const double w = hx - lam[j] * xn[j];
+                S[(size_t)(mb + j) * a.n2 + r] = w;
+                rs[j] += w * w;
+            }
+        }
     }
-    if (!exact) update_rows<T, MB, MSK, false>(a, ns, C, Cp, lam, S, HS, rs);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
     for (int j = 0; j < MB; ++j) {
@@ -983,6 +1107,107 @@ __global__ __launch_bounds__(NT) void k_update(EigArgs a, int ns_fixed, T* __res
         const int j = threadIdx.x;
         part[(size_t)blockIdx.x * MAXB + j] = red[j * 4] + red[j * 4 + 1] + red[j * 4 + 2] + red[j * 4 + 3];
     }
+}
+
+// Narrow blocks: the update and the first orthonormalisation Gram of the new W
+// in one launch, on the chunks of the Gram.  The chunk's columns of S and HS go
+// through LDS; wave j forms column j of X, HX, P, HP and W (a lane per row, its
+// coefficients in registers) and stages X, P and W for the Gram, whose entries
+// and order are k_orth_gram's.  |W_j|^2 partials follow the Gram entries in the
+// block's row.  64x64, k = 2 FP64: 5.7 and 4.3 us apart (a row per thread left
+// 32 workgroups), 4.9 together; 24 x 128x128, k = 2 FP32 (138 MB of blocks read
+// and written): 19 and 8.2, 20.1.
+template <class T, bool MSK>
+__global__ __launch_bounds__(NT) void k_update_gram(EigArgs a, int ns_fixed, T* __restrict__ S, T* __restrict__ HS,
+                                                    double* __restrict__ part, const EigCtrl* __restrict__ ctrl) {
+    S += blockIdx.y * a.s_ms;
+    HS += blockIdx.y * a.s_ms;
+    part += blockIdx.y * a.part_ms;
+    ctrl += blockIdx.y;
+    if (ctrl->done) return;
+    using SC = SmallChunk<T>;
+    constexpr int MB = SCOL / 3;
+    static_assert(RCH == WL && NT / WL == MB, "a wave per column, a row per lane");
+    __shared__ __align__(16) SC ss, sh, sn;
+    const int mb = a.mb, n2 = a.n2;
+    const int ns = sol_ns(a, ctrl, ns_fixed);
+    const bool has_p = ns > mb;
+    const int nq = has_p ? 2 * mb : mb;  // projection columns of the Gram
+    const uint8_t* mk = MSK ? member_mask(a) : nullptr;
+    const int rr = threadIdx.x % RCH;
+    const int j = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WL);
+    double cx[SCOL], cp[SCOL];  // zero beyond the basis, where the chunks hold zeros
+#pragma unroll
+    for (int i = 0; i < SCOL; ++i) {
+        const bool on = j < mb && i < ns;
+        cx[i] = on ? ctrl->C[i + ns * j] : 0.0;
+        cp[i] = on ? ctrl->Cp[i + ns * j] : 0.0;
+    }
+    const double lam = j < mb ? ctrl->lam[j] : 0.0;
+    T v[SC::Q], w[SC::Q];
+    bool in = false;
+    auto load = [&](int ch) {
+        const int r = ch * RCH + rr;
+        in = r < n2 && (!MSK || row_active(mk, a.Nsite, r));
+#pragma unroll
+        for (int q = 0; q < SC::Q; ++q) {
+            const size_t o = (size_t)SC::col(q) * n2 + r;
+            const bool on = in && SC::col(q) < ns;
+            v[q] = on ? S[o] : T(0);
+            w[q] = on ? HS[o] : T(0);
+        }
+    };
+    const OrthEntry oe(nq, mb);
+    double acc = 0.0, rs = 0.0;
+    const int nchunks = (n2 + RCH - 1) / RCH;
+    if ((int)blockIdx.x < nchunks) load(blockIdx.x);
+    for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
+        bool any = true;
+        if constexpr (MSK)
+            any = __syncthreads_or(in) != 0;
+        else
+            __syncthreads();
+        if (any) {
+            ss.put(v);
+            sh.put(w);
+        }
+        const bool mine = in;
+        if (ch + (int)gridDim.x < nchunks) load(ch + gridDim.x);
+        if (!any) continue;
+        __syncthreads();
+        if (j < mb) {
+            double x = 0.0, p = 0.0, hx = 0.0, hp = 0.0;
+#pragma unroll
+            for (int i = 0; i < SCOL; ++i) {
+                const double si = (double)ss.ts[i][rr], hi = (double)sh.ts[i][rr];
+                x += cx[i] * si;
+                p += cp[i] * si;
+                hx += cx[i] * hi;
+                hp += cp[i] * hi;
+            }
+            const T wn = (T)(hx - lam * x);
+            if (mine) {
+                const size_t r = (size_t)ch * RCH + rr;
+                S[(size_t)j * n2 + r] = (T)x;
+                HS[(size_t)j * n2 + r] = (T)hx;
+                S[(size_t)(mb + j) * n2 + r] = wn;
+                if (has_p) {
+                    S[(size_t)(2 * mb + j) * n2 + r] = (T)p;
+                    HS[(size_t)(2 * mb + j) * n2 + r] = (T)hp;
+                }
+            }
+            sn.ts[j][rr] = (T)x;
+            if (has_p) sn.ts[mb + j][rr] = (T)p;
+            sn.ts[nq + j][rr] = wn;
+            rs += (double)wn * (double)wn;
+        }
+        __syncthreads();
+        if (oe.on) acc += dot_quad(sn.ts[oe.i], sn.ts[oe.y], oe.q);
+    }
+    double* row = part + (size_t)blockIdx.x * PSTRIDE;
+    if (oe.on && oe.q == 0) row[oe.e] = acc;
+    rs = wave_sum(rs);
+    if (j < mb && rr == 0) row[(nq + mb) * mb + j] = rs;
 }
 
 // --------------------------------------------------------------------------
@@ -1098,7 +1323,7 @@ __global__ __launch_bounds__(NT) void k_update_mfma(EigArgs a, int ns_fixed, flo
 }
 
 // Convergence control: residual norms (one wavefront per column, fixed-order
-// sums), then one thread checks NaN, rank, convergence and the cap.
+// sums), then one wavefront decides.
 __global__ __launch_bounds__(NT) void k_eig_control(EigArgs a, const double* __restrict__ part, int nblk,
                                                     EigCtrl* __restrict__ ctrl, int first) {
     part += blockIdx.y * a.part_ms;
@@ -1114,32 +1339,18 @@ __global__ __launch_bounds__(NT) void k_eig_control(EigArgs a, const double* __r
         if (lane == 0) rsq[j] = s;
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    bool conv = true, bad = false;
-    for (int j = 0; j < a.mb; ++j) {
-        const double rj = sqrt(rsq[j]);
-        ctrl->resid[j] = rj;
-        if (!isfinite(rj) || !isfinite(ctrl->lam[j])) bad = true;
-        if (j < a.k && !(rj <= a.tol_abs)) conv = false;
-    }
-    ctrl->n_hvp += a.mb;
-    if (!first) {
-        ctrl->iters += 1;
-        ctrl->np = a.mb;
-    }
-    if (bad) {
-        ctrl->status = MOTO_NAN;
-        ctrl->done = 1;
-    } else if (ctrl->rank < a.k) {
-        ctrl->status = MOTO_BREAKDOWN;
-        ctrl->done = 1;
-    } else if (conv) {
-        ctrl->status = MOTO_CONVERGED;
-        ctrl->done = 1;
-    } else if (ctrl->iters >= a.max_iter) {
-        ctrl->status = MOTO_NOT_CONVERGED;
-        ctrl->done = 1;
-    }
+    if (threadIdx.x < WL) control_wave(a, rsq, first != 0, ctrl);
+}
+
+// Narrow blocks: the partials that k_update_gram left after its Gram entries.
+__global__ __launch_bounds__(WL) void k_eig_control_narrow(EigArgs a, const double* __restrict__ part, int nblk,
+                                                           EigCtrl* __restrict__ ctrl, int first) {
+    part += blockIdx.y * a.part_ms;
+    ctrl += blockIdx.y;
+    if (ctrl->done) return;
+    __shared__ double rsq[SCOL / 3];
+    reduce_rows_wg(part + (first ? 2 : 3) * a.mb * a.mb, nblk, a.mb, rsq);
+    control_wave(a, rsq, first != 0, ctrl);
 }
 
 // all_done = AND of the members' done flags (one wavefront, fixed order)
@@ -1344,40 +1555,21 @@ static void go_mask(const EigArgs& a, F&& f) {
 
 static bool narrow(const EigArgs& a) { return 3 * a.mb <= SCOL; }
 
-hipError_t launch_orth(bool f64, const EigArgs& a, int target, void* S, double* part, int nblk, double* G,
-                       EigCtrl* ctrl, hipStream_t st) {
-    const bool mf = rows_on_matrix_cores(f64, a.mb);
-    if (mf)
-        hipLaunchKernelGGL(k_orth_gram_mfma, dim3(nblk, a.P), dim3(NT), 0, st, a, target, (const float*)S, part,
-                           ctrl);
-    else
-        go_mask(a, [&](auto mk) {
-            constexpr bool M = decltype(mk)::value;
-            if (narrow(a)) {
-                if (f64)
-                    hipLaunchKernelGGL((k_orth_gram_small<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, target,
-                                       (const double*)S, part, ctrl);
-                else
-                    hipLaunchKernelGGL((k_orth_gram_small<float, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, target,
-                                       (const float*)S, part, ctrl);
-            } else  // FP32 blocks this wide run on the matrix cores
-                hipLaunchKernelGGL((k_orth_gram<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, target,
-                                   (const double*)S, part, ctrl);
-        });
-    if (narrow(a)) {
-        hipLaunchKernelGGL(k_orth_small_narrow, dim3(1, a.P), dim3(SORTH_WAVES * WL), 0, st, a, target, part, nblk,
-                           ctrl);
-    } else {
-        const int E = (target == 0 ? 1 : 3) * a.mb * a.mb;
-        hipLaunchKernelGGL(k_reduce_rows, dim3((E + RED_E - 1) / RED_E, a.P), dim3(WL), 0, st, a, part, nblk, 0,
-                           target, G, ctrl);
-        hipLaunchKernelGGL(k_orth_small, dim3(1, a.P), dim3(WL), 0, st, a, target, G, ctrl);
-    }
+// the kernel of a narrow block by type and mask: f(type, mask) with tag values
+template <class F>
+static void go_narrow(bool f64, const EigArgs& a, F&& f) {
+    go_mask(a, [&](auto mk) {
+        if (f64)
+            f(double{}, mk);
+        else
+            f(float{}, mk);
+    });
+}
+
+bool eig_control_folds(const EigArgs& a) { return narrow(a); }
+
+static void launch_orth_apply(bool f64, const EigArgs& a, int target, void* S, EigCtrl* ctrl, hipStream_t st) {
     const int nb = update_blocks(a.n2, f64, a.mb);
-    if (mf) {
-        hipLaunchKernelGGL(k_orth_apply_mfma, dim3(nb, a.P), dim3(NT), 0, st, a, target, (float*)S, ctrl);
-        return hipGetLastError();
-    }
     go_mask(a, [&](auto mk) {
         constexpr bool M = decltype(mk)::value;
         go_mb(a.mb, [&](auto mbc) {
@@ -1390,27 +1582,73 @@ hipError_t launch_orth(bool f64, const EigArgs& a, int target, void* S, double* 
                                    (float*)S, ctrl);
         });
     });
+}
+
+// Narrow blocks: the Grams of the passes over W come from the kernels that
+// formed it (k_update_gram, k_orth_apply_gram).
+static hipError_t launch_orth_narrow(bool f64, const EigArgs& a, int target, void* S, double* part, int nblk,
+                                     EigCtrl* ctrl, bool pending, hipStream_t st) {
+    if (target == 0)
+        go_narrow(f64, a, [&](auto t, auto mk) {
+            using T = decltype(t);
+            constexpr bool M = decltype(mk)::value;
+            hipLaunchKernelGGL((k_orth_gram_start<T, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, (const T*)S, part,
+                               ctrl);
+        });
+    hipLaunchKernelGGL(k_orth_small_narrow, dim3(1, a.P), dim3(SORTH_WAVES * WL), 0, st, a, target, pending ? 1 : 0,
+                       part, nblk, ctrl);
+    if (target == 1)
+        go_narrow(f64, a, [&](auto t, auto mk) {
+            using T = decltype(t);
+            constexpr bool M = decltype(mk)::value;
+            hipLaunchKernelGGL((k_orth_apply_gram<T, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, (T*)S, part, ctrl);
+        });
+    else
+        launch_orth_apply(f64, a, target, S, ctrl, st);
+    return hipGetLastError();
+}
+
+hipError_t launch_orth(bool f64, const EigArgs& a, int target, void* S, double* part, int nblk, double* G,
+                       EigCtrl* ctrl, bool pending, hipStream_t st) {
+    if (narrow(a)) return launch_orth_narrow(f64, a, target, S, part, nblk, ctrl, pending, st);
+    const bool mf = rows_on_matrix_cores(f64, a.mb);
+    if (mf)
+        hipLaunchKernelGGL(k_orth_gram_mfma, dim3(nblk, a.P), dim3(NT), 0, st, a, target, (const float*)S, part,
+                           ctrl);
+    else  // FP32 blocks this wide run on the matrix cores
+        go_mask(a, [&](auto mk) {
+            hipLaunchKernelGGL((k_orth_gram<double, decltype(mk)::value>), dim3(nblk, a.P), dim3(NT), 0, st, a,
+                               target, (const double*)S, part, ctrl);
+        });
+    const int E = (target == 0 ? 1 : 3) * a.mb * a.mb;
+    hipLaunchKernelGGL(k_reduce_rows, dim3((E + RED_E - 1) / RED_E, a.P), dim3(WL), 0, st, a, part, nblk, 0, target,
+                       G, ctrl);
+    hipLaunchKernelGGL(k_orth_small, dim3(1, a.P), dim3(WL), 0, st, a, target, G, ctrl);
+    if (mf)
+        hipLaunchKernelGGL(k_orth_apply_mfma, dim3(update_blocks(a.n2, f64, a.mb), a.P), dim3(NT), 0, st, a, target,
+                           (float*)S, ctrl);
+    else
+        launch_orth_apply(f64, a, target, S, ctrl, st);
     return hipGetLastError();
 }
 
 hipError_t launch_gram(bool f64, const EigArgs& a, int ns, const void* S, const void* HS, double* part, int nblk,
                        const EigCtrl* ctrl, hipStream_t st) {
-    if (rows_on_matrix_cores(f64, a.mb))
+    if (narrow(a))
+        go_narrow(f64, a, [&](auto t, auto mk) {
+            using T = decltype(t);
+            constexpr bool M = decltype(mk)::value;
+            hipLaunchKernelGGL((k_gram_small<T, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (const T*)S,
+                               (const T*)HS, part, ctrl);
+        });
+    else if (rows_on_matrix_cores(f64, a.mb))
         hipLaunchKernelGGL(k_gram_mfma, dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (const float*)S, (const float*)HS,
                            part, ctrl);
     else
         go_mask(a, [&](auto mk) {
             constexpr bool M = decltype(mk)::value;
-            if (narrow(a)) {
-                if (f64)
-                    hipLaunchKernelGGL((k_gram_small<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns,
-                                       (const double*)S, (const double*)HS, part, ctrl);
-                else
-                    hipLaunchKernelGGL((k_gram_small<float, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns,
-                                       (const float*)S, (const float*)HS, part, ctrl);
-            } else
-                hipLaunchKernelGGL((k_gram<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (const double*)S,
-                                   (const double*)HS, part, ctrl);
+            hipLaunchKernelGGL((k_gram<double, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (const double*)S,
+                               (const double*)HS, part, ctrl);
         });
     return hipGetLastError();
 }
@@ -1428,30 +1666,36 @@ hipError_t launch_rr(const EigArgs& a, int ns, const double* part, int nblk, dou
     return hipGetLastError();
 }
 
-hipError_t launch_update(bool f64, const EigArgs& a, int ns, void* S, void* HS, double* part, int nblk,
+hipError_t launch_update(bool f64, const EigArgs& a, int ns, void* S, void* HS, double* part, int nbg, int nbu,
                          EigCtrl* ctrl, hipStream_t st) {
-    if (rows_on_matrix_cores(f64, a.mb)) {
-        hipLaunchKernelGGL(k_update_mfma, dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (float*)S, (float*)HS, part, ctrl);
-        return hipGetLastError();
-    }
-    go_mask(a, [&](auto mk) {
-        constexpr bool M = decltype(mk)::value;
-        go_mb(a.mb, [&](auto mbc) {
-            constexpr int W = decltype(mbc)::value;
-            if (f64)
-                hipLaunchKernelGGL((k_update<double, W, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (double*)S,
-                                   (double*)HS, part, ctrl);
-            else if constexpr (W < UPDATE_MFMA_MIN_MB)
-                hipLaunchKernelGGL((k_update<float, W, M>), dim3(nblk, a.P), dim3(NT), 0, st, a, ns, (float*)S,
-                                   (float*)HS, part, ctrl);
+    if (narrow(a))
+        go_narrow(f64, a, [&](auto t, auto mk) {
+            using T = decltype(t);
+            constexpr bool M = decltype(mk)::value;
+            hipLaunchKernelGGL((k_update_gram<T, M>), dim3(nbg, a.P), dim3(NT), 0, st, a, ns, (T*)S, (T*)HS, part,
+                               ctrl);
         });
-    });
+    else if (rows_on_matrix_cores(f64, a.mb))
+        hipLaunchKernelGGL(k_update_mfma, dim3(nbu, a.P), dim3(NT), 0, st, a, ns, (float*)S, (float*)HS, part, ctrl);
+    else
+        go_mask(a, [&](auto mk) {
+            constexpr bool M = decltype(mk)::value;
+            if (a.mb <= 8)
+                hipLaunchKernelGGL((k_update<8, M>), dim3(nbu, a.P), dim3(NT), 0, st, a, ns, (double*)S, (double*)HS,
+                                   part, ctrl);
+            else
+                hipLaunchKernelGGL((k_update<MAXB, M>), dim3(nbu, a.P), dim3(NT), 0, st, a, ns, (double*)S,
+                                   (double*)HS, part, ctrl);
+        });
     return hipGetLastError();
 }
 
-hipError_t launch_eig_control(const EigArgs& a, const double* part, int nblk, EigCtrl* ctrl, int first,
+hipError_t launch_eig_control(const EigArgs& a, const double* part, int nbg, int nbu, EigCtrl* ctrl, int first,
                               hipStream_t st) {
-    hipLaunchKernelGGL(k_eig_control, dim3(1, a.P), dim3(NT), 0, st, a, part, nblk, ctrl, first);
+    if (narrow(a))
+        hipLaunchKernelGGL(k_eig_control_narrow, dim3(1, a.P), dim3(WL), 0, st, a, part, nbg, ctrl, first);
+    else
+        hipLaunchKernelGGL(k_eig_control, dim3(1, a.P), dim3(NT), 0, st, a, part, nbu, ctrl, first);
     return hipGetLastError();
 }
 

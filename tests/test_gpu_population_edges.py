@@ -38,3 +38,26 @@ def test_member_equals_its_own_solve(Lx, Ly, k, guard, dt, masked):
         assert torch.equal(one.evals, pop.evals[y]) and torch.equal(one.V, pop.V[y])
         if one.status == M.CONVERGED:
             assert float(one.resid.max()) <= tol * plan.hessian_norm_bound()
+
+
+# the convergence control is taken inside the next iteration's first small step,
+# except at the end of a chunk of iterations: the chunk length changes nothing
+@pytest.mark.parametrize("Lx,Ly", [(9, 13), (130, 130)])
+@pytest.mark.parametrize("k,guard", [(1, 0), (1, 1), (1, 2), (2, 2), (2, 3)])
+@pytest.mark.parametrize("max_iter", [5, 60])
+def test_chunk_length_changes_nothing(Lx, Ly, k, guard, max_iter):
+    from paper_2509_26269_amd import moto as M
+
+    p = S.ham_3shell(Lx, Ly)
+    plan = M.Plan.from_params(p)
+    m = S.add_tilt_noise(S.skyrmion(Lx, Ly, min(Lx, Ly) / 5.0), 0.1, np.random.default_rng(Ly))
+    md = torch.as_tensor(m, device="cuda").contiguous()
+    out = []
+    for every in (1, 3, 8):
+        opts = M.eig_opts(M.MOTO_F64, tol=1e-7, guard=guard, max_iter=max_iter, check_every=every)
+        out.append(M.moto_min_modes(plan, md, k, M.MOTO_F64, opts=opts))
+    for r in out[1:]:
+        assert (r.status, r.iters, r.n_hvp) == (out[0].status, out[0].iters, out[0].n_hvp)
+        assert torch.equal(r.evals, out[0].evals) and torch.equal(r.V, out[0].V)
+        assert torch.equal(r.resid, out[0].resid)
+    assert out[0].iters <= max_iter
