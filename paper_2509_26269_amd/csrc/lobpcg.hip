@@ -265,8 +265,7 @@ __global__ __launch_bounds__(NT) void k_orth_gram(EigArgs a, int target, const T
 // keep a quarter of a compute unit's waves; here a thread (or a quad) owns one
 // entry, and the next chunk's loads are in flight under the dot products of the
 // current one.  Entries, chunk order and dot products are the general kernels',
-// so the sums keep their bits.  Gram, 24 x 128x128 FP32, k = 2: 25 -> 17.5 us
-// a call.
+// so the sums keep their bits.
 template <class T>
 struct SmallChunk {
     static constexpr int Q = SCOL * RCH / NT;  // staged values per thread (of one matrix)
@@ -832,6 +831,13 @@ __global__ __launch_bounds__(NT) void k_gram(EigArgs a, int ns_fixed, const T* _
     }
 }
 
+// Narrow blocks.  A quad of lanes takes a 2 x 2 tile of one of the two Grams,
+// lane q of it the rows q mod 4 (dot_quad's split, so the bits stay): four
+// loads and conversions serve four products, where an entry a thread had two
+// for each.  24 x 128x128 FP32, k = 2 (50 MB read): 16.8 -> 13.6 us a call.
+constexpr int GTC = SCOL / 2;                     // tile columns
+constexpr int GTILES = GTC * (GTC + 1) / 2;       // upper-triangle tiles of one Gram
+static_assert(4 * 2 * GTILES <= NT, "a quad per tile of either Gram");
 template <class T, bool MSK>
 __global__ __launch_bounds__(NT) void k_gram_small(EigArgs a, int ns_fixed, const T* __restrict__ S,
                                                    const T* __restrict__ HS, double* __restrict__ part,
@@ -843,10 +849,9 @@ __global__ __launch_bounds__(NT) void k_gram_small(EigArgs a, int ns_fixed, cons
     if (ctrl->done) return;
     using SC = SmallChunk<T>;
     __shared__ __align__(16) SC ss, sh;
-    static_assert(SCOL * (SCOL + 1) <= NT, "one entry per thread");
     const int n2 = a.n2;
     const int ns = sol_ns(a, ctrl, ns_fixed);
-    const int Eh = ns * (ns + 1) / 2, E = 2 * Eh;
+    const int Eh = ns * (ns + 1) / 2;
     const uint8_t* mk = MSK ? member_mask(a) : nullptr;
     const int rr = threadIdx.x % RCH;
     T v[SC::Q], w[SC::Q];
@@ -862,12 +867,16 @@ __global__ __launch_bounds__(NT) void k_gram_small(EigArgs a, int ns_fixed, cons
             w[q] = on ? HS[o] : T(0);
         }
     };
-    const int e = threadIdx.x;
-    int i = 0, j = 0;
-    if (e < E) tri_index(e < Eh ? e : e - Eh, ns, i, j);
-    const T* x = ss.ts[i];
-    const T* y = e < Eh ? sh.ts[j] : ss.ts[j];
-    double acc = 0.0;
+    const int q = threadIdx.x & 3;
+    int t = threadIdx.x >> 2;
+    const bool second = t >= GTILES;  // S^T S after S^T HS
+    if (second) t -= GTILES;
+    const bool on = t < GTILES;
+    int ti = 0, tj = 0;
+    if (on) tri_index(t, GTC, ti, tj);
+    const T* x = ss.ts[2 * ti];
+    const T* y = second ? ss.ts[2 * tj] : sh.ts[2 * tj];
+    double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
     const int nchunks = (n2 + RCH - 1) / RCH;
     if ((int)blockIdx.x < nchunks) load(blockIdx.x);
     for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
@@ -883,9 +892,33 @@ __global__ __launch_bounds__(NT) void k_gram_small(EigArgs a, int ns_fixed, cons
         if (ch + (int)gridDim.x < nchunks) load(ch + gridDim.x);
         if (!any) continue;
         __syncthreads();
-        if (e < E) acc += dot_chunk(x, y);
+        if (on && 2 * tj < ns) {
+            double d[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+#pragma unroll
+            for (int r0 = 0; r0 < RCH; r0 += 4) {
+                const double x0 = (double)x[r0 + q], x1 = (double)x[RCHP<T> + r0 + q];
+                const double y0 = (double)y[r0 + q], y1 = (double)y[RCHP<T> + r0 + q];
+                d[0][0] += x0 * y0;
+                d[0][1] += x0 * y1;
+                d[1][0] += x1 * y0;
+                d[1][1] += x1 * y1;
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int z = 0; z < 2; ++z) {
+                    double s = d[u][z];
+                    s += dpp_f64<0xB1>(s);
+                    s += dpp_f64<0x4E>(s);
+                    acc[u][z] += s;
+                }
+        }
     }
-    if (e < E) part[(size_t)blockIdx.x * PSTRIDE + e] = acc;
+    // lane q stores entry (q / 2, q % 2) of the tile
+    const int i = 2 * ti + (q >> 1), j = 2 * tj + (q & 1);
+    const double r = q == 0 ? acc[0][0] : q == 1 ? acc[0][1] : q == 2 ? acc[1][0] : acc[1][1];
+    if (on && i <= j && j < ns)
+        part[(size_t)blockIdx.x * PSTRIDE + (second ? Eh : 0) + i * ns - i * (i - 1) / 2 + (j - i)] = r;
 }
 
 // The Rayleigh-Ritz Grams on the matrix cores (FP32 blocks): a wave takes
@@ -1001,8 +1034,12 @@ __global__ __launch_bounds__(RR_WAVES * WL) void k_rr(EigArgs a, int ns_fixed, c
     rr_body<MAXS + 1, RR_WAVES>(a.mb, sol_ns(a, ctrl, ns_fixed), a.drop, Gtri, ctrl);
 }
 
-// Narrow blocks: the reduction of the Grams and the step in one launch.
-__global__ __launch_bounds__(RR_WAVES * WL) void k_rr_narrow(EigArgs a, int ns_fixed, const double* __restrict__ part,
+// Narrow blocks: the reduction of the Grams and the step in one launch.  Waves
+// beyond the step's own help with the reduction, 96 entries a pass instead of
+// 32, and end (16 waves would leave 128 registers to a wave, too few for the
+// step).  64x64, k = 2 FP64, 156 entries of 128 rows: 35.5 -> 32.4 us a call.
+constexpr int RRN_WAVES = 12;
+__global__ __launch_bounds__(RRN_WAVES * WL) void k_rr_narrow(EigArgs a, int ns_fixed, const double* __restrict__ part,
                                                              int nblk, EigCtrl* __restrict__ ctrl) {
     part += blockIdx.y * a.part_ms;
     ctrl += blockIdx.y;
@@ -1010,6 +1047,7 @@ __global__ __launch_bounds__(RR_WAVES * WL) void k_rr_narrow(EigArgs a, int ns_f
     __shared__ double Gl[SGRAM];
     const int ns = sol_ns(a, ctrl, ns_fixed);
     reduce_rows_wg(part, nblk, ns * (ns + 1), Gl);
+    if (threadIdx.x >= RR_WAVES * WL) return;
     rr_body<SCOL + 1, RR_WAVES>(a.mb, ns, a.drop, Gl, ctrl);
 }
 
@@ -1656,7 +1694,7 @@ hipError_t launch_gram(bool f64, const EigArgs& a, int ns, const void* S, const 
 hipError_t launch_rr(const EigArgs& a, int ns, const double* part, int nblk, double* G, EigCtrl* ctrl,
                      hipStream_t st) {
     if (narrow(a)) {
-        hipLaunchKernelGGL(k_rr_narrow, dim3(1, a.P), dim3(RR_WAVES * WL), 0, st, a, ns, part, nblk, ctrl);
+        hipLaunchKernelGGL(k_rr_narrow, dim3(1, a.P), dim3(RRN_WAVES * WL), 0, st, a, ns, part, nblk, ctrl);
     } else {
         const int E = 3 * a.mb * (3 * a.mb + 1);
         hipLaunchKernelGGL(k_reduce_rows, dim3((E + RED_E - 1) / RED_E, a.P), dim3(WL), 0, st, a, part, nblk, 1, ns,
