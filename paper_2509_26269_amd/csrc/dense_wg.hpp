@@ -9,6 +9,8 @@
 // width.
 #pragma once
 
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace moto {
@@ -418,6 +420,96 @@ __device__ __forceinline__ void waves_sync() {
         wsync();
 }
 
+// Sum over the 16 quads of x y, equal on a quad's lanes: the bits of
+// wsum_dpp(x * y) with quad r's product on lane r of 16 and zeros beyond.  There
+// the products meet their neighbours fused (x0 y0 + x1 y1, x7 y7 + x6 y6 as the
+// mirrors have it), so the quads are read where the same ones come first.
+__device__ __forceinline__ double qsum_dpp(double x, double y) {
+    double v = fma(x, y, dpp_f64<0x141>(x * y));  // row_half_mirror: the neighbouring quad
+    v += dpp_f64<0x128>(v);                       // row_ror 8: the other pair
+    return (rdlane(v, 0) + rdlane(v, 28)) + (rdlane(v, 32) + rdlane(v, 60));
+}
+
+// The Householder reduction of an n x n matrix, n <= 16, over the whole wave:
+// lane 4 r + q holds columns q, q + 4, ... of row r in a[], so a step's product
+// A v and its rank-2 update are four multiply-adds a lane and the quad's sum,
+// where a lane per row issued sixteen (a wave alone on its SIMD pays for every
+// instruction, ~4.6 cycles).  The partial sums are those of the row form, by
+// column mod 4, and so are the bits; the update's rounding is not symmetric, and
+// step k reduces row k, so b[] carries the transpose, from which lane r takes
+// its entry of that row without a trip through LDS.  Four steps a round: that
+// entry is then b[0] of quad lane k mod 4, and finished columns are shifted out.  Reflector k goes to V + 16 k, the subdiagonal to eh; returns
+// the diagonal entry r on lane r.  vb: 64 doubles of LDS, hw: 16.  n = 12: 7.2
+// -> 4.7 us of a Rayleigh-Ritz step, n = 9: 5.5 -> 3.5.
+__device__ __forceinline__ double tridiag_quad(double (&a)[4], double (&b)[4], int n, double* V, double* eh, double* vb,
+                                               double* hw) {
+    const int lane = wlane(), r = lane >> 2, q = lane & 3;
+    double* wb = vb + 32;
+    if (lane >= 16 && lane < 32) {  // columns past the last, met by shifted-in zeros
+        vb[lane] = 0.0;
+        wb[lane] = 0.0;
+    }
+    double d = 0.0, sub = 0.0;
+#pragma unroll 1
+    for (int k0 = 0; k0 < n; k0 += 4) {
+        auto step = [&](auto kkc) {
+            constexpr int KK = decltype(kkc)::value;
+            const int k = k0 + KK;
+            if (k + 2 >= n) return;
+            const double ck = dpp_f64<KK * 0x55>(b[0]);
+            const double x = r > k ? ck : 0.0;
+            const double x0 = rdlane(x, 4 * (k + 1));
+            const double x2 = qsum_dpp(x, x);
+            double v = 0.0, alpha = 0.0;
+            if (x2 > 0.0) {
+                const double nx = sqrt(x2);
+                alpha = x0 >= 0.0 ? -nx : nx;
+                // |x - alpha e|^2 = 2 (|x|^2 - alpha x0) > 0
+                v = (x - (r == k + 1 ? alpha : 0.0)) * rsqrt_nr(2.0 * (x2 - alpha * x0));
+            }
+            V[k * 16 + r] = v;
+            vb[r] = v;
+            eh[k] = alpha;
+            wsync();
+            if (x2 > 0.0) {
+                // A <- H A H = A - 2 (v w^T + w v^T), p = A v, w = p - (v.p) v
+                double vs[4], p = 0.0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) vs[i] = vb[k0 + 4 * i + q];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) p = fma(a[i], vs[i], p);
+                p += dpp_f64<0xB1>(p);
+                p += dpp_f64<0x4E>(p);
+                const double wv = fma(-qsum_dpp(p, v), v, p);
+                wb[r] = wv;
+                wsync();
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const double wc = wb[k0 + 4 * i + q];
+                    a[i] = fma(-2.0, fma(v, wc, wv * vs[i]), a[i]);
+                    b[i] = fma(-2.0, fma(vs[i], wv, wc * v), b[i]);
+                }
+            }
+            wsync();
+        };
+        step(std::integral_constant<int, 0>{});
+        step(std::integral_constant<int, 1>{});
+        step(std::integral_constant<int, 2>{});
+        step(std::integral_constant<int, 3>{});
+        if ((r >> 2) * 4 == k0 && q == (r & 3)) d = a[0];
+        if (r == n - 1 && k0 + q == n - 2) sub = a[0];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            a[i] = i < 3 ? a[i + 1] : 0.0;
+            b[i] = i < 3 ? b[i + 1] : 0.0;
+        }
+    }
+    if (q == (r & 3)) hw[r] = d;
+    if (n >= 2 && r == n - 1 && q == ((n - 2) & 3)) eh[n - 2] = sub;  // the last subdiagonal entry
+    wsync();
+    return lane < 16 ? hw[lane] : 0.0;
+}
+
 template <int NM, int NWS, int NWV = 1>
 __device__ __forceinline__ void symeig_low_nm(double* A, int lda, double* Z, int ldz, int n, int nw, double* w,
                                               double* sb) {
@@ -442,12 +534,17 @@ __device__ __forceinline__ void symeig_low_nm(double* A, int lda, double* Z, int
             return;
         }
     }
-    // ---- 1. tridiagonalisation, lane r holding row r ----
-    double a[NM];
+    // ---- 1. tridiagonalisation, lane r holding row r (n <= 16: a quad) ----
+    constexpr bool QUAD = NM == 16 && NWV > 1;  // alone: the whole-search kernel, whose register file is full
+    constexpr int NA = QUAD ? NM / 4 : NM;
+    double a[NA];
+    [[maybe_unused]] double at[4];  // QUAD: of the transpose
     bool fin = true;
 #pragma unroll
-    for (int c = 0; c < NM; ++c) {
-        a[c] = (lane < n && c < n) ? A[lane * lda + c] : 0.0;
+    for (int c = 0; c < NA; ++c) {
+        const int r = QUAD ? lane >> 2 : lane, cc = QUAD ? 4 * c + (lane & 3) : c;
+        a[c] = (r < n && cc < n) ? A[r * lda + cc] : 0.0;
+        if constexpr (QUAD) at[c] = (r < n && cc < n) ? A[cc * lda + r] : 0.0;
         fin = fin && (fabs(a[c]) <= 1.7976931348623157e308);
     }
     if (__ballot(!fin) != 0ull) {
@@ -465,61 +562,67 @@ __device__ __forceinline__ void symeig_low_nm(double* A, int lda, double* Z, int
     }
     wsync();  // A's storage takes the reflectors from here on: row k at V + k NM
     double* V = A;
-    for (int k = 0; k + 2 < n; ++k) {
-        if (lane == k) {
+    double dr = 0.0;  // lane r: diagonal entry r
+    if constexpr (QUAD) {
+        static_assert(3 * NWS >= 4, "two rows of 32 in the solver's scratch");
+        dr = tridiag_quad(a, at, n, V, eh, U0, hw);
+    } else {
+        for (int k = 0; k + 2 < n; ++k) {
+            if (lane == k) {
 #pragma unroll
-            for (int c = 0; c < NM; ++c) bc[c] = a[c];
-        }
-        wsync();
-        const double x = (lane > k && lane < n) ? bc[lane] : 0.0;
-        const double x0 = bc[k + 1];
-        const double x2 = wsum_dpp(x * x);
-        double v = 0.0, alpha = 0.0;
-        if (x2 > 0.0) {
-            const double nx = sqrt(x2);
-            alpha = x0 >= 0.0 ? -nx : nx;
-            // |x - alpha e|^2 = 2 (|x|^2 - alpha x0) > 0
-            v = (x - (lane == k + 1 ? alpha : 0.0)) * rsqrt_nr(2.0 * (x2 - alpha * x0));
-        }
-        if (lane < NM) V[k * NM + lane] = v;
-        if (lane == 0) eh[k] = alpha;
-        wsync();
-        if (x2 > 0.0) {
-            // A <- H A H = A - 2 (v w^T + w v^T), p = A v, w = p - (v.p) v;
-            // columns <= k (v is zero there) are never read again and skipped
-            const double* vk = V + k * NM;
-            double pa[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int c0 = 0; c0 < NM; c0 += 8)
-                if (c0 + 8 > k + 1) {
-                    if constexpr (NM > 32) asm volatile("" ::: "memory");
-#pragma unroll
-                    for (int c = c0; c < c0 + 8; ++c) pa[c & 3] = fma(a[c], vk[c], pa[c & 3]);
-                }
-            const double p = (pa[0] + pa[1]) + (pa[2] + pa[3]);
-            const double wv = p - wsum_dpp(p * v) * v;
-            if (lane < NM) hw[lane] = wv;
+                for (int c = 0; c < NM; ++c) bc[c] = a[c];
+            }
             wsync();
+            const double x = (lane > k && lane < n) ? bc[lane] : 0.0;
+            const double x0 = bc[k + 1];
+            const double x2 = wsum_dpp(x * x);
+            double v = 0.0, alpha = 0.0;
+            if (x2 > 0.0) {
+                const double nx = sqrt(x2);
+                alpha = x0 >= 0.0 ? -nx : nx;
+                // |x - alpha e|^2 = 2 (|x|^2 - alpha x0) > 0
+                v = (x - (lane == k + 1 ? alpha : 0.0)) * rsqrt_nr(2.0 * (x2 - alpha * x0));
+            }
+            if (lane < NM) V[k * NM + lane] = v;
+            if (lane == 0) eh[k] = alpha;
+            wsync();
+            if (x2 > 0.0) {
+                // A <- H A H = A - 2 (v w^T + w v^T), p = A v, w = p - (v.p) v;
+                // columns <= k (v is zero there) are never read again and skipped
+                const double* vk = V + k * NM;
+                double pa[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int c0 = 0; c0 < NM; c0 += 8)
-                if (c0 + 8 > k + 1) {
-                    // one chunk of broadcast operands live at a time (the
-                    // scheduler would otherwise hoist all 2 NM of them)
-                    if constexpr (NM > 32) asm volatile("" ::: "memory");
+                for (int c0 = 0; c0 < NM; c0 += 8)
+                    if (c0 + 8 > k + 1) {
+                        if constexpr (NM > 32) asm volatile("" ::: "memory");
 #pragma unroll
-                    for (int c = c0; c < c0 + 8; ++c) a[c] -= 2.0 * (v * hw[c] + wv * vk[c]);
-                }
+                        for (int c = c0; c < c0 + 8; ++c) pa[c & 3] = fma(a[c], vk[c], pa[c & 3]);
+                    }
+                const double p = (pa[0] + pa[1]) + (pa[2] + pa[3]);
+                const double wv = p - wsum_dpp(p * v) * v;
+                if (lane < NM) hw[lane] = wv;
+                wsync();
+#pragma unroll
+                for (int c0 = 0; c0 < NM; c0 += 8)
+                    if (c0 + 8 > k + 1) {
+                        // one chunk of broadcast operands live at a time (the
+                        // scheduler would otherwise hoist all 2 NM of them)
+                        if constexpr (NM > 32) asm volatile("" ::: "memory");
+#pragma unroll
+                        for (int c = c0; c < c0 + 8; ++c) a[c] -= 2.0 * (v * hw[c] + wv * vk[c]);
+                    }
+            }
+            wsync();
         }
+        double sub = 0.0;
+#pragma unroll
+        for (int c = 0; c < NM; ++c) {
+            dr = c == lane ? a[c] : dr;
+            sub = c + 1 == lane ? a[c] : sub;
+        }
+        if (n >= 2 && lane == n - 1) eh[n - 2] = sub;  // the last subdiagonal entry
         wsync();
     }
-    double dr = 0.0, sub = 0.0;
-#pragma unroll
-    for (int c = 0; c < NM; ++c) {
-        dr = c == lane ? a[c] : dr;
-        sub = c + 1 == lane ? a[c] : sub;
-    }
-    if (n >= 2 && lane == n - 1) eh[n - 2] = sub;  // the last subdiagonal entry
-    wsync();
     const double er = lane + 1 < n ? eh[lane] : 0.0;
     const double el = (lane >= 1 && lane < n) ? eh[lane - 1] : 0.0;
     // power-of-two scale above the Gershgorin bound: ||T / s|| < 1
