@@ -198,12 +198,13 @@ def _ptr(t: Optional[torch.Tensor]):
         raise MotoError("tensor must live on the GPU")
     if not t.is_contiguous():
         raise MotoError("tensor must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dt(t: torch.Tensor) -> int:
