@@ -219,14 +219,16 @@ __device__ void symeig_wg(double* A, double* Z, int n) {
 // (n - 2) NM <= lda^2.  On return w[j] and column j of Z (leading dimension
 // ldz) hold the j-th smallest eigenpair, j < min(nw, n), ascending.  A
 // non-finite entry of A gives NaN eigenpairs.  sb: LDS scratch of
-// symeig_low_doubles(NM, NWS) doubles; eigenvectors are solved NWS at a time.
+// symeig_low_doubles(NM, NWS, NWV) doubles; eigenvectors are solved NWS at a time.
 // With NWV > 1 all NWV waves of the workgroup (threads 0 .. 64 NWV - 1) call
 // it: the multisection then counts at 64 NWV points per round (fewer rounds),
 // everything else runs on wave 0, and the waves meet at two workgroup
 // barriers; on return only wave 0 has finished the eigenvectors (the others
 // return after the multisection).
 // --------------------------------------------------------------------------
-constexpr int symeig_low_doubles(int nm, int nws) { return 3 * nm * nws + 5 * nm + WL + 2; }
+constexpr int symeig_low_doubles(int nm, int nws, int nwv) {
+    return 3 * nm * nws + 5 * nm + WL + 2 + (nwv > 1 ? nm * nws : 0);
+}
 
 // 1/x to FP64 accuracy: the hardware estimate refined by two Newton steps
 __device__ __forceinline__ double rcp_nr(double x) {
@@ -333,7 +335,8 @@ __device__ __forceinline__ int sturm_below(const double* dh, const double* e2s, 
 template <int NM, int L>
 __device__ __forceinline__ void back_reflect_split(const double* V, double* Z, int ldz, int n, int nw) {
     static_assert(L == 4 || L == 8, "quad or half-row groups");
-    constexpr int R = (NM + L - 1) / L;
+    static_assert(NM % L == 0, "whole rows per lane");
+    constexpr int R = NM / L;
     const int lane = wlane(), j = lane / L, t = lane - j * L;
     const bool act = j < nw;
     double y[R], vn[R];
@@ -346,7 +349,7 @@ __device__ __forceinline__ void back_reflect_split(const double* V, double* Z, i
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             const int r = t + L * i;
-            vn[i] = r < NM ? V[(n - 3) * NM + r] : 0.0;
+            vn[i] = V[(n - 3) * NM + r];
         }
     }
     for (int k = n - 3; k >= 0; --k) {
@@ -357,7 +360,7 @@ __device__ __forceinline__ void back_reflect_split(const double* V, double* Z, i
 #pragma unroll
             for (int i = 0; i < R; ++i) {
                 const int r = t + L * i;
-                vn[i] = r < NM ? V[(k - 1) * NM + r] : 0.0;
+                vn[i] = V[(k - 1) * NM + r];
             }
         }
         double d = 0.0;
@@ -524,9 +527,15 @@ __device__ __forceinline__ void symeig_low_nm(double* A, int lda, double* Z, int
     double* bc = e2s + NM;
     double* hw = bc + NM;
     double* lamh = hw + NM;
+    // NWV > 1: entry i of the right-hand side of the inverse iteration for
+    // eigenvector j, [i][j], of the first NWS vectors
+    double* rh = lamh + WL + 2;
     if constexpr (NWV > 1) {
-        // waves 1 .. NWV-1: only the multisection (after wave 0's reduction)
+        // waves 1 .. NWV-1: the right-hand sides (their 64-bit products off
+        // wave 0's path), then the multisection after wave 0's reduction
         if (threadIdx.x >= WL) {
+            for (int q = (int)threadIdx.x - WL; q < NM * NWS; q += (NWV - 1) * WL)
+                rh[q] = 2.0 * splitmix_uniform(0x5EED0000ull + (uint64_t)(q % NWS), (uint64_t)(q / NWS)) - 1.0;
             __syncthreads();
             if (lamh[WL] != 0.0) return;  // non-finite input
             multisect<NM, NWV>(dh, e2s, n, nw < n ? nw : n, lamh);
@@ -646,31 +655,48 @@ __device__ __forceinline__ void symeig_low_nm(double* A, int lda, double* Z, int
     multisect<NM, NWV>(dh, e2s, n, nw, lamh);
     waves_sync<NWV>();
     // ---- 3. inverse iteration, NWS eigenvalues at a time; vector j in column j of Z ----
+    // The chain of one vector's elimination sets the time.  With several waves its
+    // reads are issued without a test in front (each would otherwise wait out its
+    // latency) and its right-hand sides are ready: n = 12, four vectors, 3.9 ->
+    // 3.2 us of a Rayleigh-Ritz step, n = 36, twelve, 11.3 -> 7.1.
     constexpr double pmin = 0x1p-52;
+    constexpr bool LEAN = NWV > 1;
+    double scale = 1.0;  // 1 / |vector| of this lane
     for (int j0 = 0; j0 < nw; j0 += NWS) {
         const int sl = lane - j0;
         if (sl >= 0 && sl < NWS && lane < nw) {
             const double lm = lamh[lane];
             const uint64_t seed = 0x5EED0000ull + (uint64_t)lane;
-            double scale = 1.0;
             // one solve: lambda is exact to rounding, so the wanted component
             // grows by ~1 / (eps ||T||) and any other by 1 / gap; what is left
             // inside a cluster is removed below
             {
+                const bool tab = LEAN && j0 == 0;
                 auto rhs = [&](int i) { return 2.0 * splitmix_uniform(seed, (uint64_t)i) - 1.0; };
+                auto at = [](const double* p, int i, bool ok) { return LEAN || ok ? p[i] : 0.0; };
                 // forward elimination with row interchanges; the current row
                 // (r0, r1) sits at columns (i, i + 1), right-hand side cr
-                double r0 = dh[0] - lm, r1 = eh[0], cr = rhs(0);
+                double r0 = dh[0] - lm, r1 = eh[0], cr = tab ? rh[sl] : rhs(0);
                 for (int c0 = 0; c0 + 1 < n; c0 += 8) {
                     double sd[8], nd[8], ne[8], bn[8];
 #pragma unroll
                     for (int q = 0; q < 8; ++q) {
                         const int i = c0 + q;
                         const bool ok = i + 1 < n;
-                        sd[q] = ok ? eh[i] : 0.0;
-                        nd[q] = ok ? dh[i + 1] : 0.0;
-                        ne[q] = ok ? eh[i + 1] : 0.0;
-                        bn[q] = ok ? rhs(i + 1) : 0.0;
+                        const int i1 = LEAN && i + 1 >= NM ? NM - 1 : i + 1;
+                        sd[q] = at(eh, i, ok);
+                        nd[q] = at(dh, i1, ok);
+                        ne[q] = at(eh, i1, ok);
+                        if constexpr (!LEAN) bn[q] = ok ? rhs(i + 1) : 0.0;
+                    }
+                    if constexpr (LEAN) {
+                        if (tab) {
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) bn[q] = rh[(c0 + q + 1 >= NM ? NM - 1 : c0 + q + 1) * NWS + sl];
+                        } else {
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) bn[q] = rhs(c0 + q + 1);
+                        }
                     }
 #pragma unroll
                     for (int q = 0; q < 8; ++q) {
@@ -704,10 +730,11 @@ __device__ __forceinline__ void symeig_low_nm(double* A, int lda, double* Z, int
                     for (int q = 0; q < 8; ++q) {
                         const int i = c1 - q;
                         const bool ok = i >= 0;
-                        u0[q] = ok ? U0[i * NWS + sl] : 0.0;
-                        u1[q] = ok ? U1[i * NWS + sl] : 0.0;
-                        u2[q] = ok ? U2[i * NWS + sl] : 0.0;
-                        yy[q] = ok ? Z[i * ldz + lane] : 0.0;
+                        const int i0 = LEAN && i < 0 ? 0 : i;
+                        u0[q] = at(U0, i0 * NWS + sl, ok);
+                        u1[q] = at(U1, i0 * NWS + sl, ok);
+                        u2[q] = at(U2, i0 * NWS + sl, ok);
+                        yy[q] = at(Z, i0 * ldz + lane, ok);
                     }
 #pragma unroll
                     for (int q = 0; q < 8; ++q) {
@@ -723,7 +750,8 @@ __device__ __forceinline__ void symeig_low_nm(double* A, int lda, double* Z, int
                 }
                 scale = rsqrt_nr(ss);
             }
-            for (int i = 0; i < n; ++i) Z[i * ldz + lane] *= scale;
+            if constexpr (!LEAN)
+                for (int i = 0; i < n; ++i) Z[i * ldz + lane] *= scale;
         }
         wsync();
     }
@@ -731,7 +759,14 @@ __device__ __forceinline__ void symeig_low_nm(double* A, int lda, double* Z, int
     // the scaled norm), the own column in registers ----
     double y[NM];
 #pragma unroll
-    for (int c = 0; c < NM; ++c) y[c] = (lane < nw && c < n) ? Z[c * ldz + lane] : 0.0;
+    for (int c = 0; c < NM; ++c) {
+        if constexpr (LEAN) {
+            const double z = Z[(c < n ? c : n - 1) * ldz + (lane < nw ? lane : nw - 1)];
+            y[c] = (lane < nw && c < n) ? z * scale : 0.0;
+        } else {
+            y[c] = (lane < nw && c < n) ? Z[c * ldz + lane] : 0.0;
+        }
+    }
     const bool brk = lane < nw && (lane == 0 || lamh[lane] - lamh[lane - 1] > 1e-3);
     const unsigned long long bm = __ballot(brk) | (nw < WL ? (~0ull << nw) : 0ull);
     auto normalize = [&]() {
@@ -822,7 +857,7 @@ __device__ __forceinline__ void symeig_low_nm(double* A, int lda, double* Z, int
 template <int LD, int NWS, int NMAX = ((LD - 1 + 15) / 16) * 16, int NWV = 1>
 __device__ __forceinline__ void symeig_low(double* A, double* Z, int n, int nw, double* w) {
     static_assert(NMAX % 16 == 0 && NMAX <= WL, "one lane per row, buckets of 16 at the top");
-    __shared__ double sb[symeig_low_doubles(NMAX, NWS)];
+    __shared__ double sb[symeig_low_doubles(NMAX, NWS, NWV)];
     if (n <= 0 || nw <= 0) return;
     if (n <= 16 || NMAX == 16) {
         symeig_low_nm<16, NWS, NWV>(A, LD, Z, LD, n, nw, w, sb);
@@ -852,14 +887,27 @@ __device__ __forceinline__ void symeig_low(double* A, double* Z, int n, int nw, 
 }
 
 // --------------------------------------------------------------------------
+// quotient of small non-negative integers (i < 4096, n <= 64) by the rounded
+// reciprocal of n: the half keeps the product away from an integer by more than
+// its error
+__device__ __forceinline__ int small_div(int i, float inv_n) { return (int)(((float)i + 0.5f) * inv_n); }
+
 // Visit (a, b), a < na, b < nb, in lane-strided order of a * nb + b, with
-// one integer division per call instead of one per element.
-template <class F>
+// one integer division per call instead of one per element; LEAN: by the
+// reciprocal (a division is 40 instructions, 80 ns of a wave on its own).
+template <bool LEAN = false, class F>
 __device__ __forceinline__ void for2(int na, int nb, F&& f) {
     if (na <= 0 || nb <= 0) return;
     const int lane = wlane();
-    int a = lane / nb, b = lane % nb;
-    const int qa = WL / nb, qb = WL % nb;
+    int a, b, qa, qb;
+    if constexpr (LEAN) {
+        const float inv = __builtin_amdgcn_rcpf((float)nb);
+        a = small_div(lane, inv), b = lane - a * nb;
+        qa = small_div(WL, inv), qb = WL - qa * nb;
+    } else {
+        a = lane / nb, b = lane % nb;
+        qa = WL / nb, qb = WL % nb;
+    }
     for (int i = lane; i < na * nb; i += WL) {
         f(a, b);
         a += qa;
@@ -880,7 +928,7 @@ __device__ __forceinline__ void for2(int na, int nb, F&& f) {
 // where M = Y^T Y - B^T B = Z diag(theta) Z^T after diagonal scaling D;
 // columns whose projected norm is negligible get a zero transform.
 // --------------------------------------------------------------------------
-template <int LD>
+template <int LD, bool LEAN = false>
 __device__ bool orth_small_body(int mb, int nq, double drop, const double* G, double* Bw, double* Tw);
 
 // --------------------------------------------------------------------------
@@ -1062,23 +1110,82 @@ __device__ __forceinline__ bool chol_inv_wg(double* A, double* Z, int n, double 
     return true;
 }
 
+// The same for n <= 4 in registers, every lane alike: the factorisation is a
+// chain of divisions and square roots, to which the general form adds LDS round
+// trips and index arithmetic (2.2 us at n = 4, here 0.9).  A is left alone.
 template <int LD>
+__device__ __forceinline__ bool chol_inv_4(const double* A, double* Z, int n, double tau, double* minpiv = nullptr) {
+    constexpr int M = 4;
+    const int lane = wlane();
+    double L[M][M];
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+        for (int k = 0; k <= i; ++k) L[i][k] = A[(i < n ? i : n - 1) * LD + (k < n ? k : n - 1)];
+    double dmin = INFINITY;
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+        if (j >= n) break;
+        const double d = L[j][j];
+        if (!(d > tau)) return false;
+        dmin = fmin(dmin, d);
+        const double id = 1.0 / d;
+#pragma unroll
+        for (int i = j + 1; i < M; ++i)
+#pragma unroll
+            for (int k = j + 1; k <= i; ++k) L[i][k] = fma(-(L[i][j] * L[k][j]), id, L[i][k]);
+        const double r = sqrt(d), ir = 1.0 / r;
+#pragma unroll
+        for (int i = j + 1; i < M; ++i) L[i][j] *= ir;
+        L[j][j] = r;
+    }
+    double x[M];
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+        double v = i == lane ? 1.0 : 0.0;
+#pragma unroll
+        for (int k = 0; k < i; ++k) v = fma(-L[i][k], x[k], v);
+        x[i] = i < lane ? 0.0 : v / L[i][i];
+    }
+    if (lane < n) {
+#pragma unroll
+        for (int c = 0; c < M; ++c)
+            if (c < n) Z[lane * LD + c] = x[c];
+    }
+    wsync();
+    if (minpiv) *minpiv = dmin;
+    return true;
+}
+
+// LEAN: a narrow block's step on a wave of its own (the whole-search kernel,
+// at the register limit, takes the general forms)
+template <int LD, bool LEAN>
+__device__ __forceinline__ bool chol_inv_small(double* A, double* Z, int n, double tau, double* minpiv = nullptr) {
+    if constexpr (LEAN && LD / 3 <= 4)
+        return chol_inv_4<LD>(A, Z, n, tau, minpiv);
+    else
+        return chol_inv_wg<LD>(A, Z, n, tau, minpiv);
+}
+
+template <int LD, bool LEAN>
 __device__ bool orth_small_body(int mb, int nq, double drop, const double* G, double* Bw, double* Tw) {
-    // G is read many times below: it is first copied to LDS
+    // G is read many times below: it is first copied to LDS (LEAN: it is there)
     constexpr int MBL = LD / 3;
     __shared__ double A[MBL * LD];
     __shared__ double Z[MBL * LD];
     __shared__ double dsc[MBL], th[MBL], thv[MBL];
     __shared__ int keep[MBL];
-    __shared__ double Gl[LD * MBL];
+    __shared__ double Gl[LEAN ? 1 : LD * MBL];
     __shared__ double Mq[MBL * MBL];
     const int tid = wlane();
     const int nrow = nq + mb;
+    if constexpr (!LEAN) {
 #pragma unroll 8  // several global loads in flight per lane
-    for (int i = tid; i < nrow * mb; i += WL) Gl[i] = G[i];
-    wsync();
-    G = Gl;
-    for2(mb, nq, [&](int j, int r) {
+        for (int i = tid; i < nrow * mb; i += WL) Gl[i] = G[i];
+        wsync();
+        G = Gl;
+    }
+    for2<LEAN>(mb, nq, [&](int j, int r) {
         Bw[r + 2 * MAXB * j] = G[j * nrow + r];
     });
     // M = Y^T Y - B^T B with B = Q^T Y (B[l][c] = G[c nrow + l]); B^T B kept
@@ -1097,7 +1204,7 @@ __device__ bool orth_small_body(int mb, int nq, double drop, const double* G, do
     kept = -wmax_dpp(-kept);
     wsync();
     double emax = 0.0;
-    for2(mb, mb, [&](int c, int r) {
+    for2<LEAN>(mb, mb, [&](int c, int r) {
         const double v = A[r * LD + c] * dsc[r] * dsc[c];
         A[r * LD + c] = v;
         if (r != c) emax = fmax(emax, fabs(v));
@@ -1117,7 +1224,7 @@ __device__ bool orth_small_body(int mb, int nq, double drop, const double* G, do
                   [&](int i, int j, double v) {
                       Z[i * LD + j] = (i == j ? 1.0 : 0.0) - 0.5 * A[i * LD + j] + 0.375 * v;
                   });
-    } else if (chol_inv_wg<LD>(A, Z, mb, 1e-6, &minpiv)) {
+    } else if (chol_inv_small<LD, LEAN>(A, Z, mb, 1e-6, &minpiv)) {
         // well conditioned: T = D R^-1 spans the same space (Rayleigh-Ritz
         // does not depend on which orthonormal basis of it is taken)
         nkeep = mb;
@@ -1129,7 +1236,7 @@ __device__ bool orth_small_body(int mb, int nq, double drop, const double* G, do
         wsync();
     } else {
         // rebuild D M D (the factorisation overwrote it) and drop directions
-        for2(mb, mb, [&](int c, int r) {
+        for2<LEAN>(mb, mb, [&](int c, int r) {
             A[r * LD + c] = (G[c * nrow + nq + r] - Mq[r * MBL + c]) * dsc[r] * dsc[c];
         });
         wsync();
@@ -1138,7 +1245,7 @@ __device__ bool orth_small_body(int mb, int nq, double drop, const double* G, do
         if (tid < nkeep) th[tid] = thv[keep[tid]];
         wsync();
     }
-    for2(mb, mb, [&](int c, int row) {
+    for2<LEAN>(mb, mb, [&](int c, int row) {
         Tw[row + mb * c] = c < nkeep ? dsc[row] * Z[row * LD + keep[c]] / sqrt(th[c]) : 0.0;
     });
     wsync();
@@ -1163,6 +1270,7 @@ __device__ __forceinline__ void rr_body(int mb, int ns, double drop, const doubl
     constexpr int MBL = LD / 3;
     static_assert(MBL <= 16, "block width within one tile");
     constexpr int TX = (LD - 1 + 15) / 16;  // tiles along the basis
+    constexpr bool LEAN = NWV > 1;
     __shared__ double A[LD * LD];
     __shared__ double Z[LD * LD];
     __shared__ double Tm[LD * LD];
@@ -1188,9 +1296,13 @@ __device__ __forceinline__ void rr_body(int mb, int ns, double drop, const doubl
             GBf[i * LD + j] = Gtri[Eh + e];
         };
         if constexpr (NWV > 1) {
-            for (int q = (int)threadIdx.x; q < ns * ns; q += NWV * WL) put(q / ns, q % ns);
+            const float inv = __builtin_amdgcn_rcpf((float)ns);
+            for (int q = (int)threadIdx.x; q < ns * ns; q += NWV * WL) {
+                const int i = small_div(q, inv);
+                put(i, q - i * ns);
+            }
         } else {
-            for2(ns, ns, put);
+            for2<LEAN>(ns, ns, put);
         }
         waves_sync<NWV>();
     }
@@ -1202,7 +1314,7 @@ __device__ __forceinline__ void rr_body(int mb, int ns, double drop, const doubl
         }
         wsync();
         double emax = 0.0;
-        for2(ns, ns, [&](int r, int c) {
+        for2<LEAN>(ns, ns, [&](int r, int c) {
             const double v = dsc[r] * GB(r, c) * dsc[c];
             A[r * LD + c] = v;
             if (r != c) emax = fmax(emax, fabs(v));
@@ -1220,7 +1332,7 @@ __device__ __forceinline__ void rr_body(int mb, int ns, double drop, const doubl
             r = wave_compact(ns, [&](int i) { return dsc[i] > 0.0; }, keep);
             wave_gemm<TX, TX>(ns, ns, ns, [&](int i, int l) { return A[i * LD + l]; }, [&](int l, int j) { return A[l * LD + j]; },
                       [&](int i, int j, double v) { Z[i * LD + j] = v; });  // Z <- E^2
-            for2(ns, r, [&](int row, int c) {  // T (ns x r)
+            for2<LEAN>(ns, r, [&](int row, int c) {  // T (ns x r)
                 const int k = keep[c];
                 const double t0 = (row == k ? 1.0 : 0.0) - 0.5 * A[row * LD + k] + 0.375 * Z[row * LD + k];
                 Tm[row * LD + c] = dsc[row] * t0;
@@ -1232,7 +1344,7 @@ __device__ __forceinline__ void rr_body(int mb, int ns, double drop, const doubl
             r = wave_compact(ns, [&](int i) { return A[i * LD + i] > drop * tmax; }, keep);
             if (tid < r) th[tid] = A[keep[tid] * LD + keep[tid]];
             wsync();
-            for2(ns, r, [&](int row, int c) {  // T (ns x r)
+            for2<LEAN>(ns, r, [&](int row, int c) {  // T (ns x r)
                 Tm[row * LD + c] = dsc[row] * Z[row * LD + keep[c]] / sqrt(th[c]);
             });
             wsync();
@@ -1256,7 +1368,7 @@ __device__ __forceinline__ void rr_body(int mb, int ns, double drop, const doubl
             });
         } else {
             TtZ([&](int i, int c, double v) { A[i * LD + c] = v; });
-            for2(r, r, [&](int row, int c) {
+            for2<LEAN>(r, r, [&](int row, int c) {
                 if (row < c) {
                     const double v = 0.5 * (A[row * LD + c] + A[c * LD + row]);
                     A[row * LD + c] = v;
@@ -1286,7 +1398,7 @@ __device__ __forceinline__ void rr_body(int mb, int ns, double drop, const doubl
                   A[row * MBL + j] = v;
                   out->C[row + ns * j] = v;
               });
-    for2(mb - mcol, ns, [&](int j, int row) {
+    for2<LEAN>(mb - mcol, ns, [&](int j, int row) {
         A[row * MBL + mcol + j] = 0.0;
         out->C[row + ns * (mcol + j)] = 0.0;
     });
@@ -1294,7 +1406,7 @@ __device__ __forceinline__ void rr_body(int mb, int ns, double drop, const doubl
     if (tid == 0) out->rank = r;
     wsync();
     // ---- P complement: Cwp in the Tm region (ld MBL) ----
-    for2(mb, ns, [&](int j, int row) {
+    for2<LEAN>(mb, ns, [&](int j, int row) {
         Tm[row * MBL + j] = row < mb ? 0.0 : A[row * MBL + j];
     });
     wsync();
@@ -1316,12 +1428,12 @@ __device__ __forceinline__ void rr_body(int mb, int ns, double drop, const doubl
         dsc[tid] = d > 1e-24 ? 1.0 / sqrt(d) : 0.0;
     }
     wsync();
-    for2(mb, mb, [&](int j, int p) {
+    for2<LEAN>(mb, mb, [&](int j, int p) {
         Z[p * LD + j] = dsc[p] * h1[p + MBL * j] * dsc[j];
     });
     wsync();
     int rp;
-    if (chol_inv_wg<LD>(Z, A, mb, 1e-6)) {
+    if (chol_inv_small<LD, LEAN>(Z, A, mb, 1e-6)) {
         // well conditioned: Cp = Cwp D R^-1 (any orthonormal basis of the span)
         rp = mb;
         if (tid < mb) {
@@ -1330,7 +1442,7 @@ __device__ __forceinline__ void rr_body(int mb, int ns, double drop, const doubl
         }
         wsync();
     } else {
-        for2(mb, mb, [&](int j, int p) {
+        for2<LEAN>(mb, mb, [&](int j, int p) {
             Z[p * LD + j] = dsc[p] * h1[p + MBL * j] * dsc[j];
         });
         wsync();
@@ -1343,7 +1455,7 @@ __device__ __forceinline__ void rr_body(int mb, int ns, double drop, const doubl
     wave_gemm<TX, 1>(ns, rp, mb, [&](int row, int l) { return Tm[row * MBL + l] * dsc[l]; },
               [&](int l, int j) { return A[l * LD + keep[j]]; },
               [&](int row, int j, double v) { out->Cp[row + ns * j] = v * th[j]; });
-    for2(mb - rp, ns, [&](int j, int row) { out->Cp[row + ns * (rp + j)] = 0.0; });
+    for2<LEAN>(mb - rp, ns, [&](int j, int row) { out->Cp[row + ns * (rp + j)] = 0.0; });
     wsync();
 }
 

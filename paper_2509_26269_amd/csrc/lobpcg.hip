@@ -600,7 +600,7 @@ __global__ __launch_bounds__(SORTH_WAVES * WL) void k_orth_small_narrow(EigArgs 
     reduce_rows_wg(part, nblk, pending ? E + a.mb : E, Gl);
     if (threadIdx.x >= WL) return;
     if (pending && control_wave(a, Gl + E, false, ctrl)) return;
-    orth_settle(target, orth_small_body<SCOL + 1>(a.mb, nq, a.drop, Gl, ctrl->Bw, ctrl->Tw), ctrl);
+    orth_settle(target, orth_small_body<SCOL + 1, true>(a.mb, nq, a.drop, Gl, ctrl->Bw, ctrl->Tw), ctrl);
 }
 
 // Row transform on the vector ALUs.  MB: compile-time
