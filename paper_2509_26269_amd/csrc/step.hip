@@ -91,6 +91,12 @@ struct Ring {
     int c_new, h_new, slot;
 };
 
+// slot of logical pair j < mem (a division would cost 40 instructions)
+__device__ __forceinline__ int ring_slot(int head, int j, int mem) {
+    const int q = head + j;
+    return q >= mem ? q - mem : q;
+}
+
 __device__ __forceinline__ Ring ring_next(const StepHdr* h, int mem, int rule) {
     Ring r;
     r.slot = -1;
@@ -98,11 +104,11 @@ __device__ __forceinline__ Ring ring_next(const StepHdr* h, int mem, int rule) {
     r.h_new = h->head;
     if (h->have_prev && (rule == 0 || rule == 2)) {
         if (h->count < mem) {
-            r.slot = (h->head + h->count) % mem;
+            r.slot = ring_slot(h->head, h->count, mem);
             r.c_new = h->count + 1;
         } else {
             r.slot = h->head;
-            r.h_new = (h->head + 1) % mem;
+            r.h_new = ring_slot(h->head, 1, mem);
         }
     }
     return r;
@@ -207,7 +213,7 @@ __global__ __launch_bounds__(GNT) void k_step_gram(StepArgs a, const double* __r
             for (int r = 0; r < MAXR; ++r) vr[r][cc] = on && r < a.k_reflect ? V[r * n3 + o] : 0.0;
 #pragma unroll
             for (int q = 0; q < GJ; ++q) {
-                const int j = wv + GW * q, ph = (rg.h_new + j) % a.mem;
+                const int j = wv + GW * q, ph = ring_slot(rg.h_new, j, a.mem);
                 const bool st = on && j < c && ph != rg.slot;
                 sv[q][cc] = st ? P.S[ph * P.vstride + o] : 0.0;
                 yv[q][cc] = st ? P.Y[ph * P.vstride + o] : 0.0;
@@ -273,7 +279,7 @@ __global__ __launch_bounds__(GNT) void k_step_gram(StepArgs a, const double* __r
             for (int q = 0; q < GJ; ++q) {
                 const int j = wv + GW * q;
                 if (j >= c) break;
-                const int ph = (rg.h_new + j) % a.mem;
+                const int ph = ring_slot(rg.h_new, j, a.mem);
                 const bool fresh = ph == rg.slot;
                 if (fresh) {
 #pragma unroll
@@ -535,7 +541,7 @@ __global__ __launch_bounds__(NT) void k_step_dir(StepArgs a, const double* __res
 #pragma unroll
             for (int q = 0; q < JU; ++q) {
                 const int j = min(j0 + q, cu - 1);
-                const size_t o = ((head + j) % a.mem) * P.vstride + s;
+                const size_t o = ring_slot(head, j, a.mem) * P.vstride + s;
 #pragma unroll
                 for (int cc = 0; cc < 3; ++cc) {
                     sv[q][cc] = P.S[o + cc * N];
