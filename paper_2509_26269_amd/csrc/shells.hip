@@ -96,20 +96,29 @@ struct DiscRow {
                                                  const GenCoef<T, NS>& k, T (&acc)[TL::HSP]) {
         (term<I>(win, k, acc), ...);
     }
-    static __device__ __forceinline__ void run(const T* __restrict__ row, const GenCoef<T, NS>& k,
-                                               T (&acc)[TL::HSP]) {
-        T win[WN];
-        load(row, win);
-        terms(std::make_integer_sequence<int, HI - LO + 1>{}, win, k, acc);
-        // one row's window live at a time
-        __builtin_amdgcn_sched_barrier(0);
+    // the row's terms, with the next row's window on its way
+    static __device__ __forceinline__ void run(const T* __restrict__ base, const T (&win)[WN],
+                                               const GenCoef<T, NS>& k, T (&acc)[TL::HSP]) {
+        constexpr auto dxs = std::make_integer_sequence<int, HI - LO + 1>{};
+        if constexpr (DY < TL::RY) {
+            using Next = DiscRow<T, NS, TL, DY + 1>;
+            T nxt[Next::WN];
+            Next::load(base + (DY + 1 + TL::RY) * TL::LS, nxt);
+            terms(dxs, win, k, acc);
+            __builtin_amdgcn_sched_barrier(0);  // two windows live
+            Next::run(base, nxt, k, acc);
+        } else {
+            terms(dxs, win, k, acc);
+        }
     }
 };
 
-template <class T, int NS, class TL, int... Y>
-__device__ __forceinline__ void disc_rows(std::integer_sequence<int, Y...>, const T* __restrict__ base,
-                                          const GenCoef<T, NS>& k, T (&acc)[TL::HSP]) {
-    (DiscRow<T, NS, TL, Y - TL::RY>::run(base + Y * TL::LS, k, acc), ...);
+template <class T, int NS, class TL>
+__device__ __forceinline__ void disc_rows(const T* __restrict__ base, const GenCoef<T, NS>& k, T (&acc)[TL::HSP]) {
+    using First = DiscRow<T, NS, TL, -TL::RY>;
+    T win[First::WN];
+    First::load(base, win);
+    First::run(base, win, k, acc);
 }
 
 // Field (A u) at the thread's HSP sites (lx0.., ly0), without anisotropy.
@@ -129,7 +138,7 @@ __device__ __forceinline__ void disc_field(const TL& L, int lx0, int ly0, const 
         T acc[TL::HSP];
 #pragma unroll
         for (int q = 0; q < TL::HSP; ++q) acc[q] = T(0);
-        disc_rows<T, NS, TL>(std::make_integer_sequence<int, 2 * TL::RY + 1>{}, &L.u[cc][ly0][lx0], k, acc);
+        disc_rows<T, NS, TL>(&L.u[cc][ly0][lx0], k, acc);
 #pragma unroll
         for (int q = 0; q < TL::HSP; ++q) {
             a[q][0] = cc == 0 ? acc[q] : a[q][0];
@@ -171,17 +180,34 @@ __device__ __forceinline__ GenPos gen_pos(const Geo& g, int id) {
     return t;
 }
 
-// fill the staged tile: f(site index, u[3])
-template <class TL, class F>
-__device__ __forceinline__ void stage_gen(TL& L, const Geo& g, const GenPos& t, F&& f) {
+// Fill the staged tile: ld(site index, raw[NR]) reads, mk(raw, u[3]) makes the
+// staged vector.  A thread's sites are read 10 at a time, all loads in flight
+// (KEEP).
+template <class TL, int NR, class LD, class MK>
+__device__ __forceinline__ void stage_gen(TL& L, const Geo& g, const GenPos& t, LD&& ld, MK&& mk) {
     using T = std::remove_reference_t<decltype(L.u[0][0][0])>;
-#pragma unroll 4
-    for (int i = threadIdx.x; i < TL::LX * TL::LY; i += TL::NTH) {
-        const int ly = i / TL::LX, lx = i - ly * TL::LX;
-        T u[3];
-        f(wrap1(t.tx0 + lx - TL::RX, g.Lx) + g.Lx * wrap1(t.ty0 + ly - TL::RY, g.Ly), u);
+    constexpr int SITES = TL::LX * TL::LY, PER = (SITES + TL::NTH - 1) / TL::NTH;
+    constexpr int U = PER < 10 ? PER : 10;
+#pragma unroll 1
+    for (int i0 = threadIdx.x; i0 < SITES; i0 += U * TL::NTH) {
+        T raw[U][NR];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) L.u[d][ly][lx] = u[d];
+        for (int q = 0; q < U; ++q) {
+            const int i = min(i0 + q * TL::NTH, SITES - 1);
+            const int ly = i / TL::LX, lx = i - ly * TL::LX;
+            ld(wrap1(t.tx0 + lx - TL::RX, g.Lx) + g.Lx * wrap1(t.ty0 + ly - TL::RY, g.Ly), raw[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int i = i0 + q * TL::NTH;
+            const int ly = i / TL::LX, lx = i - ly * TL::LX;
+            T u[3];
+            mk(raw[q], u);
+            if (i < SITES) {
+#pragma unroll
+                for (int d = 0; d < 3; ++d) L.u[d][ly][lx] = u[d];
+            }
+        }
     }
 }
 
@@ -232,6 +258,46 @@ __device__ __forceinline__ void shell_field(const TL& L, int lx0, int ly0, int n
     }
 }
 
+// Output site q of a thread: consecutive lanes on consecutive sites of a row, for
+// the global loads and stores.
+template <class TL>
+struct GenSite {
+    int x, y;
+    __device__ __forceinline__ GenSite(int q) {
+        const int i = threadIdx.x + q * TL::NTH;
+        x = i % TL::HX;
+        y = i / TL::HX;
+    }
+};
+
+// Staged vector and field of the thread's output sites.  disc_field gives a thread
+// HSP consecutive sites of a row; they change hands through the tile (spent by
+// then), since stores 32 bytes apart touch eight times the cache lines: KEEP
+template <class T, int NS, class TL>
+__device__ __forceinline__ void site_fields(TL& L, const GenCoef<T, NS>& k, T (&u)[TL::HSP][3], T (&a)[TL::HSP][3]) {
+    static_assert(TL::HX * TL::HY == TL::HSP * TL::NTH, "every thread has HSP output sites");
+#pragma unroll
+    for (int q = 0; q < TL::HSP; ++q) {
+        const GenSite<TL> o(q);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) u[q][d] = L.u[d][o.y + TL::RY][o.x + TL::RX];
+    }
+    const int lx0 = (threadIdx.x % TL::TPR) * TL::HSP, ly0 = threadIdx.x / TL::TPR;
+    disc_field<T, NS>(L, lx0, ly0, k, a);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < TL::HSP; ++q)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) L.u[d][ly0][lx0 + q] = a[q][d];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < TL::HSP; ++q) {
+        const GenSite<TL> o(q);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) a[q][d] = L.u[d][o.y][o.x];
+    }
+}
+
 // Energy, gradient, c, F of the general-shell Hamiltonian; part[tile] =
 // sum_i (1/2 m_i.(A m)_i - B.m_i).
 template <class T, int NS, class TL>
@@ -244,27 +310,34 @@ __global__ __launch_bounds__(TL::NTH) void k_energy_grad_gen(Geo g, int ns, GenC
     const GenPos t = gen_pos<TL>(g, blockIdx.x);
     const size_t N = g.N;
     const T* mb = m + (size_t)t.b * 3 * N;
-    stage_gen(L, g, t, [&](int s, T(&u)[3]) {
+    stage_gen<TL, 3>(
+        L, g, t,
+        [&](int s, T(&r)[3]) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) u[d] = mb[d * N + s];
-    });
+            for (int d = 0; d < 3; ++d) r[d] = mb[d * N + s];
+        },
+        [](const T(&r)[3], T(&u)[3]) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) u[d] = r[d];
+        });
     __syncthreads();
-    const int lx0 = (threadIdx.x % TL::TPR) * TL::HSP, ly0 = threadIdx.x / TL::TPR;
-    const int y = t.ty0 + ly0;
-    T a[TL::HSP][3];
-    if constexpr (TL::HSP == 1)
-        shell_field<T, NS>(L, lx0, ly0, ns, k, a[0]);
-    else
-        disc_field<T, NS>(L, lx0, ly0, k, a);
+    T mv[TL::HSP][3], a[TL::HSP][3];
+    if constexpr (TL::HSP == 1) {
+        const GenSite<TL> o(0);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) mv[0][d] = L.u[d][o.y + TL::RY][o.x + TL::RX];
+        shell_field<T, NS>(L, o.x, o.y, ns, k, a[0]);
+    } else {
+        site_fields<T, NS>(L, k, mv, a);
+    }
     double v = 0.0;
 #pragma unroll
     for (int q = 0; q < TL::HSP; ++q) {
-        const int x = t.tx0 + lx0 + q;
+        const GenSite<TL> o(q);
+        const int x = t.tx0 + o.x, y = t.ty0 + o.y;
         if (x >= g.Lx || y >= g.Ly) continue;
         const size_t s = x + (size_t)g.Lx * y, s1 = (size_t)t.b * N + s, s3 = (size_t)t.b * 3 * N + s;
-        T mi[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) mi[d] = L.u[d][ly0 + TL::RY][lx0 + TL::RX + q];
+        const T(&mi)[3] = mv[q];
         const T ai[3] = {a[q][0], a[q][1], a[q][2] + k.cK * mi[2]};
         const T gi[3] = {ai[0] - k.B[0], ai[1] - k.B[1], ai[2] - k.B[2]};
         const T ci = mi[0] * gi[0] + mi[1] * gi[1] + mi[2] * gi[2];
@@ -303,42 +376,48 @@ __global__ __launch_bounds__(TL::NTH) void k_tangent_hvp_gen(Geo g, GenCoef<T, N
                                                              T* __restrict__ W, DoneFlags done) {
     constexpr int DV = FRAME ? 2 : 3;
     __shared__ __align__(16) TL L;
-    const int j = blockIdx.x % nvec;
-    const GenPos t = gen_pos<TL>(g, blockIdx.x / nvec);
+    const int id = xcd_order(true), j = id % nvec;
+    const GenPos t = gen_pos<TL>(g, id / nvec);
     if (done(t.b)) return;
     const size_t N = g.N;
     const T* mb = m + (size_t)t.b * 3 * N;
     const uint8_t* mk = mask ? mask + (size_t)t.b * N : nullptr;
     const T* vj = V + (size_t)t.b * vbs + (size_t)j * DV * N;
     T* wj = W + (size_t)t.b * vbs + (size_t)j * DV * N;
-    stage_gen(L, g, t, [&](int s, T(&u)[3]) {
-        const bool on = mk == nullptr || mk[s] != 0;
-        if constexpr (FRAME) {
-            T f1[3], f2[3];
-            onb(mb[s], mb[N + s], mb[2 * N + s], f1, f2);
-            const T a = on ? vj[s] : T(0);
-            const T bb = on ? vj[N + s] : T(0);
+    constexpr int NR = FRAME ? 5 : 3;  // coordinates, then the spin of the frame
+    stage_gen<TL, NR>(
+        L, g, t,
+        [&](int s, T(&r)[NR]) {
+            const bool on = mk == nullptr || mk[s] != 0;
 #pragma unroll
-            for (int d = 0; d < 3; ++d) u[d] = a * f1[d] + bb * f2[d];
-        } else {
+            for (int d = 0; d < DV; ++d) r[d] = on ? vj[d * N + s] : T(0);
+            if constexpr (FRAME) {
 #pragma unroll
-            for (int d = 0; d < 3; ++d) u[d] = on ? vj[d * N + s] : T(0);
-        }
-    });
+                for (int d = 0; d < 3; ++d) r[2 + d] = mb[d * N + s];
+            }
+        },
+        [](const T(&r)[NR], T(&u)[3]) {
+            if constexpr (FRAME) {
+                T f1[3], f2[3];
+                onb(r[2], r[3], r[4], f1, f2);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) u[d] = fma(r[0], f1[d], r[1] * f2[d]);
+            } else {
+#pragma unroll
+                for (int d = 0; d < 3; ++d) u[d] = r[d];
+            }
+        });
     __syncthreads();
-    const int lx0 = (threadIdx.x % TL::TPR) * TL::HSP, ly0 = threadIdx.x / TL::TPR;
-    const int y = t.ty0 + ly0;
-    T a[TL::HSP][3];
-    disc_field<T, NS>(L, lx0, ly0, k, a);
+    T us[TL::HSP][3], a[TL::HSP][3];
+    site_fields<T, NS>(L, k, us, a);
 #pragma unroll
     for (int q = 0; q < TL::HSP; ++q) {
-        const int x = t.tx0 + lx0 + q;
+        const GenSite<TL> o(q);
+        const int x = t.tx0 + o.x, y = t.ty0 + o.y;
         if (x >= g.Lx || y >= g.Ly) continue;
         const size_t so = x + (size_t)g.Lx * y;
         const bool on = mk == nullptr || mk[so] != 0;
-        T u[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) u[d] = L.u[d][ly0 + TL::RY][lx0 + TL::RX + q];
+        const T(&u)[3] = us[q];
         const T ci = c[(size_t)t.b * N + so];
         const T m0 = mb[so], m1 = mb[N + so], m2 = mb[2 * N + so];
         const T a0 = a[q][0], a1 = a[q][1], a2 = a[q][2] + k.cK * u[2];
