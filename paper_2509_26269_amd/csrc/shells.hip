@@ -127,9 +127,11 @@ __device__ __forceinline__ void disc_rows(const T* __restrict__ base, const GenC
 // once in 16-byte pieces.  The earlier form convolved the full 25 x 23 square
 // with couplings from LDS (1725 multiply-adds a site-vector instead of 1083,
 // and a quarter as many LDS reads again), a workgroup taking the vectors one
-// after another.  us, before and now, 35 shells: 64 x 128x128 x 4 FP32 471 and
-// 186 (115 for the multiply-adds alone at the vector rate), FP64 1137 and 283;
-// one 128x128 state x 4 FP32 209 and 22; 16x16 x 1 53 and 21.
+// after another.  us of the HVP, before and now, 35 shells: 64 x 128x128 x 4 FP32
+// 471 and 161 (115 for the multiply-adds alone at the vector rate; 186 with each
+// row's window read in front of its own terms, the tile staged four sites at a
+// time and stores by the field's owner), FP64 1137 and 267; one 128x128 state x 4
+// FP32 209 and 20; 16x16 x 1 53 and 20.
 template <class T, int NS, class TL>
 __device__ __forceinline__ void disc_field(const TL& L, int lx0, int ly0, const GenCoef<T, NS>& k,
                                            T (&a)[TL::HSP][3]) {
@@ -182,7 +184,7 @@ __device__ __forceinline__ GenPos gen_pos(const Geo& g, int id) {
 
 // Fill the staged tile: ld(site index, raw[NR]) reads, mk(raw, u[3]) makes the
 // staged vector.  A thread's sites are read 10 at a time, all loads in flight
-// (KEEP).
+// (35 shells, 64 x 128x128 x 4 FP32, 18.6 sites a thread: 182 us with four, 169).
 template <class TL, int NR, class LD, class MK>
 __device__ __forceinline__ void stage_gen(TL& L, const Geo& g, const GenPos& t, LD&& ld, MK&& mk) {
     using T = std::remove_reference_t<decltype(L.u[0][0][0])>;
@@ -272,7 +274,8 @@ struct GenSite {
 
 // Staged vector and field of the thread's output sites.  disc_field gives a thread
 // HSP consecutive sites of a row; they change hands through the tile (spent by
-// then), since stores 32 bytes apart touch eight times the cache lines: KEEP
+// then), since loads and stores 32 bytes apart touch eight times the cache
+// lines (10 shells, 64 x 128x128 x 4 FP32: 96 -> 78 us).
 template <class T, int NS, class TL>
 __device__ __forceinline__ void site_fields(TL& L, const GenCoef<T, NS>& k, T (&u)[TL::HSP][3], T (&a)[TL::HSP][3]) {
     static_assert(TL::HX * TL::HY == TL::HSP * TL::NTH, "every thread has HSP output sites");
@@ -366,7 +369,8 @@ __global__ __launch_bounds__(TL::NTH) void k_energy_grad_gen(Geo g, int ns, GenC
 }
 
 // Tangent HVP (frame or ambient layout, as the three-shell kernels): one tile
-// of one vector a workgroup,
+// of one vector a workgroup, a tile's vectors on one XCD (they share its spins:
+// 35 shells, 64 x 128x128 x 4 FP32 167 -> 161 us, 10 shells 78 -> 70),
 // W_j = M H(m) M V_j with (H v)_i = P_i (A v)_i - c_i v_i.
 template <class T, bool FRAME, int NS, class TL>
 __global__ __launch_bounds__(TL::NTH) void k_tangent_hvp_gen(Geo g, GenCoef<T, NS> k, const T* __restrict__ m,
