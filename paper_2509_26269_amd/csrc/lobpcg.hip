@@ -18,7 +18,9 @@
 // fixed-order reduction) -> Rayleigh-Ritz (tridiagonal QL) -> block update
 // X, P, HX, HP, W = HX - X Lam -> convergence control.  Every kernel returns
 // at once when the control block says the solve is done, so chunks of
-// iterations can be queued without host round trips.
+// iterations can be queued without host round trips.  Blocks of up to four
+// columns (k = 1 and 2) are latency: they take fused forms of the same sums, eight
+// launches an iteration, the control inside the next iteration's first.
 //
 // Populations: every kernel takes blockIdx.y as the member of a population
 // of independent solves on lattices of one geometry (EigArgs::P, strides
@@ -603,13 +605,13 @@ __global__ __launch_bounds__(SORTH_WAVES * WL) void k_orth_small_narrow(EigArgs 
     orth_settle(target, orth_small_body<SCOL + 1, true>(a.mb, nq, a.drop, Gl, ctrl->Bw, ctrl->Tw), ctrl);
 }
 
-// Row transform on the vector ALUs.  MB: compile-time
-// bound on the block width (mb <= MB), so that the per-row register arrays are
-// sized for the actual block and never spill.  EX: the block has exactly MB
-// columns and the basis all 3 MB (every iteration but the first), so that no
-// run-time test stands between the LDS reads of the coefficients: with one
-// there, each read waited out its latency (k_update at 64x64, k = 2 FP64: 11
-// us for 32 workgroups of one row a thread).
+// Row transform on the vector ALUs (the start block, the second pass over W, and
+// every pass of the FP64 blocks of 5 and more columns).  MB: compile-time bound on
+// the block width (mb <= MB), so that the per-row register arrays are sized for the
+// actual block and never spill.  EX: the block has exactly MB columns and the basis
+// all 3 MB (every iteration but the first), so that no run-time test stands between
+// the LDS reads of the coefficients: with one there, each read waited out its
+// latency (64x64, k = 2 FP64: 4.5 -> 4.2 us a call, the first pass included).
 template <class T, int MB, bool MSK, bool EX>
 __device__ __forceinline__ void orth_apply_rows(const EigArgs& a, const OrthCols& oc, const double* B,
                                                 const double* Tw, T* __restrict__ S) {
