@@ -214,11 +214,15 @@ __device__ __forceinline__ void stage_gen(TL& L, const Geo& g, const GenPos& t, 
 }
 
 // Field (A u) at one site of a staged tile, shell by shell: the members of a
-// shell are added first, then scaled by its coupling.  The FP32 energies keep
-// this order (a third of the rounding error of disc_field's running sum, which
-// shows in an FP64 energy), unrolled so that every neighbour is an LDS read at
-// an immediate offset; shells beyond the plan's are skipped.  64 x 128x128, 35
-// shells: 163 us with the offsets from a table, 86 now.
+// shell are added first, then scaled by its coupling.  The energies of both
+// precisions keep this order: disc_field's running sum over up to 360 bonds has
+// 2.1 times its rms error (35 shells, against 80-bit sums), in FP32 enough to
+// show in an FP64 energy, and its zero couplings carry a non-finite spin beyond
+// the plan's shells.  It is unrolled, so that every neighbour is an LDS read at
+// an immediate offset; shells beyond the plan's are skipped.  us of the energy
+// and gradient, 35 shells, with the offsets from a table, through disc_field and
+// now: 64 x 128x128 FP32 158, -, 77, FP64 298, 68, 133; 512 x 16x16 FP64 102, 60,
+// 39 (disc_field's 64 x 32 tiles mostly empty).
 template <class T, int NS, class TL, int S, int... I>
 __device__ __forceinline__ void shell_add(std::integer_sequence<int, I...>, const TL& L, int y, int x,
                                           const GenCoef<T, NS>& k, T (&a)[3]) {
@@ -301,13 +305,17 @@ __device__ __forceinline__ void site_fields(TL& L, const GenCoef<T, NS>& k, T (&
     }
 }
 
-// Energy, gradient, c, F of the general-shell Hamiltonian; part[tile] =
-// sum_i (1/2 m_i.(A m)_i - B.m_i).
-template <class T, int NS, class TL>
-__global__ __launch_bounds__(TL::NTH) void k_energy_grad_gen(Geo g, int ns, GenCoef<T, NS> k, const T* __restrict__ m,
-                                                             const uint8_t* __restrict__ mask, T* __restrict__ grad,
-                                                             T* __restrict__ cout, T* __restrict__ F,
-                                                             double* __restrict__ part) {
+// Energy, gradient, c, F of the general-shell Hamiltonian, a site a thread;
+// part[tile] = sum_i (1/2 m_i.(A m)_i - B.m_i).
+template <class T, int NS>
+using EnergyTile = GenTile<T, NS, 32, 16, 1>;
+template <class T, int NS>
+__global__ __launch_bounds__(512) void k_energy_grad_gen(Geo g, int ns, GenCoef<T, NS> k, const T* __restrict__ m,
+                                                         const uint8_t* __restrict__ mask, T* __restrict__ grad,
+                                                         T* __restrict__ cout, T* __restrict__ F,
+                                                         double* __restrict__ part) {
+    using TL = EnergyTile<T, NS>;
+    static_assert(TL::NTH == 512, "a site a thread");
     __shared__ __align__(16) TL L;
     __shared__ double red[TL::NTH / 64];
     const GenPos t = gen_pos<TL>(g, blockIdx.x);
@@ -324,24 +332,16 @@ __global__ __launch_bounds__(TL::NTH) void k_energy_grad_gen(Geo g, int ns, GenC
             for (int d = 0; d < 3; ++d) u[d] = r[d];
         });
     __syncthreads();
-    T mv[TL::HSP][3], a[TL::HSP][3];
-    if constexpr (TL::HSP == 1) {
-        const GenSite<TL> o(0);
+    const GenSite<TL> o(0);
+    const int x = t.tx0 + o.x, y = t.ty0 + o.y;
+    T mi[3], ai[3];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) mv[0][d] = L.u[d][o.y + TL::RY][o.x + TL::RX];
-        shell_field<T, NS>(L, o.x, o.y, ns, k, a[0]);
-    } else {
-        site_fields<T, NS>(L, k, mv, a);
-    }
+    for (int d = 0; d < 3; ++d) mi[d] = L.u[d][o.y + TL::RY][o.x + TL::RX];
+    shell_field<T, NS>(L, o.x, o.y, ns, k, ai);
     double v = 0.0;
-#pragma unroll
-    for (int q = 0; q < TL::HSP; ++q) {
-        const GenSite<TL> o(q);
-        const int x = t.tx0 + o.x, y = t.ty0 + o.y;
-        if (x >= g.Lx || y >= g.Ly) continue;
+    if (x < g.Lx && y < g.Ly) {
         const size_t s = x + (size_t)g.Lx * y, s1 = (size_t)t.b * N + s, s3 = (size_t)t.b * 3 * N + s;
-        const T(&mi)[3] = mv[q];
-        const T ai[3] = {a[q][0], a[q][1], a[q][2] + k.cK * mi[2]};
+        ai[2] += k.cK * mi[2];
         const T gi[3] = {ai[0] - k.B[0], ai[1] - k.B[1], ai[2] - k.B[2]};
         const T ci = mi[0] * gi[0] + mi[1] * gi[1] + mi[2] * gi[2];
         if (grad) {
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(TL::NTH) void k_energy_grad_gen(Geo g, int ns, GenC
         }
         const double mam = (double)mi[0] * ai[0] + (double)mi[1] * ai[1] + (double)mi[2] * ai[2];
         const double bm = (double)k.B[0] * mi[0] + (double)k.B[1] * mi[1] + (double)k.B[2] * mi[2];
-        v += 0.5 * mam - bm;
+        v = 0.5 * mam - bm;
     }
     v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
@@ -487,22 +487,21 @@ hipError_t launch_energy_grad_gen(const Geo& g, const CoefD& kd, bool f64, int b
                                   const uint8_t* mask, void* grad, void* c, void* F, double* part, int* tiles,
                                   hipStream_t st) {
     if (!kd.gen || kd.gen->ns > GEN_MAX_SHELLS) return hipErrorInvalidValue;
-    auto launch = [&](auto& k, auto nsc, auto tl) {
-        using TL = std::remove_pointer_t<decltype(tl)>;
-        using T = std::remove_reference_t<decltype(k.cD)>;
-        const long long n = gen_tiles<TL>(g);
-        *tiles = (int)n;
-        hipLaunchKernelGGL((k_energy_grad_gen<T, decltype(nsc)::value, TL>), dim3((unsigned)(batch * n)),
-                           dim3(TL::NTH), 0, st, g, kd.gen->ns, k, (const T*)m, mask, (T*)grad, (T*)c, (T*)F, part);
+    auto go = [&](auto tc) {
+        using T = decltype(tc);
+        with_disc<T>(kd, [&](auto& k, auto nsc) {
+            constexpr int NS = decltype(nsc)::value;
+            using TL = EnergyTile<T, NS>;
+            const long long n = gen_tiles<TL>(g);
+            *tiles = (int)n;
+            hipLaunchKernelGGL((k_energy_grad_gen<T, NS>), dim3((unsigned)(batch * n)), dim3(TL::NTH), 0, st, g,
+                               kd.gen->ns, k, (const T*)m, mask, (T*)grad, (T*)c, (T*)F, part);
+        });
     };
     if (f64)
-        with_disc<double>(kd, [&](auto& k, auto nsc) {
-            with_tile<double, decltype(nsc)::value>(g, batch, [&](auto tl) { launch(k, nsc, tl); });
-        });
+        go(double(0));
     else
-        with_disc<float>(kd, [&](auto& k, auto nsc) {
-            launch(k, nsc, (GenTile<float, decltype(nsc)::value, 32, 16, 1>*)nullptr);
-        });
+        go(float(0));
     return hipGetLastError();
 }
 
