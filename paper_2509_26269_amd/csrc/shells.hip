@@ -44,12 +44,17 @@ constexpr DiscRows make_disc(int ns) {
 }
 template <int NS>
 inline constexpr DiscRows kDisc = make_disc(NS);
+// fewest shells of a plan that takes the disc of NS
+template <int NS>
+inline constexpr int kDiscMin = NS == 10 ? 4 : NS == 20 ? 11 : 21;
 
-// couplings (cJ zero beyond the plan's shells), in scalar registers
+// couplings (cJ zero beyond the plan's shells) and the rows that the plan's
+// bonds reach, in scalar registers
 template <class T, int NS>
 struct GenCoef {
     T cJ[NS];
     T cD, cK, B[3];
+    int R;
 };
 
 // HX x HY output sites a workgroup, HSP consecutive ones of a row a thread
@@ -96,19 +101,29 @@ struct DiscRow {
                                                  const GenCoef<T, NS>& k, T (&acc)[TL::HSP]) {
         (term<I>(win, k, acc), ...);
     }
-    // the row's terms, with the next row's window on its way
+    // the row's terms unless no bond of the plan lies in it (a zero coupling
+    // would carry a non-finite value there)
+    static __device__ __forceinline__ void row(const T (&win)[WN], const GenCoef<T, NS>& k, T (&acc)[TL::HSP]) {
+        constexpr auto dxs = std::make_integer_sequence<int, HI - LO + 1>{};
+        constexpr int Y = DY < 0 ? -DY : DY;
+        if constexpr (Y > kDisc<kDiscMin<NS>>.R) {
+            if (Y <= k.R) terms(dxs, win, k, acc);
+        } else {
+            terms(dxs, win, k, acc);
+        }
+    }
+    // rows DY and on, each with the next one's window on its way
     static __device__ __forceinline__ void run(const T* __restrict__ base, const T (&win)[WN],
                                                const GenCoef<T, NS>& k, T (&acc)[TL::HSP]) {
-        constexpr auto dxs = std::make_integer_sequence<int, HI - LO + 1>{};
         if constexpr (DY < TL::RY) {
             using Next = DiscRow<T, NS, TL, DY + 1>;
             T nxt[Next::WN];
             Next::load(base + (DY + 1 + TL::RY) * TL::LS, nxt);
-            terms(dxs, win, k, acc);
+            row(win, k, acc);
             __builtin_amdgcn_sched_barrier(0);  // two windows live
             Next::run(base, nxt, k, acc);
         } else {
-            terms(dxs, win, k, acc);
+            row(win, k, acc);
         }
     }
 };
@@ -460,6 +475,7 @@ static void with_disc(const CoefD& kd, F&& f) {
         k.cD = (T)kd.cD;
         k.cK = (T)kd.cK;
         for (int d = 0; d < 3; ++d) k.B[d] = (T)kd.B[d];
+        k.R = kd.gen->R;
         f(k, nsc);
     };
     if (kd.gen->ns <= 10)

@@ -1,5 +1,5 @@
-"""Energies on more than three shells: how exact the field is, and what a
-non-finite spin reaches."""
+"""More than three shells: how exact the field of the energies is, and what a
+non-finite spin or vector reaches."""
 import numpy as np
 import pytest
 
@@ -80,3 +80,31 @@ def test_bad_spin_reaches_its_shells_only(ns, dt, bad):
         want[(y0 - dy) % L, (x0 - dx) % L] = True
     want[y0, x0] = touched[y0, x0]  # its own field holds the anisotropy only
     assert (touched == want).all()
+
+
+@pytest.mark.parametrize("ns", [4, 7, 10, 11, 13, 21, 30, 36])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("layout", [0, 1])
+def test_bad_vector_stays_in_the_rows_of_its_bonds(ns, dt, layout):
+    """The HVP convolves whole rows of a disc that may hold more shells than the
+    plan: a non-finite entry may reach further along a row, by 12 sites at
+    most, but no row without a bond."""
+    from paper_2509_26269_amd import moto as M
+
+    L = 64
+    p = _params(L, L, ns)
+    plan = M.Plan.from_params(p)
+    tdt = torch.float64 if dt == "f64" else torch.float32
+    md = torch.as_tensor(S.random_texture(L * L, np.random.default_rng(ns)), device="cuda").to(tdt)[None].contiguous()
+    c = M.moto_energy_grad(plan, md)[2]
+    V = torch.zeros(1, 1, 3 - layout, L * L, dtype=tdt, device="cuda")
+    x0, y0 = 30, 31
+    V[0, 0, :, x0 + L * y0] = float("nan")
+    W = M.moto_tangent_hvp(plan, md, c, V, layout)
+    touched = ~torch.isfinite(W[0, 0]).all(0).cpu().numpy().reshape(L, L)
+    bonds = [(dx, dy) for dx, dy, _ in O.shells(ns)]
+    for dx, dy in bonds:
+        assert touched[y0 - dy, x0 - dx]
+    reach = max(abs(dy) for _, dy in bonds)
+    ys, xs = np.nonzero(touched)
+    assert np.abs(ys - y0).max() <= reach and np.abs(xs - x0).max() <= 12
