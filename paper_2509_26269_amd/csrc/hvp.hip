@@ -915,8 +915,10 @@ __global__ __launch_bounds__(NT2) void k_hvp_march2(Geo g, Coef<T> k, const T* _
 //   in FP32, 7e-8 against 1.1e-7).
 //   FRAME: as the march.  Otherwise the ambient layout: u is read as it is
 //   and the output is a - m (m.a) - c u with a = A u.
+//   FP32 in the march's order is held to 64 VGPRs (eight waves a SIMD): the
+//   scheduler may take 73 for the same code, 10 % slower.
 template <class T, bool FRAME, bool MORDER, bool MASKED>
-__global__ __launch_bounds__(NT) void k_hvp_gather(Geo g, Coef<T> k, const T* __restrict__ m,
+__global__ __launch_bounds__(NT, MORDER && sizeof(T) == 4 ? 8 : 1) void k_hvp_gather(Geo g, Coef<T> k, const T* __restrict__ m,
                                                    const T* __restrict__ c, const uint8_t* __restrict__ mask, int nvec,
                                                    long long vbs, const T* __restrict__ V, T* __restrict__ W,
                                                    DoneFlags done, int tiles_x, int tiles_y, int nvg,
@@ -926,7 +928,7 @@ __global__ __launch_bounds__(NT) void k_hvp_gather(Geo g, Coef<T> k, const T* __
     constexpr int SX = TX + 2 * HALO, SS = SX * (TY + 2 * HALO);
     constexpr int Q = (SS + NT - 1) / NT;  // staged sites per thread
     __shared__ T su[3][SS];
-    const int lid = xcd_order(true);
+    const int lid = FRAME ? xcd_runs() : xcd_order(true);
     const int grp = lid % ngroups;
     const int rest = lid / ngroups;
     const int tiles = tiles_x * tiles_y;
