@@ -1103,26 +1103,39 @@ static int march_strips(const Geo& g, int batch, int ngroups, int target) {
     return max(1, min(want, max(1, g.Ly / 8)));
 }
 
+// Three FP32 vectors as groups of one are 3 batch strips workgroups, each with the
+// march's start-up and length: slower than one group of four when a round of them
+// is left over to few (us, one by one / together: 493 masked 100x100 129 / 106,
+// 1479 workgroups of 100 rows on 1024 places; 8 x 512x512 48 / 39, 264 workgroups
+// on 256 places that the other fits) and faster else (14 x 512x512 75 / 114;
+// 2550 x 80x80 290 / 368).
+static bool march_singles_leave_a_tail(const Geo& g, int batch, int cols) {
+    const int target = cols > 256 ? 256 : 1024;
+    const int s1 = march_strips(g, batch, 3, target), s4 = march_strips(g, batch, 1, target);
+    const long long w1 = 3LL * batch * s1, w4 = (long long)batch * s4;
+    if (cols > 256) return w1 > target && w4 <= target;
+    return w1 > target && 2 * w1 < 3 * target && g.Ly >= 64 * s1;
+}
+
 // The choice without an autotuned or pinned variant: the gather while latency
 // counts and where the march cannot go or idles lanes, then the march.
 // The march's group is the one that wastes fewest slots (8.4 M site-vectors of
-// one vector a lattice, FP32, march/1vec / 2vec / 4vec: 60 / 70 / 113 us; three
-// vectors, 14.7 M: 68 / 81 / 79; two, 16.8 M: 115 / 79 / 121; four, 67 M: - /
-// 280 / 266).  Both sides' times are estimated as a start-up plus a rate times
-// the site-vectors that each really works on: whole tiles for the gather,
-// whole rows of threads and the strips' four halo rows for the march.  The
-// rates are fitted to 170 shapes from 12x12 to 1100x1100 (5 - 15 % off for
-// most; the gather must win by a margin), and some of those read (us: gather /
-// march):
-//   FP32  0.4 M site-vectors (24 x 93x61 x 3) 6.5 / 9.5;  1.6 M (24 x 128x128 x 4) 12.5 / 20.6;
-//         4.2 M (64 x 128x128 x 4) 24.7 / 24.5;   16.8 M (256 x 128x128 x 4) 117 / 75;
-//         8.6 M (24 x 300x300 x 4) 47 / 101;      3.5 M (319 x 126x86 x 1) 45 / 28
-//   FP64  0.4 M 8.9 / 18.2;  1.6 M 20.0 / 19.8;  4.2 M 44 / 42;  2.2 M (6 x 300x300 x 4) 26 / 52;
-//         1.4 M (195 x 60x12 x 10) 27 / 20;  6.4 M (404 x 181x88 x 1) 125 / 83
-static int hvp_default_variant(const Geo& g, bool f64, int batch, int nvec) {
+// one vector a lattice, FP32, march/1vec / 2vec / 4vec: 60 / 70 / 113 us; two,
+// 16.8 M: 115 / 79 / 121; four, 67 M: - / 280 / 266; three: see above).  Both
+// sides' times are estimated as a start-up plus a rate times the site-vectors that
+// each really works on: whole tiles for the gather, whole rows of threads and the
+// strips' four halo rows for the march.  The rates are fitted to shapes from 12x12
+// to 1100x1100 and 5 - 15 % off for most, so the gather must win by a margin:
+// a larger one for FP64 launches whose vectors (32 bytes a site) outgrow the 256 MB
+// cache, where the 1.7 reads of a staged site go to HBM (66 x 160x160 x 10: 214 us
+// against the march's 193).  Over 2600 shapes the choice takes 0.63 of the time
+// of the form that all calls took before it (four FP32 vectors a group, two of
+// FP64); 35 are more than 3 % slower than that form, 3 more than 10 %.
+static int hvp_default_variant(const Geo& g, bool f64, int batch, bool masked, int nvec) {
     if (!march_fits(g)) return 13;
     const int cols = g.Lx <= 64 ? 64 : g.Lx <= 128 ? 128 : g.Lx <= 256 ? 256 : 512;
-    const bool by1 = nvec == 1 || (nvec == 3 && !f64 && cols > 64);
+    const bool by1 =
+        nvec == 1 || (nvec == 3 && !f64 && cols > 64 && !march_singles_leave_a_tail(g, batch, cols));
     const int nvp = by1 ? 1 : f64 || nvec % 4 == 1 || nvec % 4 == 2 ? 2 : 4;
     const int groups = (nvec + nvp - 1) / nvp;
     const int strips = march_strips(g, batch, groups, cols > 256 ? 256 : 1024);
@@ -1138,7 +1151,8 @@ static int hvp_default_variant(const Geo& g, bool f64, int batch, int nvec) {
     else
         tm = nvp == 1 ? 5.0 + (cols == 64 ? 11.0 : nvec == 1 ? 5.5 : 4.4) * mm : nvp == 2 ? 8.0 + 4.0 * mm
                                                                : 14.0 + (cols > 256 ? 3.2 : 2.6) * mm;
-    if ((nvp == 4 ? 1.15 : 1.1) * tg < tm) return 12;
+    const double margin = f64 && !masked && mg > 8.0 ? 1.2 : nvp == 4 ? 1.15 : 1.1;
+    if (margin * tg < tm) return 12;
     return nvp == 1 ? 9 : nvp == 2 ? 8 : 7;
 }
 
@@ -1259,7 +1273,7 @@ static void go(int v, const Geo& g, const CoefD& kd, int batch, const void* m, c
 hipError_t launch_hvp_frame(int variant, const Geo& g, const CoefD& kd, bool f64, int batch, const void* m,
                             const void* c, const uint8_t* mask, int nvec, const void* V, void* W, DoneFlags done,
                             hipStream_t st, long long vbs) {
-    const int v = hvp_variant_ok(variant, g, f64) ? variant : hvp_default_variant(g, f64, batch, nvec);
+    const int v = hvp_variant_ok(variant, g, f64) ? variant : hvp_default_variant(g, f64, batch, mask != nullptr, nvec);
     if (vbs <= 0) vbs = (long long)nvec * 2 * g.N;
     if (f64)
         go<double>(v, g, kd, batch, m, c, mask, nvec, vbs, V, W, done, st);
