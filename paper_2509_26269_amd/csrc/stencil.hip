@@ -182,12 +182,19 @@ __global__ __launch_bounds__(ONE_WG_TILES * NT) void k_energy_grad_wg(Geo g, Coe
             if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = s;
         }
         __syncthreads();
+        // added as the two launches do it: a tile's waves one after another, then
+        // the butterfly over the tiles
         if (threadIdx.x == 0) {
 #pragma unroll
             for (int q = 0; q < NP; ++q) {
-                double s = 0.0;
-                for (int i = 0; i < (int)blockDim.x / 64; ++i) s += red[i][q];
-                v[q] = s;
+                double ts[ONE_WG_TILES];
+#pragma unroll
+                for (int i = 0; i < ONE_WG_TILES; ++i) {
+                    ts[i] = 0.0;
+                    if (i < g.tiles)
+                        for (int u = 0; u < NT / 64; ++u) ts[i] += red[i * (NT / 64) + u][q];
+                }
+                v[q] = (ts[0] + ts[2]) + (ts[1] + ts[3]);
             }
             store_sums<NV>(v, b, ns, E, dth);
         }
