@@ -150,8 +150,14 @@ __global__ __launch_bounds__(NT) void k_energy_grad(Geo g, Coef<T> k, const T* _
 
 // One lattice per workgroup, NT threads for each of its (at most four) tiles:
 // the sums stay in the workgroup, so a small lattice is one launch instead of
-// two (the second costs the host and the stream about 2 us each).
+// two (the second costs the host and the stream about 2 us each).  Three and four
+// tiles in large batches take the two launches all the same: with workgroups of
+// 768 and 1024 threads few are at hand for a unit that waits, and the LDS of four
+// tiles is held by all (us of one launch / two, the energies alone, FP64, 32x32:
+// 1024 lattices 15.8 / 14.5, 4096 61 / 46; 512 8.8 / 10.8; one and two tiles gain
+// at any batch, 8192 x 64x8 44 / 49).  The results are the same bits.
 constexpr int ONE_WG_TILES = 4;
+constexpr int ONE_WG_BATCH_TILES = 4096;
 template <class T, int NP>
 __global__ __launch_bounds__(ONE_WG_TILES * NT) void k_energy_grad_wg(Geo g, Coef<T> k, const T* __restrict__ m,
                                                                       const uint8_t* __restrict__ mask,
@@ -391,7 +397,7 @@ template <class T, int NP>
 static void go_energy(const Geo& g, const CoefD& kd, int batch, const void* m, const uint8_t* mask, void* grad,
                       void* c, void* F, double* part, int ns, double* E, double* dth, hipStream_t st) {
     const Coef<T> k = coef_cast<T>(kd);
-    if (g.tiles <= ONE_WG_TILES) {
+    if (g.tiles <= 2 || (g.tiles <= ONE_WG_TILES && (long long)batch * g.tiles < ONE_WG_BATCH_TILES)) {
         hipLaunchKernelGGL((k_energy_grad_wg<T, NP>), dim3(batch), dim3(NT * g.tiles), 0, st, g, k, (const T*)m, mask,
                            (T*)grad, (T*)c, (T*)F, ns, E, dth);
         return;

@@ -48,3 +48,21 @@ def test_sums_in_the_order_of_the_two_launches(Lx, Ly, want_dtheta):
     assert np.array_equal(E.cpu().numpy(), want)
     if want_dtheta:
         assert np.array_equal(dth[:, -1].cpu().numpy(), want)
+
+
+# three and four tiles, one lattice below and at the batch that takes the two launches
+@pytest.mark.parametrize("Lx,Ly,B", [(32, 32, 1023), (32, 32, 1024), (32, 24, 1365), (32, 24, 1366), (64, 8, 2049)])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_batch_does_not_change_a_lattice(Lx, Ly, B, dt):
+    from paper_2509_26269_amd import moto as M
+
+    plan = M.Plan.from_params(S.ham_3shell(Lx, Ly))
+    g = torch.Generator(device="cuda").manual_seed(B)
+    m = torch.randn(B, 3, plan.N, generator=g, device="cuda", dtype=torch.float64)
+    m = (m / m.norm(dim=1, keepdim=True)).to(torch.float64 if dt == "f64" else torch.float32)
+    for dtheta in (False, True):
+        all_ = M.moto_energy_grad(plan, m, want_dtheta=dtheta)
+        for b in (0, B // 2, B - 1):
+            one = M.moto_energy_grad(plan, m[b : b + 1].contiguous(), want_dtheta=dtheta)
+            for x, y in zip(all_, one):
+                assert x is None or torch.equal(x[b : b + 1], y)
