@@ -337,10 +337,12 @@ moto_status moto_tangent_hvp_autotune(moto_plan p, moto_dtype dt, int32_t batch,
     for (int v = 0; v < HVP_NVARIANTS; ++v) {
         if (times_ms) times_ms[v] = -1.0f;
         if (!hvp_variant_ok(v, p->g, f64)) continue;
-        HIP_TRY(launch_hvp_frame(v, p->g, p->k, f64, batch, m, c, mask, n_vec, V, W, nullptr, st));  // warm-up
+        auto run = [&]() {
+            return launch_tangent_hvp(p->g, p->k, f64, true, batch, m, c, mask, n_vec, V, W, nullptr, st, v);
+        };
+        HIP_TRY(run());  // warm-up
         HIP_TRY(hipEventRecord(e0, st));
-        for (int r = 0; r < reps; ++r)
-            HIP_TRY(launch_hvp_frame(v, p->g, p->k, f64, batch, m, c, mask, n_vec, V, W, nullptr, st));
+        for (int r = 0; r < reps; ++r) HIP_TRY(run());
         HIP_TRY(hipEventRecord(e1, st));
         HIP_TRY(hipEventSynchronize(e1));
         float ms = 0.0f;

@@ -1231,7 +1231,8 @@ static void go_gather(const Geo& g, const CoefD& kd, int batch, const void* m, c
                       int nvec, long long vbs, const void* V, void* W, DoneFlags done, hipStream_t st) {
     const long long tiles = (long long)batch * g.tiles;
     const int want = (int)std::min(4LL, std::max(1LL, tiles * nvec / (sizeof(T) == 8 ? 512 : 1536)));
-    const int ngroups = (nvec + want - 1) / want;
+    const long long most = std::max(1LL, LAUNCH_THREADS / (NT * tiles));  // groups that a launch can have
+    const int ngroups = (int)std::min<long long>((nvec + want - 1) / want, most);
     const int nvg = (nvec + ngroups - 1) / ngroups;
     const dim3 grid((unsigned)(tiles * ngroups));
     auto launch = [&](auto mc) {

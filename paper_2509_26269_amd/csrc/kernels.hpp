@@ -102,6 +102,8 @@ hipError_t launch_param_grad_apply(const Geo& g, int ns, bool f64, int batch, co
 // per device with that device current); ENERGY_SCRATCH_BYTES long.
 constexpr size_t ENERGY_SCRATCH_BYTES = MOTO_NOALLOC_SCRATCH_BYTES;
 hipError_t energy_scratch(double** out);
+// A launch has fewer than 2^32 threads.
+constexpr long long LAUNCH_THREADS = 0xFFFFFFFFll;
 // Device flags that turn an HVP into a no-op, one per lattice `stride` ints
 // apart (stride 0: one for all); null: none.
 struct DoneFlags {

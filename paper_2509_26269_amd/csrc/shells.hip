@@ -325,7 +325,8 @@ __device__ __forceinline__ void site_fields(TL& L, const GenCoef<T, NS>& k, T (&
 template <class T, int NS>
 using EnergyTile = GenTile<T, NS, 32, 16, 1>;
 template <class T, int NS>
-__global__ __launch_bounds__(512) void k_energy_grad_gen(Geo g, int ns, GenCoef<T, NS> k, const T* __restrict__ m,
+__global__ __launch_bounds__(512) void k_energy_grad_gen(Geo g, int ns, int tile0, GenCoef<T, NS> k,
+                                                         const T* __restrict__ m,
                                                          const uint8_t* __restrict__ mask, T* __restrict__ grad,
                                                          T* __restrict__ cout, T* __restrict__ F,
                                                          double* __restrict__ part) {
@@ -333,7 +334,7 @@ __global__ __launch_bounds__(512) void k_energy_grad_gen(Geo g, int ns, GenCoef<
     static_assert(TL::NTH == 512, "a site a thread");
     __shared__ __align__(16) TL L;
     __shared__ double red[TL::NTH / 64];
-    const GenPos t = gen_pos<TL>(g, blockIdx.x);
+    const GenPos t = gen_pos<TL>(g, tile0 + blockIdx.x);
     const size_t N = g.N;
     const T* mb = m + (size_t)t.b * 3 * N;
     stage_gen<TL, 3>(
@@ -508,10 +509,12 @@ hipError_t launch_energy_grad_gen(const Geo& g, const CoefD& kd, bool f64, int b
         with_disc<T>(kd, [&](auto& k, auto nsc) {
             constexpr int NS = decltype(nsc)::value;
             using TL = EnergyTile<T, NS>;
-            const long long n = gen_tiles<TL>(g);
+            const long long n = gen_tiles<TL>(g), most = LAUNCH_THREADS / TL::NTH;
             *tiles = (int)n;
-            hipLaunchKernelGGL((k_energy_grad_gen<T, NS>), dim3((unsigned)(batch * n)), dim3(TL::NTH), 0, st, g,
-                               kd.gen->ns, k, (const T*)m, mask, (T*)grad, (T*)c, (T*)F, part);
+            for (long long t0 = 0; t0 < batch * n; t0 += most)
+                hipLaunchKernelGGL((k_energy_grad_gen<T, NS>), dim3((unsigned)std::min(most, batch * n - t0)),
+                                   dim3(TL::NTH), 0, st, g, kd.gen->ns, (int)t0, k, (const T*)m, mask, (T*)grad, (T*)c,
+                                   (T*)F, part);
         });
     };
     if (f64)
@@ -533,9 +536,15 @@ hipError_t launch_tangent_hvp_gen(const Geo& g, const CoefD& kd, bool f64, bool 
             constexpr int NS = decltype(nsc)::value;
             with_tile<T, NS>(g, (long long)batch * nvec, [&](auto tl) {
                 using TL = std::remove_pointer_t<decltype(tl)>;
-                hipLaunchKernelGGL((k_tangent_hvp_gen<T, FR, NS, TL>),
-                                   dim3((unsigned)(batch * gen_tiles<TL>(g) * nvec)), dim3(TL::NTH), 0, st, g, k,
-                                   (const T*)m, (const T*)c, mask, nvec, vbs, (const T*)V, (T*)W, done);
+                // vectors a launch
+                const long long most = std::max(1LL, LAUNCH_THREADS / (batch * gen_tiles<TL>(g) * TL::NTH));
+                for (long long j0 = 0; j0 < nvec; j0 += most) {
+                    const int nj = (int)std::min(most, nvec - j0);
+                    const size_t o = (size_t)j0 * (FR ? 2 : 3) * g.N;
+                    hipLaunchKernelGGL((k_tangent_hvp_gen<T, FR, NS, TL>),
+                                       dim3((unsigned)(batch * gen_tiles<TL>(g) * nj)), dim3(TL::NTH), 0, st, g, k,
+                                       (const T*)m, (const T*)c, mask, nj, vbs, (const T*)V + o, (T*)W + o, done);
+                }
             });
         });
     };

@@ -4,6 +4,7 @@
 // Every kernel stages a (TX+4) x (TY+4) tile of 3-vectors in LDS (periodic
 // wrap at the halo) and evaluates the three-shell stencil of the spin
 // Hamiltonian (Methods, Eq. param-hamiltonian) at one site per thread.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -462,10 +463,29 @@ hipError_t launch_param_grad_apply(const Geo& g, int ns, bool f64, int batch, co
 hipError_t launch_tangent_hvp(const Geo& g, const CoefD& kd, bool f64, bool frame, int batch, const void* m,
                               const void* c, const uint8_t* mask, int nvec, const void* V, void* W,
                               DoneFlags done, hipStream_t st, int variant, long long vbs) {
-    if (kd.gen) return launch_tangent_hvp_gen(g, kd, f64, frame, batch, m, c, mask, nvec, vbs, V, W, done, st);
-    if (frame) return launch_hvp_frame(variant, g, kd, f64, batch, m, c, mask, nvec, V, W, done, st, vbs);
-    if (vbs > 0 && vbs != (long long)nvec * 3 * g.N) return hipErrorInvalidValue;
-    return launch_hvp_ambient(g, kd, f64, batch, m, c, mask, nvec, V, W, done, st);
+    if (vbs <= 0) vbs = (long long)nvec * (frame ? 2 : 3) * g.N;
+    // lattices a launch: no kernel spends more than four times NT threads on a
+    // tile and vector
+    const long long most = std::max(1LL, LAUNCH_THREADS / (4LL * NT * g.tiles * nvec));
+    const size_t es = f64 ? sizeof(double) : sizeof(float);
+    const size_t sm = es * 3 * g.N, sc = es * g.N, sv = es * (size_t)vbs;
+    for (long long b0 = 0; b0 < batch; b0 += most) {
+        const int nb = (int)std::min(most, batch - b0);
+        const void *mb = (const char*)m + sm * b0, *cb = (const char*)c + sc * b0, *Vb = (const char*)V + sv * b0;
+        void* Wb = (char*)W + sv * b0;
+        const uint8_t* mk = mask ? mask + (size_t)g.N * b0 : nullptr;
+        const DoneFlags db(done.p ? done.p + done.stride * b0 : nullptr, done.stride);
+        hipError_t e;
+        if (kd.gen)
+            e = launch_tangent_hvp_gen(g, kd, f64, frame, nb, mb, cb, mk, nvec, vbs, Vb, Wb, db, st);
+        else if (frame)
+            e = launch_hvp_frame(variant, g, kd, f64, nb, mb, cb, mk, nvec, Vb, Wb, db, st, vbs);
+        else
+            e = vbs == (long long)nvec * 3 * g.N ? launch_hvp_ambient(g, kd, f64, nb, mb, cb, mk, nvec, Vb, Wb, db, st)
+                                                 : hipErrorInvalidValue;
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_hessian_apply(const Geo& g, const CoefD& kd, bool f64, int batch, int nvec, const void* V,
