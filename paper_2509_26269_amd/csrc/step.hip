@@ -364,6 +364,8 @@ __global__ __launch_bounds__(GNT) void k_step_gram(StepArgs a, const double* __r
 // recursion on one thread, 9.0 with an entry a lane and the dot products, now 7.8
 // (10.6 with 8 pairs).
 constexpr int CTN = 1024;  // threads
+// two entries of a row; the caller's state may be aligned to doubles only
+typedef double pair8 __attribute__((ext_vector_type(2), aligned(8)));
 __global__ __launch_bounds__(CTN) void k_step_ctrl(StepArgs a, StepPtrs P, double* __restrict__ out, StepBatch B) {
     P = member_ptrs(P, B);
     out += 2 * blockIdx.y;
@@ -385,7 +387,6 @@ __global__ __launch_bounds__(CTN) void k_step_ctrl(StepArgs a, StepPtrs P, doubl
     const int ne = nv * (nv + 1) / 2;  // and one more: |F_mmf|^2
     const int lane = wlane(), wv = threadIdx.x / WL;
     static_assert((SPART + WE - 1) / WE <= CTN / WL && SPART <= CTN, "waves for all entries, a thread for each");
-    static_assert(SPART % 2 == 0, "pairs of entries are 16-byte aligned");
     const int chunks = (ne + WE) / WE, parts = (CTN / WL) / chunks;
     const int chunk = wv % chunks, part = wv / chunks;
     {
@@ -395,10 +396,10 @@ __global__ __launch_bounds__(CTN) void k_step_ctrl(StepArgs a, StepPtrs P, doubl
             const double* pg = P.pgram + e;
             constexpr int U = 16;  // rows in flight
             for (int b0 = part; b0 < P.nblk; b0 += U * parts) {
-                double2 x[U];
+                pair8 x[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    x[u] = *(const double2*)(pg + (size_t)min(b0 + u * parts, P.nblk - 1) * SPART);
+                    x[u] = *(const pair8*)(pg + (size_t)min(b0 + u * parts, P.nblk - 1) * SPART);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const bool in = b0 + u * parts < P.nblk;
