@@ -138,22 +138,13 @@ int tuned_variant(const moto_plan p, moto_dtype dt, int batch, int nvec) {
     return -1;
 }
 
-// Offsets of the first ns shells of the triangular lattice (every lattice
-// vector dx a1 + dy a2, |.|^2 = dx^2 + dx dy + dy^2, grouped by length in
-// increasing order), copied from the compile-time table the kernels use,
-// and the halo they need (largest |dx|, |dy|).
+// Number and reach of the first ns shells of the triangular lattice; couplings zero.
 bool shell_table(int ns, GenShells* t) {
     if (ns < 1 || ns > GEN_MAX_SHELLS) return false;
     const ShellGeom& G = kShellGeom;
     int R = 0;
-    for (int s = 0; s <= ns; ++s) t->start[s] = G.start[s];
-    for (int o = 0; o < G.start[ns]; ++o) {
-        t->dx[o] = G.dx[o];
-        t->dy[o] = G.dy[o];
-        R = std::max(R, std::max(std::abs((int)G.dx[o]), std::abs((int)G.dy[o])));
-    }
+    for (int o = 0; o < G.start[ns]; ++o) R = std::max(R, std::max(std::abs((int)G.dx[o]), std::abs((int)G.dy[o])));
     t->ns = ns;
-    t->n_off = G.start[ns];
     t->R = R;
     for (int s = 0; s < GEN_MAX_SHELLS; ++s) t->cJ[s] = 0.0;
     return R <= GEN_RMAX;
@@ -224,7 +215,7 @@ moto_status moto_plan_create(const moto_hamiltonian* h, moto_plan* out) {
     p->k.gen = h->n_shells > 3 ? &p->gen : nullptr;
     double sj = 0.0, sd = 0.0;
     for (int s = 0; s < h->n_shells; ++s) {
-        const int cnt = p->gen.start[s + 1] - p->gen.start[s];
+        const int cnt = kShellGeom.start[s + 1] - kShellGeom.start[s];
         sj += cnt * std::fabs(h->J[s]);
         sd += cnt * std::fabs(h->D[s]);
     }

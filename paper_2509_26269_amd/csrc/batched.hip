@@ -123,7 +123,7 @@ constexpr int BRCH = 64;  // rows per staged chunk of the Gram reductions
 // LDS of the tile loops for one tile shape (TXV x 256 / TXV)
 template <int TXV>
 struct BTiles {
-    HvpLDS<float, true, TXV> hv;
+    HvpLDS<float, TXV> hv;
     TileLDS<double, TXV> te;
 };
 
@@ -158,16 +158,13 @@ __device__ __forceinline__ double b_energy_t(const BArgs& a, const BSearch& s, B
     k.cD = a.k.cD;
     k.cK = a.k.cK;
     for (int q = 0; q < 3; ++q) k.B[q] = a.k.B[q];
-    double v[NPART];
-#pragma unroll
-    for (int q = 0; q < NPART; ++q) v[q] = 0.0;
+    double e[1] = {0.0};
     const int ntx = (s.g.Lx + SHP::X - 1) / SHP::X, nty = (s.g.Ly + SHP::Y - 1) / SHP::Y;
     for (int t = 0; t < ntx * nty; ++t) {
         const int tx0 = (t % ntx) * SHP::X, ty0 = (t / ntx) * SHP::Y;
         energy_tile<double, TXV>(b_tiles<TXV>(sh).te, s.g, k, s.m, s.mask, nullptr, s.c64, want_F ? s.F : nullptr,
-                                 tx0, ty0, v);
+                                 tx0, ty0, e[0]);
     }
-    double e[1] = {v[0]};
     wg_sum<1>(e, sh.red);
     return e[0];
 }
@@ -189,7 +186,7 @@ __device__ __forceinline__ void b_hvp_t(const BArgs& a, const BSearch& s, BShare
     const int ntx = (s.g.Lx + SHP::X - 1) / SHP::X, nty = (s.g.Ly + SHP::Y - 1) / SHP::Y;
     for (int t = 0; t < ntx * nty; ++t) {
         const int tx0 = (t % ntx) * SHP::X, ty0 = (t / ntx) * SHP::Y;
-        tangent_hvp_tile<float, true, TXV>(b_tiles<TXV>(sh).hv, s.g, k, s.m32, s.c32, s.mask, BMB, W, HW, tx0,
+        tangent_hvp_tile<float, TXV>(b_tiles<TXV>(sh).hv, s.g, k, s.m32, s.c32, s.mask, BMB, W, HW, tx0,
                                            ty0);
     }
     __syncthreads();

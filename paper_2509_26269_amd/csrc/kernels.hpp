@@ -13,23 +13,20 @@ namespace moto {
 constexpr int NPART = 11;
 
 // Stencil coefficients in FP64 (cast to the kernel precision at launch).
-// Shell table of a Hamiltonian with more than three exchange shells: the
-// lattice offsets of every shell (sorted by distance, shell s = offsets
-// [start[s], start[s+1])), the largest |dx|, |dy| (the tile halo) and the
-// stencil coefficients cJ[s] = -2 J_s.
+// Exchange of a Hamiltonian with more than three shells: their number, the largest
+// |dx|, |dy| of a bond and the stencil coefficients cJ[s] = -2 J_s.
 constexpr int GEN_MAX_SHELLS = MOTO_MAX_SHELLS;
 constexpr int GEN_MAX_OFF = 448;
 constexpr int GEN_RMAX = 12;
 struct GenShells {
-    int ns, n_off, R;
-    int start[GEN_MAX_SHELLS + 1];
-    signed char dx[GEN_MAX_OFF], dy[GEN_MAX_OFF];
+    int ns, R;
     double cJ[GEN_MAX_SHELLS];
 };
 
-// The same offsets as a compile-time table (the shell geometry is fixed;
-// only the couplings vary), so that the general-shell kernels address LDS
-// with immediate offsets.  Shell s: squared length = the s-th smallest
+// The lattice offsets of every shell, sorted by distance (shell s = offsets
+// [start[s], start[s+1])), as a compile-time table (only the couplings vary), so
+// that the general-shell kernels address LDS with immediate offsets.  Shell s:
+// squared length = the s-th smallest
 // value of dx^2 + dx dy + dy^2 > 0 over |dx|, |dy| <= GEN_RMAX.
 struct ShellGeom {
     int n_off;

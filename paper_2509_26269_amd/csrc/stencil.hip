@@ -28,59 +28,6 @@ __device__ __forceinline__ TileIdx tile_of(const Geo& g, int id) {
     return r;
 }
 
-// --------------------------------------------------------------------------
-// Energy, gradient, c, F and parameter partials.
-// Sums (FP64) over the sites of
-//   [e_i, -m.S_0, -m.S_1, -m.S_2, m.Q_0, m.Q_1, m.Q_2, -m_z^2, -m_x, -m_y, -m_z]
-// with e_i = 1/2 m_i.(A m)_i - B.m_i, so that E = sum_i e_i and
-// dE/dJ_s = -sum_i m_i.S_s, dE/dD_s = sum_i m_i.Q_s, dE/dK = -sum m_z^2,
-// dE/dB = -sum m.  NP: how many of them the caller asked for (0 none, 1 the
-// energy, NPART all).  The parameter sums cost more than the field itself
-// (the unit-strength shells again and eleven block reductions): on 64 x
-// 128x128 FP64 states with all vector outputs the call took 44 us with them
-// always formed.
-// --------------------------------------------------------------------------
-template <class T, int NP>
-__device__ __forceinline__ void energy_site(const TileLDS<T>& t, int cx, int cy, int s, const Geo& g, const Coef<T>& k,
-                                            const uint8_t* __restrict__ mk, T* __restrict__ gb, T* __restrict__ cb,
-                                            T* __restrict__ fb, double* v) {
-    T a[3];
-    apply_A_tile(t, cx, cy, k, a);
-    const T mi[3] = {t.u[0][cy][cx], t.u[1][cy][cx], t.u[2][cy][cx]};
-    const T gi[3] = {a[0] - k.B[0], a[1] - k.B[1], a[2] - k.B[2]};
-    const T ci = mi[0] * gi[0] + mi[1] * gi[1] + mi[2] * gi[2];
-    const size_t N = g.N;
-    if (gb) {
-        gb[s] = gi[0];
-        gb[N + s] = gi[1];
-        gb[2 * N + s] = gi[2];
-    }
-    if (cb) cb[s] = ci;
-    if (fb) {
-        const bool act = mk == nullptr || mk[s] != 0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) fb[c * N + s] = act ? -(gi[c] - ci * mi[c]) : T(0);
-    }
-    if constexpr (NP > 0) {
-        const double mam = (double)mi[0] * a[0] + (double)mi[1] * a[1] + (double)mi[2] * a[2];
-        const double bm = (double)k.B[0] * mi[0] + (double)k.B[1] * mi[1] + (double)k.B[2] * mi[2];
-        v[0] = 0.5 * mam - bm;
-    }
-    if constexpr (NP == NPART) {
-        T S[3][3], Q[3][3];
-        shell_sums(t, cx, cy, S, Q);
-#pragma unroll
-        for (int sh = 0; sh < 3; ++sh) {
-            v[1 + sh] = -((double)mi[0] * S[sh][0] + (double)mi[1] * S[sh][1] + (double)mi[2] * S[sh][2]);
-            v[4 + sh] = (double)mi[0] * Q[sh][0] + (double)mi[1] * Q[sh][1] + (double)mi[2] * Q[sh][2];
-        }
-        v[7] = -(double)mi[2] * mi[2];
-        v[8] = -(double)mi[0];
-        v[9] = -(double)mi[1];
-        v[10] = -(double)mi[2];
-    }
-}
-
 // spins of one tile and its halo (tid: thread among the tile's NT)
 template <class T>
 __device__ __forceinline__ void stage_spins(TileLDS<T>& t, const Geo& g, const T* __restrict__ mb, int tx0, int ty0,
@@ -138,7 +85,7 @@ __global__ __launch_bounds__(NT) void k_energy_grad(Geo g, Coef<T> k, const T* _
 #pragma unroll
     for (int q = 0; q < NP; ++q) v[q] = 0.0;
     if (x < g.Lx && y < g.Ly)
-        energy_site<T, NP>(t, lx + HALO, ly + HALO, x + g.Lx * y, g, k, mask ? mask + off1 : nullptr,
+        energy_site<T, NP, TX>(t, lx + HALO, ly + HALO, x + g.Lx * y, g, k, mask ? mask + off1 : nullptr,
                            grad ? grad + off3 : nullptr, cout ? cout + off1 : nullptr, F ? F + off3 : nullptr, v);
     if constexpr (NP > 0) {
         block_sum<NP>(v, red);
@@ -180,7 +127,7 @@ __global__ __launch_bounds__(ONE_WG_TILES * NT) void k_energy_grad_wg(Geo g, Coe
 #pragma unroll
     for (int q = 0; q < NP; ++q) v[q] = 0.0;
     if (x < g.Lx && y < g.Ly)
-        energy_site<T, NP>(t[w], lx + HALO, ly + HALO, x + g.Lx * y, g, k, mask ? mask + off1 : nullptr,
+        energy_site<T, NP, TX>(t[w], lx + HALO, ly + HALO, x + g.Lx * y, g, k, mask ? mask + off1 : nullptr,
                            grad ? grad + off3 : nullptr, cout ? cout + off1 : nullptr, F ? F + off3 : nullptr, v);
     if constexpr (NP > 0) {
 #pragma unroll
