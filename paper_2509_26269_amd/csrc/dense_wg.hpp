@@ -1235,7 +1235,8 @@ __device__ bool orth_small_body(int mb, int nq, double drop, const double* G, do
         }
         wsync();
     } else {
-        // rebuild D M D (the factorisation overwrote it) and drop directions
+        // rebuild D M D (the LDS form of the factorisation overwrites it) and
+        // drop directions
         for2<LEAN>(mb, mb, [&](int c, int r) {
             A[r * LD + c] = (G[c * nrow + nq + r] - Mq[r * MBL + c]) * dsc[r] * dsc[c];
         });

@@ -1,6 +1,7 @@
-// hvp.hip -- frame-layout tangent Hessian-vector product (Methods, HVP
+// hvp.hip -- tangent Hessian-vector product of up to three shells (Methods, HVP
 // operator mode): W_j = M H(m) M V_j with (H v)_i = P_i (A v)_i - c_i v_i and
-// tangent vectors stored as two coordinates in the per-site frame (e1, e2).
+// tangent vectors stored as two coordinates in the per-site frame (e1, e2), or
+// ambient (always the gather).
 // This is the memory-bound kernel of the inner layer: 12 bytes of spins plus
 // 16 bytes per vector and site (FP32).
 //
@@ -13,14 +14,17 @@
 //                  lines); NVP vectors staged per pass with one frame build per
 //                  site; each thread owns one column and 4 rows and sweeps the
 //                  input rows once (register sliding window);
-//   gather:        tiles of 32 x 8 again, for launches too small to fill the
-//                  chip with strips: the march's sums with one barrier;
+//   gather:        tiles of 32 x 8 again, a whole vector's tile staged under one
+//                  barrier; in the march's order of sums for launches where
+//                  latency counts or the march idles lanes, in the tiled
+//                  kernels' for rows of under 4 or over 512 sites and the
+//                  ambient layout;
 //   march<NVP>:    one workgroup per full-width strip of rows, marching down
 //                  the strip one input row at a time with the accumulators of
 //                  five output rows in registers (each input element is read
 //                  and converted once; see the kernel).
 // All but the first order the blocks so that consecutive tiles of a lattice
-// run on the same XCD: workgroups are dealt round-robin to the 8 XCDs, each
+// run on the same XCD (all but the gather only on grids that divide by eight): workgroups are dealt round-robin to the 8 XCDs, each
 // with its own L2, and halo rows re-read by the next tile then hit that L2
 // instead of HBM.  The autotuner in the host API times the variants on the
 // caller's shape and keeps the fastest.

@@ -3,8 +3,9 @@
 // 360 bonds per site; Supplementary Note 4, Table S1).
 //
 // With hundreds of offsets per site the stencil is bound by multiply-adds, not
-// by HBM: a workgroup stages a tile with the halo of its disc of bonds in LDS
-// and convolves it row by row.  The spin Hamiltonian is the one of the
+// by HBM: a workgroup stages a tile with the halo of its disc of bonds in LDS and
+// convolves it row by row (the HVP) or adds it up shell by shell (the energies,
+// which keep the smaller rounding error).  The spin Hamiltonian is the one of the
 // three-shell kernels (Methods, Eq. param-hamiltonian): exchange on every
 // shell, interfacial DMI on the nearest-neighbour shell, uniaxial anisotropy,
 // Zeeman field.
@@ -143,10 +144,12 @@ __device__ __forceinline__ void disc_rows(const T* __restrict__ base, const GenC
 // with couplings from LDS (1725 multiply-adds a site-vector instead of 1083,
 // and a quarter as many LDS reads again), a workgroup taking the vectors one
 // after another.  us of the HVP, before and now, 35 shells: 64 x 128x128 x 4 FP32
-// 471 and 161 (115 for the multiply-adds alone at the vector rate; 186 with each
+// 471 and 162 (115 for the multiply-adds alone at the vector rate; 186 with each
 // row's window read in front of its own terms, the tile staged four sites at a
-// time and stores by the field's owner), FP64 1137 and 267; one 128x128 state x 4
-// FP32 209 and 20; 16x16 x 1 53 and 20.
+// time and stores by the field's owner), FP64 1137 and 241; one 128x128 state x 4
+// FP32 212 and 20; 16x16 x 1 53 and 20.  A zero coupling of the disc still meets
+// the sites of the plan's rows beyond its shells (up to 11 along the row), so a
+// non-finite vector entry shows there too, as it did in the square.
 template <class T, int NS, class TL>
 __device__ __forceinline__ void disc_field(const TL& L, int lx0, int ly0, const GenCoef<T, NS>& k,
                                            T (&a)[TL::HSP][3]) {

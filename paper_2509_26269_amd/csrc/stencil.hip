@@ -1,8 +1,9 @@
-// stencil.hip -- lattice kernels: energy/gradient, tangent HVP, Euclidean
-// Hessian apply, mixed parameter derivatives, topological charge.
+// stencil.hip -- lattice kernels: energy/gradient, Euclidean Hessian apply, mixed
+// parameter derivatives, topological charge; the entry to the tangent HVP's
+// kernels and to those for more than three shells.
 //
-// Every kernel stages a (TX+4) x (TY+4) tile of 3-vectors in LDS (periodic
-// wrap at the halo) and evaluates the three-shell stencil of the spin
+// Every kernel of the stencil stages a (TX+4) x (TY+4) tile of 3-vectors in LDS
+// (periodic wrap at the halo) and evaluates the three-shell sums of the spin
 // Hamiltonian (Methods, Eq. param-hamiltonian) at one site per thread.
 #include <algorithm>
 #include <mutex>

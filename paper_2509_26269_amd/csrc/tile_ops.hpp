@@ -1,6 +1,7 @@
-// tile_ops.hpp -- per-tile bodies of the lattice kernels, shared by the
-// one-launch-per-step kernels (one tile per workgroup) and the persistent
-// batched search (one workgroup looping over the tiles of its lattice).
+// tile_ops.hpp -- per-site and per-tile bodies of the lattice kernels: the energy
+// of a site, shared by the energy kernels (one tile per workgroup) and the
+// persistent batched search, and the tiles that one workgroup of that search
+// loops over.
 //
 // A tile is TX x TY output sites (TileShape; 32 x 8 unless a caller picks
 // another shape); the workgroup stages the (TX+4) x (TY+4)
