@@ -75,12 +75,13 @@ __device__ __forceinline__ int xcd_order(bool remap) {
 
 // The same for any grid, XCD x taking one more while x < gridDim.x % 8.  The
 // gather HVP needs it: halo rows cross L2s as soon as its workgroups do not
-// divide by eight, and a launch that its estimate gives to it was then up to 1.3
-// times slower than the march (us of the gather before and now: FP32 283 x 96x96
-// x 3 70 and 40, 42 x 96x492 x 2 44 and 24; FP64 28 x 400x114 32 and 23; means
-// of 399 and 446 such shapes 0.82 and 0.90).  The march keeps the order above: its
-// last workgroups may be strips past the last row, and one or two of those
-// beyond a full round of 256 cost nothing only at the end (7 x 300x300, four
+// divide by eight.  Launches that its estimate gives to it were then up to 1.3
+// times slower than the march, and masked ambient ones up to 1.4 times slower than
+// the one workgroup a tile that they had (us of the gather before and now: FP32
+// 283 x 96x96 x 3 70 and 40, 42 x 96x492 x 2 44 and 24; FP64 28 x 400x114 32 and
+// 23; means of 399 and 446 such shapes 0.82 and 0.90).  The march keeps the order
+// above: its last workgroups may be strips past the last row, and one or two of
+// those beyond a full round of 256 cost nothing only at the end (7 x 300x300, four
 // vectors a group: 25 us, 48 with them spread).
 __device__ __forceinline__ int xcd_runs() {
     const int x = blockIdx.x % 8, per = gridDim.x / 8, rest = gridDim.x % 8;

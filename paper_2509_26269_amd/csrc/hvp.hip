@@ -932,7 +932,10 @@ __global__ __launch_bounds__(NT, MORDER && sizeof(T) == 4 ? 8 : 1) void k_hvp_ga
     constexpr int SX = TX + 2 * HALO, SS = SX * (TY + 2 * HALO);
     constexpr int Q = (SS + NT - 1) / NT;  // staged sites per thread
     __shared__ T su[3][SS];
-    const int lid = FRAME ? xcd_runs() : xcd_order(true);
+    // FP32 ambient without a mask keeps the other order: it would take 73 registers
+    // for 70 and a wave less on a SIMD (4 - 8 % on grids that divide by eight)
+    constexpr bool RUNS = FRAME || MASKED || sizeof(T) == 8;
+    const int lid = RUNS ? xcd_runs() : xcd_order(true);
     const int grp = lid % ngroups;
     const int rest = lid / ngroups;
     const int tiles = tiles_x * tiles_y;
@@ -960,6 +963,8 @@ __global__ __launch_bounds__(NT, MORDER && sizeof(T) == 4 ? 8 : 1) void k_hvp_ga
     int ss[Q];
     bool on[Q];
     T raw[Q][DV], f1[Q][3], f2[Q][3];
+    // masked vectors are read at active sites only where the tiled kernels did so
+    auto read = [&](int q) { return MORDER || !MASKED || on[q]; };
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const int i = threadIdx.x + q * NT;
@@ -970,7 +975,7 @@ __global__ __launch_bounds__(NT, MORDER && sizeof(T) == 4 ? 8 : 1) void k_hvp_ga
         if (i < SS) {
             if constexpr (MASKED) on[q] = mk[ss[q]] != 0;
 #pragma unroll
-            for (int d = 0; d < DV; ++d) raw[q][d] = Vj[d * N + ss[q]];
+            for (int d = 0; d < DV; ++d) raw[q][d] = read(q) ? Vj[d * N + ss[q]] : T(0);
             if constexpr (FRAME) frame(mx[ss[q]], my[ss[q]], mz[ss[q]], f1[q], f2[q]);
         }
     }
@@ -1007,7 +1012,7 @@ __global__ __launch_bounds__(NT, MORDER && sizeof(T) == 4 ? 8 : 1) void k_hvp_ga
             for (int q = 0; q < Q; ++q)
                 if ((int)threadIdx.x + q * NT < SS)
 #pragma unroll
-                    for (int d = 0; d < DV; ++d) raw[q][d] = Vj[d * N + ss[q]];
+                    for (int d = 0; d < DV; ++d) raw[q][d] = read(q) ? Vj[d * N + ss[q]] : T(0);
         }
         __syncthreads();
         if (out) {
@@ -1229,12 +1234,15 @@ static void go_march2(const Geo& g, const CoefD& kd, int batch, const void* m, c
 
 // vectors per workgroup: one while the tiles alone do not fill the chip, then
 // up to four to share the frames (three vectors of 24 x 93x61 in FP64: 9.7 us
-// one by one, 8.9 together; 12 of one 128x128: 5.3 and 6.4), in even groups
+// one by one, 8.9 together; 12 of one 128x128: 5.3 and 6.4), in even groups.
+// Masked ambient vectors, of which little is read, up to sixteen: a group's own
+// reads are its mask and spins (7 x 900x352 x 6 FP64 188 us in groups of three,
+// 174 in one; 191 x 34x86 x 13 156 in fours and 130).
 template <class T, bool FRAME, bool MORDER>
 static void go_gather(const Geo& g, const CoefD& kd, int batch, const void* m, const void* c, const uint8_t* mask,
                       int nvec, long long vbs, const void* V, void* W, DoneFlags done, hipStream_t st) {
     const long long tiles = (long long)batch * g.tiles;
-    const int want = (int)std::min(4LL, std::max(1LL, tiles * nvec / (sizeof(T) == 8 ? 512 : 1536)));
+    const int want = (int)std::min(!FRAME && mask ? 16LL : 4LL, std::max(1LL, tiles * nvec / (sizeof(T) == 8 ? 512 : 1536)));
     const long long most = std::max(1LL, LAUNCH_THREADS / (NT * tiles));  // groups that a launch can have
     const int ngroups = (int)std::min<long long>((nvec + want - 1) / want, most);
     const int nvg = (nvec + ngroups - 1) / ngroups;
